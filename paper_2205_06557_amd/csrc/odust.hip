@@ -44,6 +44,7 @@ constexpr int kPad = 256;
 constexpr int kMaxSplitSingle = 4;             // source splits of one system's pair sum
 constexpr int kConfNr = 32, kConfNz = 32;      // intervals of the confinement grid along r, z
 constexpr int kConfNodes = (kConfNr + 1) * (kConfNz + 1);
+constexpr int kConfSlices = 32;                // slices of the ions in the grid's sums
 
 thread_local std::string g_err;
 
@@ -433,7 +434,8 @@ bool fit_confinement(const double* grid, double* coef)
 }
 
 // Confinement field of one system (Appendix A), from its ions at X, Y, Z:
-// the grid on the device into dbuf (kConfNodes doubles), the fit on the host.
+// the grid on the device into dbuf (kConfNodes * kConfSlices doubles), the fit
+// on the host.
 // Fills grid (dimensionless potentials), the field of the pair kernels and
 // e E_out at every grain for the force of Eq. (1).  Synchronises the stream.
 template <typename T>
@@ -441,11 +443,18 @@ od_status setup_confinement(hipStream_t st, const T* X, const T* Y, const T* Z, 
                             double* dbuf, SysConsts& c, double Te, std::vector<double>& grid)
 {
     const double R = c.pu.R, Hh = 0.5 * c.pu.H;
-    odk::conf_grid_kernel<T><<<kConfNodes, 256, 0, st>>>(X, Y, Z, N, c.pa.Cd, R, Hh, kConfNr, kConfNz, dbuf);
+    static_assert((kConfNz + 1) % odk::kConfRow == 0, "a block's nodes share k");
+    const int slices = (int)std::min<int64_t>(kConfSlices, (N + 1023) / 1024);
+    odk::conf_grid_kernel<T><<<dim3(kConfNodes / odk::kConfRow, slices), 256, 0, st>>>(X, Y, Z, N, R, Hh, kConfNr,
+                                                                                     kConfNz, dbuf);
     HIPCHK(hipGetLastError());
-    grid.assign(kConfNodes, 0.0);
-    HIPCHK(hipMemcpyAsync(grid.data(), dbuf, kConfNodes * sizeof(double), hipMemcpyDeviceToHost, st));
+    std::vector<double> part((size_t)kConfNodes * slices);
+    HIPCHK(hipMemcpyAsync(part.data(), dbuf, part.size() * sizeof(double), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
+    grid.assign(kConfNodes, 0.0);
+    for (int k = 0; k < slices; ++k)
+        for (int g = 0; g < kConfNodes; ++g) grid[g] += part[(size_t)k * kConfNodes + g];
+    for (int g = 0; g < kConfNodes; ++g) grid[g] = 1.0 - c.pa.Cd * grid[g];
     odk::ConfField& cf = c.pa.cf;
     if (!fit_confinement(grid.data(), cf.c)) return fail(OD_ENUMERIC, "confinement fit failed");
     cf.on = 1;
@@ -732,7 +741,7 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
     }
     st = read_status(s);
     if (st == OD_OK && (sim->flags & OD_FLAG_CONFINEMENT)) {
-        double* dbuf = (double*)dev_alloc(s, kConfNodes * sizeof(double));
+        double* dbuf = (double*)dev_alloc(s, (size_t)kConfNodes * kConfSlices * sizeof(double));
         if (!dbuf) st = fail(OD_ENOMEM, "device allocation of the confinement grid failed");
         SysConsts c;
         c.lam = s->lam; c.ds = s->ds; c.pa = s->pa; c.pu = s->pu; c.fa = s->fa;
