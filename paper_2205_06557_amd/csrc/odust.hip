@@ -124,9 +124,10 @@ struct od_system {
     int pair_kind = OD_PAIR_AUTO;
     bool sym = false;
     unsigned long long* acc_fix = nullptr;  // [3][Npad] int64 fixed-point pair sums
-    odk::SymItem* sym_items = nullptr;
+    odk::SymItem* sym_items = nullptr;      // in acc_fix's allocation
     int n_sym_items = 0;
-    // device memory
+    // device memory: one allocation (mem), cut into the buffers below
+    void* mem = nullptr;
     void* x = nullptr;
     void* v = nullptr;
     void* a = nullptr;
@@ -178,7 +179,6 @@ void free_cutoff(od_system* s)
 void free_sym(od_system* s)
 {
     dev_free(s, s->acc_fix);
-    dev_free(s, s->sym_items);
     s->acc_fix = nullptr;
     s->sym_items = nullptr;
     s->n_sym_items = 0;
@@ -194,16 +194,17 @@ od_status setup_sym(od_system* s)
     const int T = (int)(s->Npad / kPairBlock);
     std::vector<odk::SymItem> items;
     if (s->pa.ion_ion) items = sym_items(T);
-    s->acc_fix = (unsigned long long*)dev_alloc(s, 3 * (size_t)s->Npad * sizeof(unsigned long long));
-    if (!items.empty()) s->sym_items = (odk::SymItem*)dev_alloc(s, items.size() * sizeof(odk::SymItem));
-    if (!s->acc_fix || (!items.empty() && !s->sym_items)) {
+    const size_t totals = 3 * (size_t)s->Npad * sizeof(unsigned long long);      // a multiple of 256
+    s->acc_fix = (unsigned long long*)dev_alloc(s, totals + items.size() * sizeof(odk::SymItem));
+    if (!s->acc_fix) {
         free_sym(s);
         return fail(OD_ENOMEM, "device allocation of the symmetric pair sum failed");
     }
+    s->sym_items = (odk::SymItem*)((char*)s->acc_fix + totals);
     if (!items.empty())
         HIPCHK(hipMemcpyAsync(s->sym_items, items.data(), items.size() * sizeof(odk::SymItem),
                               hipMemcpyHostToDevice, s->stream));
-    HIPCHK(hipMemsetAsync(s->acc_fix, 0, 3 * (size_t)s->Npad * sizeof(unsigned long long), s->stream));
+    HIPCHK(hipMemsetAsync(s->acc_fix, 0, totals, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
     s->n_sym_items = (int)items.size();
     s->sym = true;
@@ -392,42 +393,57 @@ double ipow(double x, int k)
     return r;
 }
 
+// Householder QR of the (nodes x 15) design matrix of the fit, in the scaled
+// variables u = (k/nr)^2, v = (p/nz)^2.  The matrix is the same for every
+// system, so it is factored once per process (0.17 of the fit's 0.18 ms).
+struct ConfQr {
+    static constexpr int m = kConfNodes, n = 15;
+    std::vector<double> a;       // column major: the Householder vector of step j in [j, m) of column j, R above
+    double rdiag[n], vv[n];
+    bool ok = true;
+    ConfQr() : a((size_t)m * n)
+    {
+        for (int g = 0; g < m; ++g) {
+            const double r = (double)(g / (kConfNz + 1)) / kConfNr, z = (double)(g % (kConfNz + 1)) / kConfNz;
+            for (int j = 0; j < n; ++j) a[(size_t)j * m + g] = ipow(r * r, kTermU[j]) * ipow(z * z, kTermV[j]);
+        }
+        for (int j = 0; j < n && ok; ++j) {
+            double* h = &a[(size_t)j * m];
+            double nrm = 0.0;
+            for (int i = j; i < m; ++i) nrm += h[i] * h[i];
+            nrm = std::sqrt(nrm);
+            ok = nrm > 0.0;
+            rdiag[j] = h[j] > 0.0 ? -nrm : nrm;
+            h[j] -= rdiag[j];
+            vv[j] = 0.0;
+            for (int i = j; i < m; ++i) vv[j] += h[i] * h[i];
+            for (int k = j + 1; k < n; ++k) reflect(j, &a[(size_t)k * m]);
+        }
+    }
+    void reflect(int j, double* col) const
+    {
+        const double* h = &a[(size_t)j * m];
+        double dot = 0.0;
+        for (int i = j; i < m; ++i) dot += h[i] * col[i];
+        const double f = 2.0 * dot / vv[j];
+        for (int i = j; i < m; ++i) col[i] -= f * h[i];
+    }
+};
+
 // Least-squares fit of Eq. (A.3) to the confinement grid (node (k, p) at
-// index (kConfNz + 1) k + p), every node weighted alike: Householder QR of
-// the (nodes x 15) design matrix in the scaled variables u = (k/nr)^2,
-// v = (p/nz)^2, then back substitution.  False if the matrix is singular.
+// index (kConfNz + 1) k + p), every node weighted alike: the reflections of
+// the factored design matrix, then back substitution.  False if the matrix is
+// singular.
 bool fit_confinement(const double* grid, double* coef)
 {
-    const int m = kConfNodes, n = 15;
-    std::vector<double> A((size_t)m * n), b(grid, grid + m), rdiag(n);   // A column-major
-    for (int g = 0; g < m; ++g) {
-        const double r = (double)(g / (kConfNz + 1)) / kConfNr, z = (double)(g % (kConfNz + 1)) / kConfNz;
-        for (int j = 0; j < n; ++j) A[(size_t)j * m + g] = ipow(r * r, kTermU[j]) * ipow(z * z, kTermV[j]);
-    }
-    for (int j = 0; j < n; ++j) {
-        double* a = &A[(size_t)j * m];
-        double nrm = 0.0;
-        for (int i = j; i < m; ++i) nrm += a[i] * a[i];
-        nrm = std::sqrt(nrm);
-        if (!(nrm > 0.0)) return false;
-        const double alpha = a[j] > 0.0 ? -nrm : nrm;
-        a[j] -= alpha;                                  // Householder vector in a[j..m)
-        double vv = 0.0;
-        for (int i = j; i < m; ++i) vv += a[i] * a[i];
-        auto reflect = [&](double* col) {
-            double dot = 0.0;
-            for (int i = j; i < m; ++i) dot += a[i] * col[i];
-            const double f = 2.0 * dot / vv;
-            for (int i = j; i < m; ++i) col[i] -= f * a[i];
-        };
-        for (int k = j + 1; k < n; ++k) reflect(&A[(size_t)k * m]);
-        reflect(b.data());
-        rdiag[j] = alpha;
-    }
-    for (int j = n - 1; j >= 0; --j) {
+    static const ConfQr qr;
+    if (!qr.ok) return false;
+    std::vector<double> b(grid, grid + qr.m);
+    for (int j = 0; j < qr.n; ++j) qr.reflect(j, b.data());
+    for (int j = qr.n - 1; j >= 0; --j) {
         double t = b[j];
-        for (int k = j + 1; k < n; ++k) t -= A[(size_t)k * m + j] * coef[k];
-        coef[j] = t / rdiag[j];
+        for (int k = j + 1; k < qr.n; ++k) t -= qr.a[(size_t)k * qr.m + j] * coef[k];
+        coef[j] = t / qr.rdiag[j];
         if (!std::isfinite(coef[j])) return false;
     }
     return true;
@@ -444,7 +460,7 @@ od_status setup_confinement(hipStream_t st, const T* X, const T* Y, const T* Z, 
 {
     const double R = c.pu.R, Hh = 0.5 * c.pu.H;
     static_assert((kConfNz + 1) % odk::kConfRow == 0, "a block's nodes share k");
-    const int slices = (int)std::min<int64_t>(kConfSlices, (N + 1023) / 1024);
+    const int slices = (int)std::min<int64_t>(kConfSlices, std::max(1, N / 1024));
     odk::conf_grid_kernel<T><<<dim3(kConfNodes / odk::kConfRow, slices), 256, 0, st>>>(X, Y, Z, N, R, Hh, kConfNr,
                                                                                      kConfNz, dbuf);
     HIPCHK(hipGetLastError());
@@ -708,16 +724,26 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
     }
 
     const size_t vec = 3 * (size_t)s->Npad * s->esz;
-    s->x = dev_alloc(s, vec);
-    s->v = dev_alloc(s, vec);
-    s->a = dev_alloc(s, vec * (s->prec == OD_PREC_FP32 ? kMaxSplitSingle : 1));
-    s->ev = (uint8_t*)dev_alloc(s, (size_t)s->Npad);
-    s->lost = (int2*)dev_alloc(s, (size_t)odk::kSlots * odk::lost_cap(s->Npad / 256) * sizeof(int2));
-    s->ctl = (odk::Ctl*)dev_alloc(s, sizeof(odk::Ctl));
-    if (!s->x || !s->v || !s->a || !s->ev || !s->lost || !s->ctl) {
+    // One allocation for all of them: a hipMalloc and its hipFree cost about
+    // 0.1 ms, more than the initial state of 2^17 ions.
+    const size_t sizes[6] = {vec, vec,
+                             std::max(vec * (s->prec == OD_PREC_FP32 ? kMaxSplitSingle : 1), kConfNodes * sizeof(double)),
+                             (size_t)s->Npad,
+                             (size_t)odk::kSlots * odk::lost_cap(s->Npad / 256) * sizeof(int2), sizeof(odk::Ctl)};
+    size_t at[7] = {0};
+    for (int k = 0; k < 6; ++k) at[k + 1] = at[k] + (sizes[k] + 255) / 256 * 256;
+    s->mem = dev_alloc(s, at[6]);
+    if (!s->mem) {
         od_destroy(s);
-        return fail(OD_ENOMEM, "device allocation of %zu bytes failed", 3 * vec);
+        return fail(OD_ENOMEM, "device allocation of %zu bytes failed", at[6]);
     }
+    char* base = (char*)s->mem;
+    s->x = base + at[0];
+    s->v = base + at[1];
+    s->a = base + at[2];
+    s->ev = (uint8_t*)(base + at[3]);
+    s->lost = (int2*)(base + at[4]);
+    s->ctl = (odk::Ctl*)(base + at[5]);
     odk::Ctl h{};
     std::memset(&h, 0, sizeof h);
     for (int d = 0; d < n_dust; ++d) h.Q[d] = dust[d].q0 / kQE;
@@ -741,8 +767,9 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
     }
     st = read_status(s);
     if (st == OD_OK && (sim->flags & OD_FLAG_CONFINEMENT)) {
-        double* dbuf = (double*)dev_alloc(s, (size_t)kConfNodes * kConfSlices * sizeof(double));
-        if (!dbuf) st = fail(OD_ENOMEM, "device allocation of the confinement grid failed");
+        // the grid's sums use the acceleration planes, which no step has
+        // written yet: at most 8.5 bytes per ion and one slice
+        double* dbuf = (double*)s->a;
         SysConsts c;
         c.lam = s->lam; c.ds = s->ds; c.pa = s->pa; c.pu = s->pu; c.fa = s->fa;
         const int64_t P = s->Npad;
@@ -753,10 +780,8 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
             const double* x = (const double*)s->x;
             st = setup_confinement<double>(s->stream, x, x + P, x + 2 * P, (int)s->N, dbuf, c, plasma->T_e, s->conf_grid);
         }
-        if (dbuf) {
-            (void)hipStreamSynchronize(s->stream);
-            dev_free(s, dbuf);
-        }
+        if (hipMemsetAsync(s->a, 0, sizes[2], s->stream) != hipSuccess && st == OD_OK)
+            st = fail(OD_EDEVICE, "clearing the accelerations failed");
         s->pa = c.pa;
         s->fa = c.fa;
     }
@@ -844,13 +869,8 @@ void od_destroy(od_system* s)
     drop_graph(s);
     free_cutoff(s);
     free_sym(s);
-    dev_free(s, s->x);
-    dev_free(s, s->v);
-    dev_free(s, s->a);
-    dev_free(s, s->ev);
-    dev_free(s, s->lost);
     dev_free(s, s->hist);
-    dev_free(s, s->ctl);
+    dev_free(s, s->mem);
     for (hipEvent_t e : s->evpool) (void)hipEventDestroy(e);
     delete s;
 }
