@@ -242,16 +242,24 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * on scheduling and is bitwise reproducible; it rounds differently from the
  * one-sided kernel.  A pair closer than about 4e-6 of the mean ion spacing
  * overflows the range and is reported as OD_ENUMERIC.
- * OD_PAIR_AUTO (the default) takes the symmetric kernel, which is the faster
- * one at every size (1.5x at 2^20, 1.8x at 2^18 and 2.4x at 2^12 ions on
- * MI355X).
+ * OD_PAIR_AUTO (the default) takes the symmetric sum, the faster one at every
+ * size, and for large systems (from 81,920 ions on, domains up to 24 r_De
+ * across) evaluates it as near pairs, one by one, plus a smooth far part on a
+ * grid in 64 bits.  That is the same all-pairs sum: the far part is within
+ * 1e-7 of the rms acceleration of the direct sum in 64 bits, below the FP32
+ * rounding of the direct kernel's pair terms, and is bitwise reproducible too
+ * (8x faster at 2^18 ions, 39x at 2^20).  Its memory, about 100 MB at 2^17 and
+ * 500 MB at 2^20 ions, is taken by the first step, or at creation where the
+ * system has an allocator of its own; where it is refused, and for the step
+ * after od_set_state puts ions outside the domain, the direct sum is used.
+ * OD_PAIR_SYMMETRIC always sums every pair directly.
  * The symmetric kernel needs 24 bytes per ion of accumulators.  FP64 systems
  * always use the one-sided kernel; a cutoff (od_set_cutoff) takes precedence
  * over either.  In test-particle mode (OD_FLAG_NO_ION_ION) the symmetric
  * setting runs no pair kernel at all: the step's tail adds the grain, drive
  * and confinement terms (the one-sided setting adds them in a pair kernel
  * without ion-ion terms, in FP64).  od_get_pair_kernel reports the kernel in
- * use. */
+ * use (OD_PAIR_SYMMETRIC for the split sum too). */
 #define OD_PAIR_AUTO 0
 #define OD_PAIR_ONE_SIDED 1
 #define OD_PAIR_SYMMETRIC 2

@@ -1,0 +1,786 @@
+// mesh.hpp -- the all-pairs ion-ion sum of large systems, split into near
+// pairs and a smooth far part on a grid (the split and its constants:
+// meshplan.hpp).  The direct sum costs N^2 / 2 pair terms however far apart
+// the ions are; here a pair is evaluated one by one only within r_c (a few ion
+// spacings) and everything else is a few thousand operations per ion, all of
+// it in 64 bits.
+//
+// Launch sequence of one step (all sizes fixed by the plan, so that a step can
+// be captured):
+//   mesh_bin_kernel      sort bin of every ion: column of kx x kx cells, slice
+//                        along z; arrival number within the bin (atomic)
+//   mesh_scan_kernel     per column, prefix sum over its bins
+//   mesh_cols_kernel     prefix over columns, each padded to whole 64-ion tiles
+//   mesh_place_kernel    ion index to its bin's slots, in arrival order
+//   mesh_order_kernel    slots of a bin put in ion order (arrival order depends
+//                        on scheduling, ion order does not); sorted positions
+//   mesh_box_kernel      bounding box of every 16 sorted ions
+//   mesh_spread_kernel   charges to the grid, one brick of cells per block, in
+//                        LDS as int64 fixed point (order-free)
+//   mesh_sum_kernel      overlapping brick margins added
+//   mesh_conv_kernel     Gaussian convolutions along x, y and z (64-bit MFMA)
+//   mesh_gather_kernel   far acceleration of every ion, from bricks in LDS
+//   mesh_near_kernel     near pairs; totals to the fixed-point planes that the
+//                        step's tail reads
+// Every sum has a fixed order or is an integer sum: results are reproducible
+// bit for bit.
+#pragma once
+
+#include <type_traits>
+
+#include "kernels.hpp"
+#include "meshplan.hpp"
+
+namespace odk {
+
+// Device buffers of one system's split (one arena, see mesh_bytes).
+struct MeshBufs {
+    int* key;              // [N] sort bin of each ion
+    int* arr;              // [N] arrival number in the bin
+    int* count;            // [bins] ions per bin; zero between steps
+    int* rel;              // [columns][nzb + 1] bin starts within the column
+    int* col;              // [columns + 1] first slot of each column
+    int* temp;             // [cap] ions in arrival order, -1 where a column is padded
+    int* idx;              // [cap] ion of each sorted slot, -1 for padding
+    float* s;              // [3][cap] sorted positions
+    float* box;            // [6][cap / 16] min x, y, z, max x, y, z
+    double* far;           // [3][cap] far part by sorted slot
+    double* green;         // [M][ng] Green's tables
+    float* near0;          // constant term of the near polynomial (mesh_zero_kernel)
+    double* q;             // grid charges
+    double* phi;           // far potential on the grid
+    double* t1;            // convolution scratch, mc grids each
+    double* t2;
+    unsigned long long* brick;  // brick sums (shares t1's memory)
+    int mc;                // Gaussians per convolution pass
+};
+
+__device__ __forceinline__ int mesh_cell(double x, double lo, double inv_h, int nc)
+{
+    return (int)fmin(fmax(floor((x - lo) * inv_h), 0.0), (double)(nc - 1));
+}
+
+__device__ __forceinline__ int mesh_zbin(double z, const MeshArgs& m)
+{
+    return (int)fmin(fmax(floor((z + m.Hh) * (m.inv_h * m.zsub)), 0.0), (double)(m.nzb - 1));
+}
+
+// Sort bin of every ion; also marks every slot empty.
+__global__ __launch_bounds__(256) void mesh_bin_kernel(const float* __restrict__ x, long long plane, MeshArgs m,
+                                                       MeshBufs b)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < m.cap) b.temp[i] = -1;
+    if (i >= m.N) return;
+    const int cx = mesh_cell(x[i], -m.R, m.inv_h, m.nc[0]) / m.kx;
+    const int cy = mesh_cell(x[plane + i], -m.R, m.inv_h, m.nc[1]) / m.kx;
+    const int key = (cy * m.ncx + cx) * m.nzb + mesh_zbin(x[2 * plane + i], m);
+    b.key[i] = key;
+    b.arr[i] = atomicAdd(&b.count[key], 1);
+}
+
+// One block per column: bin starts relative to the column; clears the counts.
+__global__ __launch_bounds__(256) void mesh_scan_kernel(MeshArgs m, MeshBufs b)
+{
+    __shared__ int wsum[4];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    int* cnt = b.count + (long long)blockIdx.x * m.nzb;
+    int* rel = b.rel + (long long)blockIdx.x * (m.nzb + 1);
+    int carry = 0;
+    for (int k0 = 0; k0 < m.nzb; k0 += 256) {
+        const int k = k0 + threadIdx.x;
+        const int v = k < m.nzb ? cnt[k] : 0;
+        int s = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(s, d, 64);
+            if (lane >= d) s += u;
+        }
+        if (lane == 63) wsum[wv] = s;
+        __syncthreads();
+        int before = carry;
+        for (int w = 0; w < wv; ++w) before += wsum[w];
+        if (k < m.nzb) {
+            rel[k] = before + s - v;
+            cnt[k] = 0;
+        }
+        carry += wsum[0] + wsum[1] + wsum[2] + wsum[3];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) rel[m.nzb] = carry;
+}
+
+// First slot of each column (one block).
+__global__ __launch_bounds__(1024) void mesh_cols_kernel(MeshArgs m, MeshBufs b)
+{
+    __shared__ int wsum[16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int ncol = m.ncx * m.ncy;
+    int carry = 0;
+    for (int k0 = 0; k0 < ncol; k0 += 1024) {
+        const int k = k0 + threadIdx.x;
+        const int v = k < ncol ? (b.rel[(long long)k * (m.nzb + 1) + m.nzb] + kMeshTile - 1) / kMeshTile * kMeshTile : 0;
+        int s = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(s, d, 64);
+            if (lane >= d) s += u;
+        }
+        if (lane == 63) wsum[wv] = s;
+        __syncthreads();
+        int before = carry, all = 0;
+        for (int w = 0; w < 16; ++w) {
+            if (w < wv) before += wsum[w];
+            all += wsum[w];
+        }
+        if (k < ncol) b.col[k] = before + s - v;
+        carry += all;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) b.col[ncol] = carry;
+}
+
+__device__ __forceinline__ int mesh_bin_start(const MeshArgs& m, const MeshBufs& b, int key)
+{
+    const int c = key / m.nzb;
+    return b.col[c] + b.rel[(long long)c * (m.nzb + 1) + (key - c * m.nzb)];
+}
+
+__global__ __launch_bounds__(256) void mesh_place_kernel(MeshArgs m, MeshBufs b)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < m.N) b.temp[mesh_bin_start(m, b, b.key[i]) + b.arr[i]] = i;
+}
+
+// Slot order within a bin by ion index; sorted positions.  Padding slots stand
+// outside the domain, more than r_c from every ion and near enough that the
+// near part's rounding at r_c times their distance is nothing.
+__global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict__ x, long long plane, MeshArgs m,
+                                                         MeshBufs b)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= b.col[m.ncx * m.ncy]) return;
+    const int i = b.temp[t];
+    if (i < 0) {
+        b.idx[t] = -1;
+        b.s[t] = (float)m.R + 2.0f;
+        b.s[m.cap + t] = (float)m.R + 2.0f;
+        b.s[2 * (long long)m.cap + t] = (float)m.Hh + 2.0f;
+        return;
+    }
+    const int key = b.key[i];
+    const int c = key / m.nzb, z = key - c * m.nzb;
+    const int* rel = b.rel + (long long)c * (m.nzb + 1);
+    const int s0 = b.col[c] + rel[z], s1 = b.col[c] + rel[z + 1];
+    int to = s0;
+    for (int k = s0; k < s1; ++k) to += b.temp[k] < i;
+    b.idx[to] = i;
+    b.s[to] = x[i];
+    b.s[m.cap + to] = x[plane + i];
+    b.s[2 * (long long)m.cap + to] = x[2 * plane + i];
+}
+
+// Bounding box of every 16 sorted ions (empty: an inverted box).
+__global__ __launch_bounds__(256) void mesh_box_kernel(MeshArgs m, MeshBufs b)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    if (t >= b.col[m.ncx * m.ncy]) return;     // a multiple of 64
+    const bool live = b.idx[t] >= 0;
+    const int ns = m.cap / kMeshSub;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float v = b.s[(long long)c * m.cap + t];
+        float lo = live ? v : 1.0e30f, hi = live ? v : -1.0e30f;
+#pragma unroll
+        for (int d = 1; d < kMeshSub; d <<= 1) {
+            lo = fminf(lo, __shfl_xor(lo, d, 64));
+            hi = fmaxf(hi, __shfl_xor(hi, d, 64));
+        }
+        if ((threadIdx.x & (kMeshSub - 1)) == 0) {
+            b.box[(long long)c * ns + t / kMeshSub] = lo;
+            b.box[(long long)(c + 3) * ns + t / kMeshSub] = hi;
+        }
+    }
+}
+
+// Window weights of the ten nodes around a coordinate u cells from its cell's
+// lower edge, and their derivatives along the axis per cell when DER; z = ((u + 4 - k) / 5.
+template <bool DER>
+__device__ __forceinline__ double mesh_window(const MeshArgs& m, double u, int k, double& der)
+{
+    const double z = (u + (4.0 - k)) * 0.2;
+    const double s = fma(-2.0 * z, z, 1.0);
+    double p = m.win[kMeshWDeg], d = 0.0;
+#pragma unroll
+    for (int j = kMeshWDeg - 1; j >= 0; --j) {
+        if (DER) d = fma(d, s, p);
+        p = fma(p, s, m.win[j]);
+    }
+    if (DER) der = d * (-0.8 * z);             // ds/dz = -4 z, dz = 1/5 per cell
+    return p;
+}
+
+// Slots of a brick's ions, column by column: start[k] .. start[k] + (pre[k+1] - pre[k]).
+struct BrickRuns {
+    int start[64], pre[65];
+};
+
+__device__ __forceinline__ void mesh_brick_runs(const MeshArgs& m, const MeshBufs& b, int bx, int by, int bz,
+                                                BrickRuns& r)
+{
+    const int g2 = m.g * m.g;
+    if (threadIdx.x < 64) {
+        int len = 0, s0 = 0;
+        if ((int)threadIdx.x < g2) {
+            const int cx = bx * m.g + threadIdx.x % m.g, cy = by * m.g + threadIdx.x / m.g;
+            if (cx < m.ncx && cy < m.ncy) {
+                const int c = cy * m.ncx + cx;
+                const int* rel = b.rel + (long long)c * (m.nzb + 1);
+                s0 = rel[min(bz * m.bz * m.zsub, m.nzb)];
+                len = rel[min((bz + 1) * m.bz * m.zsub, m.nzb)] - s0;
+                s0 += b.col[c];
+            }
+        }
+        int inc = len;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int u = __shfl_up(inc, d, 64);
+            if ((int)threadIdx.x >= d) inc += u;
+        }
+        r.start[threadIdx.x] = s0;
+        r.pre[threadIdx.x] = inc - len;
+        if (threadIdx.x == 63) r.pre[64] = inc;
+    }
+    __syncthreads();
+}
+
+__device__ __forceinline__ int mesh_brick_slot(const BrickRuns& r, int g2, int k)
+{
+    int c = 0;
+    while (c + 1 < g2 && r.pre[c + 1] <= k) ++c;
+    return r.start[c] + (k - r.pre[c]);
+}
+
+// Fixed point of the grid charges: weights are at most 1, so a node holds
+// fewer than 2^26 of them.
+constexpr double kMeshScale = 137438953472.0;    // 2^37
+
+// Spreads the charges of one brick's ions onto the brick's nodes: a thread per
+// ion, int64 additions in LDS (exact, so the order in which ions arrive does
+// not matter).  Bound by the LDS atomics: 1,000 per ion.
+__global__ __launch_bounds__(256) void mesh_spread_kernel(MeshArgs m, MeshBufs b)
+{
+    extern __shared__ unsigned long long grid[];
+    __shared__ BrickRuns runs;
+    const int lx = m.bc + kMeshP - 1, lz = m.bz + kMeshP - 1, total = lx * lx * lz;
+    const int bx = blockIdx.x % m.nbx, by = blockIdx.x / m.nbx % m.nby, bz = blockIdx.x / (m.nbx * m.nby);
+    for (int k = threadIdx.x; k < total; k += 256) grid[k] = 0ull;
+    mesh_brick_runs(m, b, bx, by, bz, runs);
+    const int g2 = m.g * m.g, cnt = runs.pre[64];
+    for (int k = threadIdx.x; k < cnt; k += 256) {
+        const int t = mesh_brick_slot(runs, g2, k);
+        const double px = b.s[t], py = b.s[m.cap + t], pz = b.s[2 * (long long)m.cap + t];
+        const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]), cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]),
+                  cz = mesh_cell(pz, -m.Hh, m.inv_h, m.nc[2]);
+        const double ux = (px + m.R) * m.inv_h - cx, uy = (py + m.R) * m.inv_h - cy,
+                     uz = (pz + m.Hh) * m.inv_h - cz;
+        double wx[kMeshP], wy[kMeshP], dummy;
+#pragma unroll
+        for (int j = 0; j < kMeshP; ++j) {
+            wx[j] = mesh_window<false>(m, ux, j, dummy);
+            wy[j] = mesh_window<false>(m, uy, j, dummy);
+        }
+        const int base = ((cz - bz * m.bz) * lx + (cy - by * m.bc)) * lx + (cx - bx * m.bc);
+#pragma unroll 1
+        for (int jz = 0; jz < kMeshP; ++jz) {
+            const double wz = mesh_window<false>(m, uz, jz, dummy) * kMeshScale;
+            int at = base + jz * lx * lx;
+#pragma unroll
+            for (int jy = 0; jy < kMeshP; ++jy) {
+                const double wzy = wz * wy[jy];
+#pragma unroll
+                for (int jx = 0; jx < kMeshP; ++jx) {
+                    // 1.5 2^52 + w has the rounded integer in its low bits
+                    const double f = fma(wzy, wx[jx], 6755399441055744.0);
+                    const unsigned long long w = __builtin_bit_cast(unsigned long long, f) - 0x4338000000000000ull;
+                    __hip_atomic_fetch_add(&grid[at + jx], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+                }
+                at += lx;
+            }
+        }
+    }
+    __syncthreads();
+    unsigned long long* o = b.brick + (long long)blockIdx.x * total;
+    for (int k = threadIdx.x; k < total; k += 256) o[k] = grid[k];
+}
+
+// Grid charges: a node lies in at most two bricks along each axis.
+__global__ __launch_bounds__(256) void mesh_sum_kernel(MeshArgs m, MeshBufs b)
+{
+    const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
+    if (v >= (long long)nx * ny * nz) return;
+    const int x = (int)(v % nx), y = (int)(v / nx % ny), z = (int)(v / ((long long)nx * ny));
+    const int lx = m.bc + kMeshP - 1, lz = m.bz + kMeshP - 1;
+    const long long total = (long long)lx * lx * lz;
+    long long s = 0;
+    for (int bz = z / m.bz, i = 0; i < 2; ++i, --bz) {
+        if (bz < 0 || bz >= m.nbz || z - bz * m.bz >= lz) continue;
+        for (int by = y / m.bc, j = 0; j < 2; ++j, --by) {
+            if (by < 0 || by >= m.nby || y - by * m.bc >= lx) continue;
+            for (int bx = x / m.bc, k = 0; k < 2; ++k, --bx) {
+                if (bx < 0 || bx >= m.nbx || x - bx * m.bc >= lx) continue;
+                s += (long long)b.brick[((long long)(bz * m.nby + by) * m.nbx + bx) * total +
+                                        ((z - bz * m.bz) * lx + (y - by * m.bc)) * lx + (x - bx * m.bc)];
+            }
+        }
+    }
+    b.q[v] = (double)s / kMeshScale;
+}
+
+// Green's tables, once per system (block m): the one-dimensional kernel g_m
+// on the grid whose product with two windows is e^(-t_m^2 x^2).  Its symbol is
+// the least-squares one, (sum over the alias images of W^2 G) / (sum of W^2)^2
+// with W the window's and G the Gaussian's transform (wave numbers per cell).
+constexpr int kMeshNk = 768;
+
+__global__ __launch_bounds__(256) void mesh_green_kernel(MeshArgs m, double i0_beta, double* __restrict__ green)
+{
+    __shared__ double sym[kMeshNk];
+    __shared__ double part[4][64];
+    const double th = m.th[blockIdx.x];
+    for (int j = threadIdx.x; j < kMeshNk; j += 256) {
+        double num = 0.0, den = 0.0;
+        for (int a = -2; a <= 2; ++a) {
+            const double k = kPi * ((j + 0.5) / kMeshNk + 2.0 * a);
+            const double q = kMeshBeta * kMeshBeta - 0.25 * kMeshP * kMeshP * k * k;
+            const double r = sqrt(fabs(q));
+            const double w = r < 1e-6 ? 1.0 : (q > 0.0 ? sinh(r) : sin(r)) / r;
+            const double w2 = w * w * (kMeshP * kMeshP / (i0_beta * i0_beta));
+            num += w2 * (sqrt(kPi) / th) * exp(-0.25 * k * k / (th * th));
+            den += w2;
+        }
+        sym[j] = num / (den * den) / kMeshNk;
+    }
+    __syncthreads();
+    const int n = blockIdx.y * 64 + (threadIdx.x & 63), q = threadIdx.x >> 6;
+    double s = 0.0;
+    if (n < max(m.n[0], m.n[2]))
+        for (int j = q * (kMeshNk / 4); j < (q + 1) * (kMeshNk / 4); ++j)
+            s = fma(sym[j], cospi((double)((2 * j + 1) * n % (4 * kMeshNk)) / (2.0 * kMeshNk)), s);
+    part[q][threadIdx.x & 63] = s;
+    __syncthreads();
+    if (q == 0 && n < m.ng)
+        green[(long long)blockIdx.x * m.ng + n] = ((part[0][n & 63] + part[1][n & 63]) + part[2][n & 63]) + part[3][n & 63];
+}
+
+// One axis of the Gaussian convolutions as a matrix product with the Toeplitz
+// matrix g[|i - k|], 64-bit MFMA.  A wave computes 64 nodes of 16 grid lines;
+// the four 16 x 16 tiles share each loaded line value.  AXIS 0 and 1 apply
+// Gaussian m0 + blockIdx.z; AXIS 2 sums over Gaussians m0 .. m0 + mc - 1 with
+// their weights (add: on top of what out holds).  v_mfma_f64_16x16x4_f64
+// operands, lane l: A[l % 16][l / 16], B[l / 16][l % 16], D[4 r + l / 16][l % 16].
+template <int AXIS>
+__global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double* __restrict__ in,
+                                                        double* __restrict__ out,
+                                                        const double* __restrict__ green, int m0, int mc, int add)
+{
+    typedef double d4 __attribute__((ext_vector_type(4)));
+    extern __shared__ double tab[];
+    const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
+    const int len = AXIS == 0 ? nx : AXIS == 1 ? ny : nz;
+    const int lines = AXIS == 0 ? ny * nz : AXIS == 1 ? nx * nz : nx * ny;
+    const long long vol = (long long)nx * ny * nz;
+    const long long sk = AXIS == 0 ? 1 : AXIS == 1 ? nx : (long long)nx * ny;
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int line = (blockIdx.x * 4 + wv) * 16 + (lane & 15);
+    const int ln = min(line, lines - 1);
+    const long long base = AXIS == 0 ? (long long)ln * nx
+                         : AXIS == 1 ? (long long)(ln / nx) * nx * ny + ln % nx : ln;
+    const int i0 = blockIdx.y * 64, kq = lane >> 4;
+    d4 acc[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+    const int first = AXIS == 2 ? 0 : blockIdx.z, count = AXIS == 2 ? mc : 1;
+    for (int g = first; g < first + count; ++g) {
+        const double w = AXIS == 2 ? m.w[m0 + g] : 1.0;
+        __syncthreads();
+        for (int k = threadIdx.x; k < m.ng; k += 256) tab[k] = w * green[(long long)(m0 + g) * m.ng + k];
+        __syncthreads();
+        const double* src = in + (AXIS == 0 ? 0 : g * vol) + base;
+        for (int k0 = 0; k0 < len; k0 += 16) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + 4 * u + kq;
+                v[u] = k < len ? src[k * sk] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int k = k0 + 4 * u + kq;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const double a = tab[abs(i0 + 16 * t + (lane & 15) - k)];
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v[u], acc[t], 0, 0, 0);
+                }
+            }
+        }
+    }
+    if (line >= lines) return;
+    double* dst = out + (AXIS == 2 ? 0 : first * vol) + base;
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = i0 + 16 * t + 4 * r + kq;
+            if (i < len) dst[i * sk] = acc[t][r] + (AXIS == 2 && add ? dst[i * sk] : 0.0);
+        }
+}
+
+// Far part of every ion's raw pair sum, minus the gradient of the gridded
+// potential: a thread per ion, the brick's nodes in LDS.  The window's
+// derivative is taken of the normalised interpolant (sum w phi / sum w), which
+// makes a constant potential exactly force free: the mean potential is 1e4
+// times what matters here.
+__global__ __launch_bounds__(256) void mesh_gather_kernel(MeshArgs m, MeshBufs b)
+{
+    extern __shared__ double node[];
+    __shared__ BrickRuns runs;
+    const int lx = m.bc + kMeshP - 1, lz = m.bz + kMeshP - 1, total = lx * lx * lz;
+    const int bx = blockIdx.x % m.nbx, by = blockIdx.x / m.nbx % m.nby, bz = blockIdx.x / (m.nbx * m.nby);
+    mesh_brick_runs(m, b, bx, by, bz, runs);
+    const int g2 = m.g * m.g, cnt = runs.pre[64];
+    if (cnt == 0) return;
+    for (int k = threadIdx.x; k < total; k += 256) {
+        const int x = bx * m.bc + k % lx, y = by * m.bc + k / lx % lx, z = bz * m.bz + k / (lx * lx);
+        node[k] = x < m.n[0] && y < m.n[1] && z < m.n[2] ? b.phi[((long long)z * m.n[1] + y) * m.n[0] + x] : 0.0;
+    }
+    __syncthreads();
+    for (int k = threadIdx.x; k < cnt; k += 256) {
+        const int t = mesh_brick_slot(runs, g2, k);
+        const double px = b.s[t], py = b.s[m.cap + t], pz = b.s[2 * (long long)m.cap + t];
+        const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]), cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]),
+                  cz = mesh_cell(pz, -m.Hh, m.inv_h, m.nc[2]);
+        const double ux = (px + m.R) * m.inv_h - cx, uy = (py + m.R) * m.inv_h - cy,
+                     uz = (pz + m.Hh) * m.inv_h - cz;
+        double wx[kMeshP], dx[kMeshP], wy[kMeshP], dy[kMeshP];
+        double sx = 0.0, tx = 0.0, sy = 0.0, ty = 0.0;
+#pragma unroll
+        for (int j = 0; j < kMeshP; ++j) {
+            wx[j] = mesh_window<true>(m, ux, j, dx[j]);
+            wy[j] = mesh_window<true>(m, uy, j, dy[j]);
+            sx += wx[j]; tx += dx[j];
+            sy += wy[j]; ty += dy[j];
+        }
+        const double qx = tx / sx, qy = ty / sy;
+#pragma unroll
+        for (int j = 0; j < kMeshP; ++j) {
+            dx[j] = fma(-qx, wx[j], dx[j]);
+            dy[j] = fma(-qy, wy[j], dy[j]);
+        }
+        const int base = ((cz - bz * m.bz) * lx + (cy - by * m.bc)) * lx + (cx - bx * m.bc);
+        double fx = 0.0, fy = 0.0, fz = 0.0, pw = 0.0, sz = 0.0, tz = 0.0;
+#pragma unroll 1
+        for (int jz = 0; jz < kMeshP; ++jz) {
+            double dz;
+            const double wz = mesh_window<true>(m, uz, jz, dz);
+            int at = base + jz * lx * lx;
+            double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+#pragma unroll
+            for (int jy = 0; jy < kMeshP; ++jy) {
+                double r0 = 0.0, r1 = 0.0;
+#pragma unroll
+                for (int jx = 0; jx < kMeshP; ++jx) {
+                    const double p = node[at + jx];
+                    r0 = fma(p, dx[jx], r0);
+                    r1 = fma(p, wx[jx], r1);
+                }
+                a0 = fma(r0, wy[jy], a0);
+                a1 = fma(r1, dy[jy], a1);
+                a2 = fma(r1, wy[jy], a2);
+                at += lx;
+            }
+            fx = fma(a0, wz, fx);
+            fy = fma(a1, wz, fy);
+            fz = fma(a2, dz, fz);
+            pw = fma(a2, wz, pw);
+            sz += wz;
+            tz += dz;
+        }
+        fz = fma(-tz / sz, pw, fz);
+        b.far[t] = -fx * m.inv_h;
+        b.far[m.cap + t] = -fy * m.inv_h;
+        b.far[2 * (long long)m.cap + t] = -fz * m.inv_h;
+    }
+}
+
+// Near part of the pair term at squared distance r2: (1 + r) e^-r / r^3 - f_L.
+// Beyond r_c it is evaluated at r_c, where it vanishes.
+__device__ __forceinline__ float mesh_near_f(const MeshArgs& m, float near0, float r2)
+{
+    const float y = __builtin_amdgcn_fmed3f(r2, 0.0f, m.rc2);
+    const float ri = __builtin_amdgcn_rsqf(y);
+    const float s = fmaf(y, m.irc2, 1.0f);
+    float p = m.near[kMeshNearDeg];
+#pragma unroll
+    for (int d = kMeshNearDeg - 1; d > 0; --d) p = fmaf(p, s, m.near[d]);
+    p = fmaf(p, s, near0);
+    const float ri2 = ri * ri;
+    const float e = __builtin_amdgcn_exp2f((y * ri) * -1.4426950408889634f);
+    return fmaf(fmaf(ri2, ri, ri2), e, -p);
+}
+
+// Constant term of the near polynomial that makes mesh_near_f vanish at r_c as
+// the hardware rounds it (once per system): every pair beyond r_c within a
+// box contributes that value, so what is left of it adds up.
+__global__ void mesh_zero_kernel(MeshArgs m, float* near0)
+{
+    float c = m.near[0];
+    for (int k = 0; k < 4; ++k) c += mesh_near_f(m, c, m.rc2);
+    if (threadIdx.x == 0) *near0 = c;
+}
+
+// Near pairs of one 64-ion tile by S waves.  First the waves share the search:
+// the columns within r_c of the tile's box and, in each, the slots within r_c
+// along z, 64 boxes of 16 ions at a time against the tile's box; the boxes
+// kept are listed in LDS.  Then the waves take the listed boxes in turn: every
+// lane holds a target and the 16 sources come through the scalar cache, one
+// register operand each, so a pair costs its arithmetic and no LDS or vector
+// load.  FP32 terms, FP64 sums of every 16.  Bound by FP32 issue.
+constexpr int kMeshList = 256;      // listed boxes per wave; further ones are done at once
+
+template <int S>
+__global__ __launch_bounds__(64 * S) void mesh_near_kernel(MeshArgs m, MeshBufs b,
+                                                           unsigned long long* __restrict__ fix, long long fstride,
+                                                           double scale, int* status)
+{
+    __shared__ int list[S][kMeshList];
+    __shared__ int listed[S];
+    __shared__ int2 cand[256];
+    __shared__ int ncand;
+    __shared__ double part[S][3][kMeshTile];
+    const int ncol = m.ncx * m.ncy;
+    // consecutive tiles share sources: give each of the 8 XCDs a run of them
+    const int tiles = b.col[ncol] / kMeshTile;
+    const int per = (tiles + 7) / 8;
+    const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || tile >= tiles) return;
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int slot = tile * kMeshTile + lane;
+    const float* __restrict__ X = b.s;
+    const float* __restrict__ Y = b.s + m.cap;
+    const float* __restrict__ Z = b.s + 2 * (long long)m.cap;
+    const float xi = X[slot], yi = Y[slot], zi = Z[slot];
+    const int ns = m.cap / kMeshSub;
+    // the tile's box
+    float lo[3], hi[3];
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        const float4 l = *(const float4*)&b.box[(long long)c * ns + tile * 4];
+        const float4 h = *(const float4*)&b.box[(long long)(c + 3) * ns + tile * 4];
+        lo[c] = fminf(fminf(l.x, l.y), fminf(l.z, l.w));
+        hi[c] = fmaxf(fmaxf(h.x, h.y), fmaxf(h.z, h.w));
+    }
+    const float R = (float)m.R, icw = 1.0f / m.cw, slack = 1.0e-4f * m.rc;
+    auto column = [&](float v, int nc) { return (int)fminf(fmaxf(floorf((v + R) * icw), 0.0f), (float)(nc - 1)); };
+    const int x0 = column(lo[0] - m.rc, m.ncx), x1 = column(hi[0] + m.rc, m.ncx);
+    const int y0 = column(lo[1] - m.rc, m.ncy), y1 = column(hi[1] + m.rc, m.ncy);
+    const int nx = x1 - x0 + 1, all = nx > 0 && y1 >= y0 ? nx * (y1 - y0 + 1) : 0;    // a tile of NaNs has no box
+    const float near0 = b.near0[0];
+    double sx = 0.0, sy = 0.0, sz = 0.0;
+
+    auto pairs = [&](int sub) {
+        const int j0 = sub * kMeshSub;
+        float ax = 0.0f, ay = 0.0f, az = 0.0f;
+        const int self = (sub >> 2) == tile ? lane - (sub & 3) * kMeshSub : -1;
+        const bool own = (sub >> 2) == tile;
+        float qx[kMeshSub], qy[kMeshSub], qz[kMeshSub];
+#pragma unroll
+        for (int k = 0; k < kMeshSub; ++k) {
+            qx[k] = X[j0 + k];
+            qy[k] = Y[j0 + k];
+            qz[k] = Z[j0 + k];
+        }
+        auto term = [&](int k, bool skip) {
+            const float dx = xi - qx[k], dy = yi - qy[k], dz = zi - qz[k];
+            float f = mesh_near_f(m, near0, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+            if (skip) f = k == self ? 0.0f : f;
+            ax = fmaf(f, dx, ax);
+            ay = fmaf(f, dy, ay);
+            az = fmaf(f, dz, az);
+        };
+        if (own) {
+#pragma unroll
+            for (int k = 0; k < kMeshSub; ++k) term(k, true);
+        } else {
+#pragma unroll
+            for (int k = 0; k < kMeshSub; ++k) term(k, false);
+        }
+        sx += (double)ax;
+        sy += (double)ay;
+        sz += (double)az;
+    };
+
+    int n = 0;
+    for (int c0 = 0; c0 < all; c0 += 256) {
+        // candidate columns: slots within r_c along z, as runs of boxes
+        __syncthreads();
+        const int have = min(256, all - c0);
+        for (int t = threadIdx.x; t < have; t += 64 * S) {
+            const int cx = x0 + (c0 + t) % nx, cy = y0 + (c0 + t) / nx;
+            // the outer columns also hold ions that sit on the boundary to rounding
+            const float gx = fmaxf(0.0f, fmaxf(cx * m.cw - R - hi[0], lo[0] - ((cx + 1) * m.cw - R)) - slack);
+            const float gy = fmaxf(0.0f, fmaxf(cy * m.cw - R - hi[1], lo[1] - ((cy + 1) * m.cw - R)) - slack);
+            const float left = m.rc2 - gx * gx - gy * gy;
+            int2 e = make_int2(0, 0);
+            if (left > 0.0f) {
+                const float dz = sqrtf(left) + slack;
+                const int c = cy * m.ncx + cx;
+                const int* rel = b.rel + (long long)c * (m.nzb + 1);
+                const int s0 = rel[mesh_zbin(lo[2] - dz, m)], s1 = rel[mesh_zbin(hi[2] + dz, m) + 1];
+                if (s1 > s0) {
+                    const int first = (b.col[c] + s0) / kMeshSub;
+                    e = make_int2(first, (b.col[c] + s1 + kMeshSub - 1) / kMeshSub - first);
+                }
+            }
+            cand[t] = e;
+        }
+        __syncthreads();
+        int unit = 0;
+        for (int t = 0; t < have; ++t) {
+            const int2 e = cand[t];
+            const int first = __builtin_amdgcn_readfirstlane(e.x), len = __builtin_amdgcn_readfirstlane(e.y);
+            for (int o = 0; o < len; o += 64, ++unit) {
+                if (unit % S != wv) continue;
+                const int sub = first + o + lane;
+                bool keep = false;
+                if (o + lane < len) {
+                    const float gx = fmaxf(0.0f, fmaxf(b.box[sub] - hi[0], lo[0] - b.box[3ll * ns + sub]));
+                    const float gy = fmaxf(0.0f, fmaxf(b.box[ns + sub] - hi[1], lo[1] - b.box[4ll * ns + sub]));
+                    const float gz = fmaxf(0.0f, fmaxf(b.box[2ll * ns + sub] - hi[2], lo[2] - b.box[5ll * ns + sub]));
+                    keep = gx * gx + gy * gy + gz * gz < m.rc2;
+                }
+                unsigned long long mask = __ballot(keep);
+                const int k = __popcll(mask);
+                if (n + k <= kMeshList) {
+                    if (keep) list[wv][n + __popcll(mask & ((1ull << lane) - 1ull))] = sub;
+                    n += k;
+                } else {
+                    for (; mask; mask &= mask - 1) pairs(first + o + __ffsll((long long)mask) - 1);
+                }
+            }
+        }
+    }
+    if (lane == 0) listed[wv] = n;
+    __syncthreads();
+    int total = 0;
+    for (int w = 0; w < S; ++w) total += __builtin_amdgcn_readfirstlane(listed[w]);
+    for (int k = wv; k < total; k += S) {
+        int w = 0, o = k;
+        for (int c; o >= (c = __builtin_amdgcn_readfirstlane(listed[w])); ++w) o -= c;
+        pairs(__builtin_amdgcn_readfirstlane(list[w][o]));
+    }
+    part[wv][0][lane] = sx;
+    part[wv][1][lane] = sy;
+    part[wv][2][lane] = sz;
+    __syncthreads();
+    if (wv != 0) return;
+    const int i = b.idx[slot];
+    if (i < 0) return;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+        double t = part[0][c][lane];
+#pragma unroll
+        for (int w = 1; w < S; ++w) t += part[w][c][lane];
+        fix[c * fstride + i] = to_fixed(t + b.far[(long long)c * m.cap + slot], scale, status);
+    }
+}
+
+// Convolution scratch.  All 14 Gaussians at once where they fit: 2.09 against
+// 2.06 ms per step at 2^18 ions and 6.61 against 6.56 at 2^20 with 160 MB.
+constexpr int kMeshScratchMb = 400;
+
+// Lays the buffers out in an arena at `base` (null: only the size, in bytes).
+inline size_t mesh_layout(const MeshArgs& m, char* base, MeshBufs& b)
+{
+    size_t at = 0;
+    auto take = [&](auto** p, size_t bytes) {
+        *p = (std::remove_reference_t<decltype(**p)>*)(base ? base + at : nullptr);
+        at += (bytes + 255) / 256 * 256;
+    };
+    const size_t ncol = (size_t)m.ncx * m.ncy, cap = (size_t)m.cap, v = (size_t)m.n[0] * m.n[1] * m.n[2];
+    take(&b.key, (size_t)m.N * 4);
+    take(&b.arr, (size_t)m.N * 4);
+    take(&b.count, ncol * m.nzb * 4);
+    take(&b.rel, ncol * (m.nzb + 1) * 4);
+    take(&b.col, (ncol + 1) * 4);
+    take(&b.temp, cap * 4);
+    take(&b.idx, cap * 4);
+    take(&b.s, 3 * cap * 4);
+    take(&b.box, 6 * (cap / kMeshSub) * 4);
+    take(&b.far, 3 * cap * 8);
+    take(&b.green, (size_t)kMeshM * m.ng * 8);
+    take(&b.near0, 4);
+    take(&b.q, v * 8);
+    take(&b.phi, v * 8);
+    // convolution scratch: as many Gaussians at a time as fit
+    b.mc = (int)std::min<size_t>(kMeshM, std::max<size_t>(1, ((size_t)kMeshScratchMb << 20) / (16 * v)));
+    const int passes = (kMeshM + b.mc - 1) / b.mc;
+    b.mc = (kMeshM + passes - 1) / passes;
+    const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * mesh_brick_nodes(m) * 8;
+    take(&b.t1, std::max(conv, brick));
+    b.t2 = b.t1 ? b.t1 + (size_t)b.mc * v : nullptr;
+    b.brick = (unsigned long long*)b.t1;
+    return at;
+}
+
+// Clears the bin counts and computes the Green's tables (once per system).
+inline hipError_t mesh_start(const MeshArgs& m, const MeshBufs& b, hipStream_t st)
+{
+    const int lds = mesh_brick_nodes(m) * 8;
+    hipError_t e = hipFuncSetAttribute((const void*)mesh_spread_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess)
+        e = hipFuncSetAttribute((const void*)mesh_gather_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e == hipSuccess) e = hipMemsetAsync(b.count, 0, (size_t)m.ncx * m.ncy * m.nzb * 4, st);
+    if (e != hipSuccess) return e;
+    mesh_zero_kernel<<<1, 64, 0, st>>>(m, b.near0);
+    mesh_green_kernel<<<dim3(kMeshM, (m.ng + 63) / 64), 256, 0, st>>>(m, mesh_i0(kMeshBeta), b.green);
+    return hipGetLastError();
+}
+
+// The pair sum of one step: positions x (planes `plane` apart) to the
+// fixed-point totals fix (planes `fstride` apart).
+inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float* x, long long plane,
+                              unsigned long long* fix, long long fstride, double scale, int* status, hipStream_t st)
+{
+    const int gi = (m.N + 255) / 256, gc = (m.cap + 255) / 256, ncol = m.ncx * m.ncy;
+    const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
+    const long long v = (long long)nx * ny * nz;
+    mesh_bin_kernel<<<gc, 256, 0, st>>>(x, plane, m, b);
+    mesh_scan_kernel<<<ncol, 256, 0, st>>>(m, b);
+    mesh_cols_kernel<<<1, 1024, 0, st>>>(m, b);
+    mesh_place_kernel<<<gi, 256, 0, st>>>(m, b);
+    mesh_order_kernel<<<gc, 256, 0, st>>>(x, plane, m, b);
+    mesh_box_kernel<<<gc, 256, 0, st>>>(m, b);
+    const int bricks = m.nbx * m.nby * m.nbz;
+    const size_t lds = (size_t)mesh_brick_nodes(m) * 8, tab = (size_t)m.ng * 8;
+    mesh_spread_kernel<<<bricks, 256, lds, st>>>(m, b);
+    mesh_sum_kernel<<<(unsigned)((v + 255) / 256), 256, 0, st>>>(m, b);
+    auto lines = [](long long n) { return (unsigned)((n + 63) / 64); };
+    for (int m0 = 0; m0 < kMeshM; m0 += b.mc) {
+        const int mc = std::min(b.mc, kMeshM - m0);
+        // mesh_conv_kernel<2> reads t2 and, except on the first pass, adds to the potential
+        mesh_conv_kernel<0><<<dim3(lines((long long)ny * nz), lines(nx), mc), 256, tab, st>>>(m, b.q, b.t1, b.green, m0, mc, 0);
+        mesh_conv_kernel<1><<<dim3(lines((long long)nx * nz), lines(ny), mc), 256, tab, st>>>(m, b.t1, b.t2, b.green, m0, mc, 0);
+        mesh_conv_kernel<2><<<dim3(lines((long long)nx * ny), lines(nz), 1), 256, tab, st>>>(m, b.t2, b.phi, b.green, m0, mc, m0 > 0);
+    }
+    mesh_gather_kernel<<<bricks, 256, lds, st>>>(m, b);
+    const int tiles = (m.cap / kMeshTile + 7) / 8 * 8;
+    if (m.cap / kMeshTile >= 8192)
+        mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b, fix, fstride, scale, status);
+    else
+        mesh_near_kernel<8><<<tiles, 512, 0, st>>>(m, b, fix, fstride, scale, status);
+    return hipGetLastError();
+}
+
+}  // namespace odk

@@ -1,0 +1,260 @@
+// meshplan.hpp -- host side: how the ion-ion sum of a large system is split
+// into a near part and a smooth far part (kernels: mesh.hpp).  Plain C++.
+//
+// The screened Coulomb energy e^-r / r is written L(r) + [e^-r / r - L(r)]
+// with L a sum of Gaussians,
+//   L(r) = sum_m w_m e^(-t_m^2 r^2),   t_m geometric from t_min to 2.8 / r_c,
+// whose weights are fitted (least squares on the force) so that L equals the
+// screened energy beyond r_c.  The bracket then vanishes beyond r_c and is
+// summed over near pairs; L is smooth and is summed over all ions on a
+// regular grid: charges spread with a Kaiser-Bessel window of ten nodes per
+// axis, each Gaussian applied as three one-dimensional convolutions (a
+// Gaussian is a product over the axes) with the window's transform divided
+// out, and the potential's gradient taken with the window's derivative.
+// With r_c / h = 7.5 cells and window shape 22 the far part is within 1e-7 of
+// the rms acceleration (2^14 .. 2^20 ions, measured against 64-bit direct
+// sums), below the FP32 rounding of the pair terms.
+#pragma once
+
+#include <algorithm>
+#include <cmath>
+#include <vector>
+
+namespace odk {
+
+constexpr int kMeshP = 10;          // window nodes per axis
+constexpr int kMeshM = 14;          // Gaussians
+constexpr int kMeshWDeg = 18;       // degree of the window polynomial in 1 - 2 z^2
+constexpr int kMeshNearDeg = 12;    // degree of the near part's polynomial in 1 - 2 r^2 / r_c^2
+constexpr double kMeshBeta = 22.0;  // Kaiser-Bessel shape
+constexpr double kMeshRatio = 7.5;  // r_c / h
+constexpr double kMeshTop = 2.8;    // t_max r_c
+constexpr int kMeshSub = 16;        // sources per box of the near search
+constexpr int kMeshTile = 64;       // targets per tile
+
+// Constants of one system's split, passed to the kernels by value.
+struct MeshArgs {
+    int N, cap;                     // ions; sorted slots (columns padded to whole tiles)
+    int nc[3], n[3];                // grid cells and nodes (nc + 9) per axis
+    int kx, ncx, ncy;               // column width in cells; columns along x and y
+    int zsub, nzb;                  // sort bins per cell along z; bins per column
+    int g, bc, bz;                  // brick: g x g columns = bc x bc cells, bz cells along z
+    int nbx, nby, nbz;              // bricks per axis
+    int ng;                         // entries of one Green's table (zero padded)
+    double R, Hh, h, inv_h;         // domain radius and half height; grid spacing
+    float rc, rc2, irc2, cw;        // near radius, its square, -2 / rc^2; column width
+    float near[kMeshNearDeg + 1];   // f_L(r) = -L'/r in powers of 1 - 2 r^2 / r_c^2
+    double win[kMeshWDeg + 1];      // window in powers of s = 1 - 2 z^2
+    double w[kMeshM], th[kMeshM];   // weights; t_m h
+};
+
+// Grid nodes that the ions of one brick reach.
+inline int mesh_brick_nodes(const MeshArgs& a)
+{
+    const int lx = a.bc + kMeshP - 1;
+    return lx * lx * (a.bz + kMeshP - 1);
+}
+
+// Least squares of an m x n system (column major A, overwritten) by
+// Householder QR; columns scaled by the caller.
+inline void mesh_lstsq(std::vector<double>& A, std::vector<double>& b, int m, int n, double* x)
+{
+    std::vector<double> d(n);
+    for (int j = 0; j < n; ++j) {
+        double* a = &A[(size_t)j * m];
+        double s = 0.0;
+        for (int i = j; i < m; ++i) s += a[i] * a[i];
+        s = std::sqrt(s);
+        const double alpha = a[j] > 0 ? -s : s;
+        a[j] -= alpha;
+        double vv = 0.0;
+        for (int i = j; i < m; ++i) vv += a[i] * a[i];
+        auto reflect = [&](double* c) {
+            double dot = 0.0;
+            for (int i = j; i < m; ++i) dot += a[i] * c[i];
+            const double f = vv > 0 ? 2.0 * dot / vv : 0.0;
+            for (int i = j; i < m; ++i) c[i] -= f * a[i];
+        };
+        for (int k = j + 1; k < n; ++k) reflect(&A[(size_t)k * m]);
+        reflect(b.data());
+        d[j] = alpha;
+    }
+    for (int j = n - 1; j >= 0; --j) {
+        double t = b[j];
+        for (int k = j + 1; k < n; ++k) t -= A[(size_t)k * m + j] * x[k];
+        x[j] = t / d[j];
+    }
+}
+
+// Interpolation of f at the deg + 1 extrema of the Chebyshev polynomial on
+// [-1, 1] (end points among them), as powers of s.
+template <typename F>
+void mesh_cheb(const F& f, int deg, std::vector<double>& mono)
+{
+    const int n = deg + 1;
+    std::vector<double> c(n, 0.0), fv(n);
+    const double pi = 3.14159265358979323846;
+    for (int k = 0; k < n; ++k) fv[k] = f(std::cos(pi * k / deg)) * (k == 0 || k == deg ? 0.5 : 1.0);
+    for (int j = 0; j < n; ++j) {
+        for (int k = 0; k < n; ++k) c[j] += fv[k] * std::cos(pi * j * k / deg);
+        c[j] *= (j == 0 || j == deg ? 1.0 : 2.0) / deg;
+    }
+    // Chebyshev to monomial
+    std::vector<double> t0(n, 0.0), t1(n, 0.0), t2(n);
+    mono.assign(n, 0.0);
+    t0[0] = 1.0;
+    if (n > 1) t1[1] = 1.0;
+    for (int j = 0; j < n; ++j) {
+        for (int k = 0; k < n; ++k) mono[k] += c[j] * t0[k];
+        t2.assign(n, 0.0);
+        for (int k = 0; k + 1 < n; ++k) t2[k + 1] = 2.0 * t1[k];
+        for (int k = 0; k < n; ++k) t2[k] -= t0[k];
+        t0 = t1;
+        t1 = t2;
+    }
+}
+
+inline double mesh_i0(double x)
+{
+    double t = 1.0, s = 1.0;
+    const double q = 0.25 * x * x;
+    for (int k = 1; k < 200; ++k) {
+        t *= q / ((double)k * k);
+        s += t;
+        if (t < 1e-18 * s) break;
+    }
+    return s;
+}
+
+// Volume swept by a box of sides (a, b, c) and a ball of radius r.
+inline double mesh_swept(double a, double b, double c, double r)
+{
+    const double pi = 3.14159265358979323846;
+    return a * b * c + 2.0 * r * (a * b + b * c + c * a) + pi * r * r * (a + b + c) + 4.0 / 3.0 * pi * r * r * r;
+}
+
+// Grid and columns for a near radius; false if the domain is outside what the
+// split is made for.
+inline bool mesh_dims(double N, double R, double H, double rc, MeshArgs& a)
+{
+    const double pi = 3.14159265358979323846;
+    const double n = N / (pi * R * R * H);
+    const double h = rc / kMeshRatio, b = std::cbrt(kMeshTile / n);
+    a.h = h;
+    a.inv_h = 1.0 / h;
+    a.R = R;
+    a.Hh = 0.5 * H;
+    a.nc[0] = a.nc[1] = (int)std::ceil(2.0 * R / h);
+    a.nc[2] = (int)std::ceil(H / h);
+    for (int c = 0; c < 3; ++c) {
+        if (a.nc[c] < 8 || a.nc[c] > 500) return false;
+        a.n[c] = a.nc[c] + kMeshP - 1;
+    }
+    a.kx = std::min(16, std::max(2, (int)std::lround(b / h)));
+    a.ncx = a.ncy = (a.nc[0] + a.kx - 1) / a.kx;
+    a.zsub = a.kx < 8 ? 2 : 1;
+    a.nzb = a.nc[2] * a.zsub;
+    a.cw = (float)(a.kx * h);
+    a.rc = (float)rc;
+    a.rc2 = a.rc * a.rc;
+    a.irc2 = -2.0f / a.rc2;
+    return true;
+}
+
+// The split of a system of N ions (dimensionless R, H).  Chooses r_c by a cost
+// model (microseconds, MI355X): near pairs at kNear per 64, the convolutions'
+// 64-bit matrix rate, and the grid's traffic.  False: use the direct sum.
+inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
+{
+    const double diag = std::sqrt(4.0 * R * R + H * H);
+    if (diag > 24.0 || N < 1024 || N > (1ll << 26)) return false;
+    const double pi = 3.14159265358979323846;
+    const double n = (double)N / (pi * R * R * H), b = std::cbrt(kMeshTile / n);
+    double best = 0.0, rc = 0.0;
+    for (double q = 0.9; q <= 4.0; q *= 1.04) {
+        const double r = q * b;
+        if (r > 1.5 || r < 0.1 || r > 0.45 * diag) continue;
+        MeshArgs t{};
+        if (!mesh_dims((double)N, R, H, r, t)) continue;
+        const double v = (double)t.n[0] * t.n[1] * t.n[2];
+        if (v > 3.0e7) continue;
+        const double s = t.kx * t.h, dz = kMeshTile / (n * s * s);
+        const double pairs = (double)N * std::min((double)N, n * mesh_swept(2 * s, 2 * s, 1.25 * dz, r));
+        const double near = pairs / 64.0 * 0.050e-3;
+        const double conv = 2.0 * kMeshM * v * (t.n[0] + t.n[1] + t.n[2]) / 40.0e6 + v * kMeshM * 32.0 / 3.0e6;
+        const double cost = near + conv + v * 7.0 * 24.0 / 3.0e6;
+        if (rc == 0.0 || cost < best) {
+            best = cost;
+            rc = r;
+        }
+    }
+    if (rc == 0.0 || !mesh_dims((double)N, R, H, rc, a)) return false;
+    a.N = (int)N;
+    const long long cap = (N + 63ll * a.ncx * a.ncy + 63) / 64 * 64;
+    if (cap > (1ll << 28)) return false;
+    a.cap = (int)cap;
+    // bricks of about 10 cells a side (smaller for small systems, so that the
+    // spreading and gathering blocks fill the chip)
+    const int want = N >= (1 << 18) ? 10 : 6;
+    a.g = std::max(1, (want + a.kx / 2) / a.kx);
+    a.bc = a.g * a.kx;
+    while (a.bc < kMeshP - 1) a.bc = ++a.g * a.kx;       // a node lies in at most two bricks per axis
+    a.bz = std::max(kMeshP - 1, want);
+    a.nbx = (a.nc[0] + a.bc - 1) / a.bc;
+    a.nby = (a.nc[1] + a.bc - 1) / a.bc;
+    a.nbz = (a.nc[2] + a.bz - 1) / a.bz;
+    a.ng = std::max(a.n[0], a.n[2]) + 80;
+    if (mesh_brick_nodes(a) * 8 > 128 * 1024) return false;      // a brick's nodes are kept in LDS
+
+    // Gaussians: force of L fitted to that of e^-r / r on [r_c, diag]
+    constexpr int m = 160, M = kMeshM;
+    const double t0 = std::max(0.2, 0.6 / diag), t1 = kMeshTop / rc;
+    double t2[M];
+    for (int j = 0; j < M; ++j) {
+        const double t = t0 * std::pow(t1 / t0, (double)j / (M - 1));
+        t2[j] = t * t;
+        a.th[j] = t * a.h;
+    }
+    std::vector<double> A((size_t)m * M), rhs(m), sc(M, 0.0);
+    for (int i = 0; i < m; ++i) {
+        const double r = rc * std::pow(diag * 1.01 / rc, (double)i / (m - 1));
+        // weighted by r; r_c itself heavily, because pairs a little beyond it
+        // are evaluated at r_c, where the near part has to vanish
+        const double wt = i == 0 ? 1.0e4 : 1.0;
+        rhs[i] = wt * (1.0 + r) * std::exp(-r) / r;
+        for (int j = 0; j < M; ++j) A[(size_t)j * m + i] = wt * 2.0 * t2[j] * r * r * std::exp(-t2[j] * r * r);
+    }
+    for (int j = 0; j < M; ++j) {
+        for (int i = 0; i < m; ++i) sc[j] = std::max(sc[j], std::fabs(A[(size_t)j * m + i]));
+        for (int i = 0; i < m; ++i) A[(size_t)j * m + i] /= sc[j];
+    }
+    mesh_lstsq(A, rhs, m, M, a.w);
+    for (int j = 0; j < M; ++j) {
+        a.w[j] /= sc[j];
+        if (!std::isfinite(a.w[j])) return false;
+    }
+    // a domain whose force the Gaussians do not reproduce to this keeps the direct sum
+    for (int i = 0; i < m; ++i) {
+        const double r = rc * std::pow(diag / rc, (double)i / (m - 1));
+        double f = -(1.0 + r) * std::exp(-r) / (r * r * r);
+        for (int j = 0; j < M; ++j) f += a.w[j] * 2.0 * t2[j] * std::exp(-t2[j] * r * r);
+        if (!(std::fabs(f) * r * r * rc < 2.5e-5)) return false;
+    }
+    // near part: f_L in powers of s = 1 - 2 r^2 / r_c^2
+    std::vector<double> mono;
+    mesh_cheb([&](double s) {
+        const double y = 0.5 * (1.0 - s) * rc * rc;
+        double f = 0.0;
+        for (int j = 0; j < M; ++j) f += a.w[j] * 2.0 * t2[j] * std::exp(-t2[j] * y);
+        return f;
+    }, kMeshNearDeg, mono);
+    for (int k = 0; k <= kMeshNearDeg; ++k) a.near[k] = (float)mono[k];
+    // window I0(beta sqrt(1 - z^2)) / I0(beta) in powers of s = 1 - 2 z^2
+    const double top = mesh_i0(kMeshBeta);
+    mesh_cheb([&](double s) { return mesh_i0(kMeshBeta * std::sqrt(std::max(0.0, 0.5 * (1.0 + s)))) / top; },
+              kMeshWDeg, mono);
+    for (int k = 0; k <= kMeshWDeg; ++k) a.win[k] = mono[k];
+    return true;
+}
+
+}  // namespace odk

@@ -12,8 +12,9 @@
 //             last-step record, running sums, step counter, status word).
 // All per-step state stays on the device; a step is three launches (pair sum;
 // the per-ion tail, whose last block finalizes the step; reinjection of the
-// ions the tail listed; a cutoff adds the slab sort and its epilogue) and
-// needs no host synchronisation.
+// ions the tail listed; a cutoff adds the slab sort and its epilogue, the
+// split sum of large systems its sort and grid kernels) and needs no host
+// synchronisation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -28,6 +29,7 @@
 #include "kernels.hpp"
 #include "cutoff.hpp"
 #include "pairsym.hpp"
+#include "mesh.hpp"
 #include "worksplit.hpp"
 
 namespace {
@@ -124,8 +126,16 @@ struct od_system {
     int pair_kind = OD_PAIR_AUTO;
     bool sym = false;
     unsigned long long* acc_fix = nullptr;  // [3][Npad] int64 fixed-point pair sums
-    odk::SymItem* sym_items = nullptr;      // in acc_fix's allocation
+    odk::SymItem* sym_items = nullptr;
     int n_sym_items = 0;
+    // the same sum split into near pairs and a gridded far part (large systems)
+    int mesh_planned = 0;               // 1 planned, -1 not for this system
+    bool mesh = false;
+    odk::MeshArgs ma{};
+    odk::MeshBufs mb{};
+    void* mesh_mem = nullptr;
+    bool fix_in_mem = false;            // acc_fix lies in mem
+    int direct_steps = 0;               // steps to sum directly first: the state has ions outside the domain
     // device memory: one allocation (mem), cut into the buffers below
     void* mem = nullptr;
     void* x = nullptr;
@@ -176,53 +186,132 @@ void free_cutoff(od_system* s)
     s->cut = false;
 }
 
+// Systems up to this size sum their pairs directly.  Direct against split, ms
+// per step of one grain at R = 3, H = 6: 1.16 / 0.69 at 2^16, 4.1 / 1.15 at
+// 2^17, 16.0 / 2.1 at 2^18; 257 / 6.6 at 2^20 (two grains, H = 8).
+constexpr int64_t kMeshMinN = 81920;
+
+// Whether the system's pair sum can be split into near pairs and a far part
+// on a grid (mesh.hpp); plans it the first time.
+bool plan_mesh(od_system* s)
+{
+    if (s->mesh_planned == 0)
+        s->mesh_planned = s->prec == OD_PREC_FP32 && s->N >= kMeshMinN && s->pa.ion_ion &&
+                                  odk::mesh_plan(s->N, s->pu.R, s->pu.H, s->ma)
+                              ? 1 : -1;
+    return s->mesh_planned > 0;
+}
+
+void free_mesh(od_system* s)
+{
+    dev_free(s, s->mesh_mem);
+    s->mesh_mem = nullptr;
+    s->mesh = false;
+}
+
 void free_sym(od_system* s)
 {
-    dev_free(s, s->acc_fix);
+    if (!s->fix_in_mem) dev_free(s, s->acc_fix);
+    dev_free(s, s->sym_items);
     s->acc_fix = nullptr;
     s->sym_items = nullptr;
     s->n_sym_items = 0;
-    s->sym = false;
+    s->sym = s->fix_in_mem = false;
 }
 
-// Sets up the symmetric pair sum: its fixed-point totals and work items.  In
-// test-particle mode there are no items (no pair kernel runs); the totals stay
-// zero and the step's tail adds the grain, drive and confinement terms.
-od_status setup_sym(od_system* s)
+// Work items of the direct symmetric sum.  In test-particle mode there are
+// none (no pair kernel runs).
+od_status setup_items(od_system* s, hipStream_t st)
 {
-    if (s->sym) return OD_OK;
-    const int T = (int)(s->Npad / kPairBlock);
-    std::vector<odk::SymItem> items;
-    if (s->pa.ion_ion) items = sym_items(T);
-    const size_t totals = 3 * (size_t)s->Npad * sizeof(unsigned long long);      // a multiple of 256
-    s->acc_fix = (unsigned long long*)dev_alloc(s, totals + items.size() * sizeof(odk::SymItem));
-    if (!s->acc_fix) {
-        free_sym(s);
-        return fail(OD_ENOMEM, "device allocation of the symmetric pair sum failed");
-    }
-    s->sym_items = (odk::SymItem*)((char*)s->acc_fix + totals);
-    if (!items.empty())
-        HIPCHK(hipMemcpyAsync(s->sym_items, items.data(), items.size() * sizeof(odk::SymItem),
-                              hipMemcpyHostToDevice, s->stream));
-    HIPCHK(hipMemsetAsync(s->acc_fix, 0, totals, s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
+    if (s->n_sym_items > 0 || !s->pa.ion_ion) return OD_OK;
+    const std::vector<odk::SymItem> items = sym_items((int)(s->Npad / kPairBlock));
+    s->sym_items = (odk::SymItem*)dev_alloc(s, items.size() * sizeof(odk::SymItem));
+    if (!s->sym_items) return fail(OD_ENOMEM, "device allocation of the symmetric pair sum failed");
+    HIPCHK(hipMemcpyAsync(s->sym_items, items.data(), items.size() * sizeof(odk::SymItem), hipMemcpyHostToDevice, st));
+    HIPCHK(hipStreamSynchronize(st));
     s->n_sym_items = (int)items.size();
-    s->sym = true;
     return OD_OK;
+}
+
+// Sets up the split, or, where its memory is refused, the direct sum.
+od_status setup_mesh(od_system* s, hipStream_t st)
+{
+    s->mesh_mem = dev_alloc(s, odk::mesh_layout(s->ma, nullptr, s->mb));
+    if (!s->mesh_mem) {
+        (void)hipGetLastError();
+        s->mesh_planned = -1;
+        return setup_items(s, st);
+    }
+    odk::mesh_layout(s->ma, (char*)s->mesh_mem, s->mb);
+    HIPCHK(odk::mesh_start(s->ma, s->mb, st));
+    s->mesh = true;
+    return OD_OK;
+}
+
+bool use_mesh(const od_system* s) { return s->sym && s->pair_kind == OD_PAIR_AUTO && s->mesh_planned > 0; }
+
+// The split's memory (up to a few hundred MB) is taken by the first step that
+// needs it, not when the system is created: hipMalloc and hipFree of more than
+// 64 MB take 0.3 ms, and milliseconds in a row, which a program that only
+// draws initial states would pay for nothing.  A system with an allocator of
+// its caller's takes it at creation, where the allocator may be called.  When
+// the caller is capturing the stream the set-up runs on a stream of its own.
+od_status first_step_setup(od_system* s)
+{
+    if (s->cut || !use_mesh(s) || s->mesh) return OD_OK;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (s->stream) HIPCHK(hipStreamIsCapturing(s->stream, &cs));
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
+    hipStream_t st = s->stream;
+    od_status r = OD_OK;
+    if (cs != hipStreamCaptureStatusNone && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess)
+        r = fail(OD_EDEVICE, "hipStreamCreateWithFlags failed");
+    if (r == OD_OK) r = setup_mesh(s, st);
+    if (st != s->stream) {
+        if (hipStreamSynchronize(st) != hipSuccess && r == OD_OK) r = fail(OD_EDEVICE, "setting up the pair sum failed");
+        (void)hipStreamDestroy(st);
+    }
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    return r;
+}
+
+size_t fix_bytes(const od_system* s) { return 3 * (size_t)s->Npad * sizeof(unsigned long long); }
+
+// Sets up the symmetric pair sum: its fixed-point totals, and the work items
+// of the direct sum unless the split takes its place.  In test-particle mode
+// the totals stay zero and the step's tail adds the grain, drive and
+// confinement terms.  room: memory set aside for the totals, or null.
+od_status setup_sym(od_system* s, void* room)
+{
+    if (!s->sym) {
+        s->fix_in_mem = room != nullptr;
+        s->acc_fix = (unsigned long long*)(room ? room : dev_alloc(s, fix_bytes(s)));
+        if (!s->acc_fix) return fail(OD_ENOMEM, "device allocation of the symmetric pair sum failed");
+        HIPCHK(hipMemsetAsync(s->acc_fix, 0, fix_bytes(s), s->stream));
+        s->sym = true;
+    }
+    od_status st = OD_OK;
+    if (!use_mesh(s) || s->direct_steps > 0) st = setup_items(s, s->stream);
+    if (st == OD_OK && s->custom_alloc) st = first_step_setup(s);
+    if (st == OD_OK) HIPCHK(hipStreamSynchronize(s->stream));
+    return st;
 }
 
 // Chooses the all-pairs kernel for the system's kind: the symmetric one
 // unless one-sided is asked for (it is the faster at every size).
-od_status apply_pair_kind(od_system* s)
+od_status apply_pair_kind(od_system* s, void* room = nullptr)
 {
     const bool able = s->prec == OD_PREC_FP32;
     const bool want = able && (s->pair_kind == OD_PAIR_SYMMETRIC || s->pair_kind == OD_PAIR_AUTO);
-    if (want && !s->sym) {
-        od_status st = setup_sym(s);
-        if (st != OD_OK) return st;
-    } else if (!want && s->sym) {
-        free_sym(s);
+    if (s->mesh && s->pair_kind != OD_PAIR_AUTO) free_mesh(s);
+    if (want) {
+        const bool had = s->sym;
+        od_status st = setup_sym(s, room);
+        if (st != OD_OK && !had) free_sym(s);
+        return st;
     }
+    if (s->sym) free_sym(s);
     return OD_OK;
 }
 
@@ -595,6 +684,9 @@ od_status launch_step(od_system* s, bool timed)
                 s->xs_sorted, s->slab_start, s->cut_fix, s->pa, s->ca, s->ctl);
             odk::pair_cut_epilogue<<<nb, 256, 0, s->stream>>>(s->xs_sorted, s->idx_sorted, s->cut_fix,
                                                                (float*)s->a, s->pa, s->ds, s->ctl);
+        } else if (k == 0 && s->mesh && s->direct_steps == 0) {
+            HIPCHK(odk::mesh_launch(s->ma, s->mb, (const float*)s->x, s->Npad, s->acc_fix, s->Npad, s->pa.sym_scale,
+                                    &s->ctl->status, s->stream));
         } else if (k == 0 && s->sym) {
             if (s->n_sym_items > 0)     // none in test-particle mode
                 odk::pair_sym_kernel<kPairBlock><<<s->n_sym_items, kPairBlock, 0, s->stream>>>(
@@ -732,7 +824,15 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
                              (size_t)odk::kSlots * odk::lost_cap(s->Npad / 256) * sizeof(int2), sizeof(odk::Ctl)};
     size_t at[7] = {0};
     for (int k = 0; k < 6; ++k) at[k + 1] = at[k] + (sizes[k] + 255) / 256 * 256;
-    s->mem = dev_alloc(s, at[6]);
+    // with room for the default pair sum
+    const size_t fix = s->prec == OD_PREC_FP32 ? fix_bytes(s) : 0;
+    bool roomy = true;
+    s->mem = dev_alloc(s, at[6] + fix);
+    if (!s->mem) {
+        (void)hipGetLastError();
+        roomy = false;
+        s->mem = dev_alloc(s, at[6]);
+    }
     if (!s->mem) {
         od_destroy(s);
         return fail(OD_ENOMEM, "device allocation of %zu bytes failed", at[6]);
@@ -765,6 +865,7 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         od_destroy(s);
         return fail(OD_EDEVICE, "init kernel launch failed: %s", hipGetErrorString(e));
     }
+    (void)plan_mesh(s);                 // while the device draws the initial state
     st = read_status(s);
     if (st == OD_OK && (sim->flags & OD_FLAG_CONFINEMENT)) {
         // the grid's sums use the acceleration planes, which no step has
@@ -785,7 +886,8 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         s->pa = c.pa;
         s->fa = c.fa;
     }
-    if (st == OD_OK) st = apply_pair_kind(s);
+    if (st == OD_OK)
+        st = apply_pair_kind(s, roomy && fix ? base + at[6] : nullptr);
     if (st != OD_OK) {
         od_destroy(s);
         return st;
@@ -799,6 +901,15 @@ od_status od_step(od_system* s, int64_t n_steps)
     if (!s) return fail(OD_EINVAL, "null system");
     if (n_steps < 0) return fail(OD_EINVAL, "n_steps < 0");
     int64_t left = n_steps;
+    if (left > 0) {
+        const od_status st = first_step_setup(s);
+        if (st != OD_OK) return st;
+    }
+    for (; s->direct_steps > 0 && left > 0; --left) {
+        od_status st = launch_step(s, s->timing);
+        if (st != OD_OK) return st;
+        --s->direct_steps;
+    }
     if (s->graph_steps > 0 && !s->timing) {
         if (!s->gexec && left >= s->graph_steps) {
             od_status st = capture_graph(s);
@@ -869,6 +980,7 @@ void od_destroy(od_system* s)
     drop_graph(s);
     free_cutoff(s);
     free_sym(s);
+    free_mesh(s);
     dev_free(s, s->hist);
     dev_free(s, s->mem);
     for (hipEvent_t e : s->evpool) (void)hipEventDestroy(e);
@@ -1020,9 +1132,12 @@ od_status od_set_state(od_system* s, const void* x, const void* v, const double*
         for (int64_t k = 0; k < 3 * N; ++k)
             if (!std::isfinite(val(p, k))) return fail(OD_ENUMERIC, "non-finite state value at %lld", (long long)k);
     }
+    bool outside = false;
     if (x) {
+        const double Ro = s->pu.R * (1.0 + 1e-6), Ho = 0.5 * s->pu.H * (1.0 + 1e-6);
         for (int64_t i = 0; i < N; ++i) {
             const double px = val(x, i), py = val(x, N + i), pz = val(x, 2 * N + i);
+            outside = outside || std::fabs(px) > Ro || std::fabs(py) > Ro || std::fabs(pz) > Ho;
             for (int d = 0; d < s->nd; ++d) {
                 const double a0 = px - s->ds.pos[d][0], a1 = py - s->ds.pos[d][1], a2 = pz - s->ds.pos[d][2];
                 if (a0 * a0 + a1 * a1 + a2 * a2 <= s->ds.rad2[d])
@@ -1035,6 +1150,12 @@ od_status od_set_state(od_system* s, const void* x, const void* v, const double*
             if (!std::isfinite(q[d])) return fail(OD_ENUMERIC, "non-finite charge");
     HIPCHK(hipStreamSynchronize(s->stream));
     drop_graph(s);
+    // ions outside the domain leave it in the next step; until then the grid cannot hold them
+    if (x) s->direct_steps = outside ? 1 : 0;
+    if (outside && s->sym) {
+        const od_status st = setup_items(s, s->stream);
+        if (st != OD_OK) return st;
+    }
     const size_t row = (size_t)N * s->esz;
     const size_t drow = (size_t)s->Npad * s->esz;
     for (int c = 0; c < 3; ++c) {
