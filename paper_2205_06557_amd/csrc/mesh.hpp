@@ -10,11 +10,11 @@
 //   mesh_bin_kernel      sort bin of every ion: column of kx x kx cells, slice
 //                        along z; arrival number within the bin (atomic)
 //   mesh_scan_kernel     per column, prefix sum over its bins
-//   mesh_cols_kernel     prefix over columns, each padded to whole 64-ion tiles
+//   mesh_cols_kernel     prefix over columns, each padded to whole groups of 16
 //   mesh_place_kernel    ion index to its bin's slots, in arrival order
 //   mesh_order_kernel    slots of a bin put in ion order (arrival order depends
 //                        on scheduling, ion order does not); sorted positions
-//   mesh_box_kernel      bounding box of every 16 sorted ions
+//   mesh_box_kernel      bounding box of every 8 sorted ions
 //   mesh_spread_kernel   charges to the grid, one brick of cells per block, in
 //                        LDS as int64 fixed point (order-free)
 //   mesh_sum_kernel      overlapping brick margins added
@@ -42,8 +42,8 @@ struct MeshBufs {
     int* col;              // [columns + 1] first slot of each column
     int* temp;             // [cap] ions in arrival order, -1 where a column is padded
     int* idx;              // [cap] ion of each sorted slot, -1 for padding
-    float* s;              // [3][cap] sorted positions
-    float* box;            // [6][cap / 16] min x, y, z, max x, y, z
+    float4* s;             // [cap] sorted positions
+    float* box;            // [6][cap / 8] min x, y, z, max x, y, z of 8 sorted ions
     double* far;           // [3][cap] far part by sorted slot
     double* green;         // [M][ng] Green's tables
     float* near0;          // constant term of the near polynomial (mesh_zero_kernel)
@@ -163,9 +163,7 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
     const int i = b.temp[t];
     if (i < 0) {
         b.idx[t] = -1;
-        b.s[t] = (float)m.R + 2.0f;
-        b.s[m.cap + t] = (float)m.R + 2.0f;
-        b.s[2 * (long long)m.cap + t] = (float)m.Hh + 2.0f;
+        b.s[t] = make_float4((float)m.R + 2.0f, (float)m.R + 2.0f, (float)m.Hh + 2.0f, 0.0f);
         return;
     }
     const int key = b.key[i];
@@ -175,21 +173,21 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
     int to = s0;
     for (int k = s0; k < s1; ++k) to += b.temp[k] < i;
     b.idx[to] = i;
-    b.s[to] = x[i];
-    b.s[m.cap + to] = x[plane + i];
-    b.s[2 * (long long)m.cap + to] = x[2 * plane + i];
+    b.s[to] = make_float4(x[i], x[plane + i], x[2 * plane + i], 0.0f);
 }
 
-// Bounding box of every 16 sorted ions (empty: an inverted box).
+// Bounding box of every 8 sorted ions (empty: an inverted box).
 __global__ __launch_bounds__(256) void mesh_box_kernel(MeshArgs m, MeshBufs b)
 {
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= b.col[m.ncx * m.ncy]) return;     // a multiple of 64
+    if (t >= b.col[m.ncx * m.ncy]) return;     // a multiple of 16
     const bool live = b.idx[t] >= 0;
     const int ns = m.cap / kMeshSub;
+    const float4 p = b.s[t];
+    const float at[3] = {p.x, p.y, p.z};
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const float v = b.s[(long long)c * m.cap + t];
+        const float v = at[c];
         float lo = live ? v : 1.0e30f, hi = live ? v : -1.0e30f;
 #pragma unroll
         for (int d = 1; d < kMeshSub; d <<= 1) {
@@ -279,7 +277,8 @@ __global__ __launch_bounds__(256) void mesh_spread_kernel(MeshArgs m, MeshBufs b
     const int g2 = m.g * m.g, cnt = runs.pre[64];
     for (int k = threadIdx.x; k < cnt; k += 256) {
         const int t = mesh_brick_slot(runs, g2, k);
-        const double px = b.s[t], py = b.s[m.cap + t], pz = b.s[2 * (long long)m.cap + t];
+        const float4 p = b.s[t];
+        const double px = p.x, py = p.y, pz = p.z;
         const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]), cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]),
                   cz = mesh_cell(pz, -m.Hh, m.inv_h, m.nc[2]);
         const double ux = (px + m.R) * m.inv_h - cx, uy = (py + m.R) * m.inv_h - cy,
@@ -458,7 +457,8 @@ __global__ __launch_bounds__(256) void mesh_gather_kernel(MeshArgs m, MeshBufs b
     __syncthreads();
     for (int k = threadIdx.x; k < cnt; k += 256) {
         const int t = mesh_brick_slot(runs, g2, k);
-        const double px = b.s[t], py = b.s[m.cap + t], pz = b.s[2 * (long long)m.cap + t];
+        const float4 p = b.s[t];
+        const double px = p.x, py = p.y, pz = p.z;
         const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]), cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]),
                   cz = mesh_cell(pz, -m.Hh, m.inv_h, m.nc[2]);
         const double ux = (px + m.R) * m.inv_h - cx, uy = (py + m.R) * m.inv_h - cy,
@@ -491,9 +491,9 @@ __global__ __launch_bounds__(256) void mesh_gather_kernel(MeshArgs m, MeshBufs b
                 double r0 = 0.0, r1 = 0.0;
 #pragma unroll
                 for (int jx = 0; jx < kMeshP; ++jx) {
-                    const double p = node[at + jx];
-                    r0 = fma(p, dx[jx], r0);
-                    r1 = fma(p, wx[jx], r1);
+                    const double v = node[at + jx];
+                    r0 = fma(v, dx[jx], r0);
+                    r1 = fma(v, wx[jx], r1);
                 }
                 a0 = fma(r0, wy[jy], a0);
                 a1 = fma(r1, dy[jy], a1);
@@ -540,159 +540,230 @@ __global__ void mesh_zero_kernel(MeshArgs m, float* near0)
     if (threadIdx.x == 0) *near0 = c;
 }
 
-// Near pairs of one 64-ion tile by S waves.  First the waves share the search:
-// the columns within r_c of the tile's box and, in each, the slots within r_c
-// along z, 64 boxes of 16 ions at a time against the tile's box; the boxes
-// kept are listed in LDS.  Then the waves take the listed boxes in turn: every
-// lane holds a target and the 16 sources come through the scalar cache, one
-// register operand each, so a pair costs its arithmetic and no LDS or vector
-// load.  FP32 terms, FP64 sums of every 16.  Bound by FP32 issue.
-constexpr int kMeshList = 256;      // listed boxes per wave; further ones are done at once
+// Near pairs.  A block of S waves takes 64 sorted ions, as four groups of 16
+// with a box each; quarter q of every wave holds group q's targets.
+//
+// Search: the waves share the columns within r_c of the groups' boxes and list
+// in LDS, per group, the boxes of 8 ions within r_c of the group's.  Then the
+// waves take the listed boxes of each group two at a time: the quarter's lanes
+// load the 16 sources (the next ones while the present are worked on), pass
+// them through LDS and read them back one by one, the same for the quarter.
+// FP32 terms, FP64 sums of every 16.
+//
+// Bound by FP32 issue (31 slots a pair), so what counts is how few pairs
+// beyond r_c are evaluated: 3.3 times the pairs within r_c with groups of 16
+// and boxes of 8, 5.8 with 64 and 16 and wider columns, whose sources could be
+// scalar loads: at 2^20 ions 2.9 ms with r_c = 0.39, where the wider search took 3.7 ms with 0.33.
+constexpr int kMeshList = 64;       // boxes a wave lists per group in a round
+constexpr int kMeshCand = 64;       // candidate columns per group of a round
 
 template <int S>
-__global__ __launch_bounds__(64 * S) void mesh_near_kernel(MeshArgs m, MeshBufs b,
-                                                           unsigned long long* __restrict__ fix, long long fstride,
-                                                           double scale, int* status)
+__global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(6, 8)))
+void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* __restrict__ box,
+                      const int* __restrict__ rel_, const int* __restrict__ col, const int* __restrict__ idx,
+                      const double* __restrict__ far, const float* __restrict__ near0_,
+                      unsigned long long* __restrict__ fix, long long fstride, double scale, int* status)
 {
-    __shared__ int list[S][kMeshList];
-    __shared__ int listed[S];
-    __shared__ int2 cand[256];
-    __shared__ int ncand;
-    __shared__ double part[S][3][kMeshTile];
-    const int ncol = m.ncx * m.ncy;
+    __shared__ int seg[S][4][kMeshList];            // boxes listed by each wave
+    __shared__ int list[4][S * kMeshList];          // the same, one after the other
+    __shared__ int listed[4][S];
+    __shared__ int full[S];
+    __shared__ int2 cand[4][kMeshCand];
+    __shared__ float4 src[S][64];
+    __shared__ double part[S][3][64];
+    const int total = col[m.ncx * m.ncy];
     // consecutive tiles share sources: give each of the 8 XCDs a run of them
-    const int tiles = b.col[ncol] / kMeshTile;
-    const int per = (tiles + 7) / 8;
+    const int tiles = (total + 63) / 64, per = (tiles + 7) / 8;
     const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if ((int)(blockIdx.x >> 3) >= per || tile >= tiles) return;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int slot = tile * kMeshTile + lane;
-    const float* __restrict__ X = b.s;
-    const float* __restrict__ Y = b.s + m.cap;
-    const float* __restrict__ Z = b.s + 2 * (long long)m.cap;
-    const float xi = X[slot], yi = Y[slot], zi = Z[slot];
+    const int q = lane >> 4, l16 = lane & 15;
+    const int slot = tile * 64 + lane;
+    const bool here = slot < total;                 // the same for a group
+    const float4 me = pos[here ? slot : 0];
     const int ns = m.cap / kMeshSub;
-    // the tile's box
-    float lo[3], hi[3];
+    float lo[3], hi[3];                             // the group's box
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const float4 l = *(const float4*)&b.box[(long long)c * ns + tile * 4];
-        const float4 h = *(const float4*)&b.box[(long long)(c + 3) * ns + tile * 4];
-        lo[c] = fminf(fminf(l.x, l.y), fminf(l.z, l.w));
-        hi[c] = fmaxf(fmaxf(h.x, h.y), fmaxf(h.z, h.w));
+        const float2 l = *(const float2*)&box[(long long)c * ns + (tile * 4 + q) * 2];
+        const float2 h = *(const float2*)&box[(long long)(c + 3) * ns + (tile * 4 + q) * 2];
+        lo[c] = here ? fminf(l.x, l.y) : 1.0e30f;
+        hi[c] = here ? fmaxf(h.x, h.y) : -1.0e30f;
     }
-    const float R = (float)m.R, icw = 1.0f / m.cw, slack = 1.0e-4f * m.rc;
-    auto column = [&](float v, int nc) { return (int)fminf(fmaxf(floorf((v + R) * icw), 0.0f), (float)(nc - 1)); };
-    const int x0 = column(lo[0] - m.rc, m.ncx), x1 = column(hi[0] + m.rc, m.ncx);
-    const int y0 = column(lo[1] - m.rc, m.ncy), y1 = column(hi[1] + m.rc, m.ncy);
-    const int nx = x1 - x0 + 1, all = nx > 0 && y1 >= y0 ? nx * (y1 - y0 + 1) : 0;    // a tile of NaNs has no box
-    const float near0 = b.near0[0];
+    const float R = (float)m.R, icw = 1.0f / m.cw, slack = 1.0e-4f * m.rc, near0 = near0_[0];
     double sx = 0.0, sy = 0.0, sz = 0.0;
 
-    auto pairs = [&](int sub) {
-        const int j0 = sub * kMeshSub;
-        float ax = 0.0f, ay = 0.0f, az = 0.0f;
-        const int self = (sub >> 2) == tile ? lane - (sub & 3) * kMeshSub : -1;
-        const bool own = (sub >> 2) == tile;
-        float qx[kMeshSub], qy[kMeshSub], qz[kMeshSub];
+    // where the search goes on: candidate columns from c0, candidate t0, its box o0 (t0, o0 per
+    // group and wave)
+    int c0 = 0, t0 = 0, o0 = 0;
+    bool fresh = true;
+    for (;;) {
+        if (fresh) {
+            // candidate columns of each group: slots within r_c along z, as runs of boxes.
+            // Thread t works for group t % 4, whose box it needs
+            __syncthreads();
+            const int g = threadIdx.x & 3;
+            float glo[3], ghi[3];
 #pragma unroll
-        for (int k = 0; k < kMeshSub; ++k) {
-            qx[k] = X[j0 + k];
-            qy[k] = Y[j0 + k];
-            qz[k] = Z[j0 + k];
-        }
-        auto term = [&](int k, bool skip) {
-            const float dx = xi - qx[k], dy = yi - qy[k], dz = zi - qz[k];
-            float f = mesh_near_f(m, near0, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
-            if (skip) f = k == self ? 0.0f : f;
-            ax = fmaf(f, dx, ax);
-            ay = fmaf(f, dy, ay);
-            az = fmaf(f, dz, az);
-        };
-        if (own) {
-#pragma unroll
-            for (int k = 0; k < kMeshSub; ++k) term(k, true);
-        } else {
-#pragma unroll
-            for (int k = 0; k < kMeshSub; ++k) term(k, false);
-        }
-        sx += (double)ax;
-        sy += (double)ay;
-        sz += (double)az;
-    };
-
-    int n = 0;
-    for (int c0 = 0; c0 < all; c0 += 256) {
-        // candidate columns: slots within r_c along z, as runs of boxes
-        __syncthreads();
-        const int have = min(256, all - c0);
-        for (int t = threadIdx.x; t < have; t += 64 * S) {
-            const int cx = x0 + (c0 + t) % nx, cy = y0 + (c0 + t) / nx;
-            // the outer columns also hold ions that sit on the boundary to rounding
-            const float gx = fmaxf(0.0f, fmaxf(cx * m.cw - R - hi[0], lo[0] - ((cx + 1) * m.cw - R)) - slack);
-            const float gy = fmaxf(0.0f, fmaxf(cy * m.cw - R - hi[1], lo[1] - ((cy + 1) * m.cw - R)) - slack);
-            const float left = m.rc2 - gx * gx - gy * gy;
-            int2 e = make_int2(0, 0);
-            if (left > 0.0f) {
-                const float dz = sqrtf(left) + slack;
-                const int c = cy * m.ncx + cx;
-                const int* rel = b.rel + (long long)c * (m.nzb + 1);
-                const int s0 = rel[mesh_zbin(lo[2] - dz, m)], s1 = rel[mesh_zbin(hi[2] + dz, m) + 1];
-                if (s1 > s0) {
-                    const int first = (b.col[c] + s0) / kMeshSub;
-                    e = make_int2(first, (b.col[c] + s1 + kMeshSub - 1) / kMeshSub - first);
-                }
+            for (int c = 0; c < 3; ++c) {
+                glo[c] = __shfl(lo[c], g * 16, 64);
+                ghi[c] = __shfl(hi[c], g * 16, 64);
             }
-            cand[t] = e;
+            auto column = [&](float v, int nc) { return (int)fminf(fmaxf(floorf((v + R) * icw), 0.0f), (float)(nc - 1)); };
+            const int x0 = column(glo[0] - m.rc, m.ncx), x1 = column(ghi[0] + m.rc, m.ncx);
+            const int y0 = column(glo[1] - m.rc, m.ncy), y1 = column(ghi[1] + m.rc, m.ncy);
+            const int nx = x1 - x0 + 1, all = nx > 0 && y1 >= y0 && glo[2] <= ghi[2] ? nx * (y1 - y0 + 1) : 0;
+            for (int t = threadIdx.x >> 2; t < kMeshCand; t += 16 * S) {
+                int2 e = make_int2(0, 0);
+                if (c0 + t < all) {
+                    const int cx = x0 + (c0 + t) % nx, cy = y0 + (c0 + t) / nx;
+                    // the outer columns also hold ions that sit on the boundary to rounding
+                    const float gx = fmaxf(0.0f, fmaxf(cx * m.cw - R - ghi[0], glo[0] - ((cx + 1) * m.cw - R)) - slack);
+                    const float gy = fmaxf(0.0f, fmaxf(cy * m.cw - R - ghi[1], glo[1] - ((cy + 1) * m.cw - R)) - slack);
+                    const float left = m.rc2 - gx * gx - gy * gy;
+                    if (left > 0.0f) {
+                        const float dz = sqrtf(left) + slack;
+                        const int c = cy * m.ncx + cx;
+                        const int* rel = rel_ + (long long)c * (m.nzb + 1);
+                        const int s0 = rel[mesh_zbin(glo[2] - dz, m)], s1 = rel[mesh_zbin(ghi[2] + dz, m) + 1];
+                        if (s1 > s0) {
+                            const int first = (col[c] + s0) / kMeshSub;
+                            e = make_int2(first, (col[c] + s1 + kMeshSub - 1) / kMeshSub - first);
+                        }
+                    }
+                }
+                cand[g][t] = e;
+            }
+            __syncthreads();
+            t0 = wv;
+            o0 = 0;
         }
-        __syncthreads();
-        int unit = 0;
-        for (int t = 0; t < have; ++t) {
-            const int2 e = cand[t];
-            const int first = __builtin_amdgcn_readfirstlane(e.x), len = __builtin_amdgcn_readfirstlane(e.y);
-            for (int o = 0; o < len; o += 64, ++unit) {
-                if (unit % S != wv) continue;
-                const int sub = first + o + lane;
-                bool keep = false;
-                if (o + lane < len) {
-                    const float gx = fmaxf(0.0f, fmaxf(b.box[sub] - hi[0], lo[0] - b.box[3ll * ns + sub]));
-                    const float gy = fmaxf(0.0f, fmaxf(b.box[ns + sub] - hi[1], lo[1] - b.box[4ll * ns + sub]));
-                    const float gz = fmaxf(0.0f, fmaxf(b.box[2ll * ns + sub] - hi[2], lo[2] - b.box[5ll * ns + sub]));
+        // this wave's candidates of each group, 16 boxes at a time
+        int n = 0;
+        bool stop = false;
+        while (__any(t0 < kMeshCand && !stop)) {
+            bool keep = false;
+            int sub = 0;
+            const bool on = t0 < kMeshCand && !stop;
+            int2 e = make_int2(0, 0);
+            if (on) {
+                e = cand[q][t0];
+                sub = e.x + o0 + l16;
+                if (o0 + l16 < e.y) {
+                    const float gx = fmaxf(0.0f, fmaxf(box[sub] - hi[0], lo[0] - box[3ll * ns + sub]));
+                    const float gy = fmaxf(0.0f, fmaxf(box[ns + sub] - hi[1], lo[1] - box[4ll * ns + sub]));
+                    const float gz = fmaxf(0.0f, fmaxf(box[2ll * ns + sub] - hi[2], lo[2] - box[5ll * ns + sub]));
                     keep = gx * gx + gy * gy + gz * gz < m.rc2;
                 }
-                unsigned long long mask = __ballot(keep);
-                const int k = __popcll(mask);
-                if (n + k <= kMeshList) {
-                    if (keep) list[wv][n + __popcll(mask & ((1ull << lane) - 1ull))] = sub;
-                    n += k;
+            }
+            const unsigned mask = (unsigned)(__ballot(keep) >> (q * 16)) & 0xffffu;
+            const int k = __popc(mask);
+            if (on) {
+                if (n + k > kMeshList) {
+                    stop = true;                    // the list is full: go on here in the next round
                 } else {
-                    for (; mask; mask &= mask - 1) pairs(first + o + __ffsll((long long)mask) - 1);
+                    if (keep) seg[wv][q][n + __popc(mask & ((1u << l16) - 1u))] = sub;
+                    n += k;
+                    o0 += 16;
+                    if (o0 >= e.y) {
+                        t0 += S;
+                        o0 = 0;
+                    }
                 }
             }
         }
-    }
-    if (lane == 0) listed[wv] = n;
-    __syncthreads();
-    int total = 0;
-    for (int w = 0; w < S; ++w) total += __builtin_amdgcn_readfirstlane(listed[w]);
-    for (int k = wv; k < total; k += S) {
-        int w = 0, o = k;
-        for (int c; o >= (c = __builtin_amdgcn_readfirstlane(listed[w])); ++w) o -= c;
-        pairs(__builtin_amdgcn_readfirstlane(list[w][o]));
+        if (l16 == 0) listed[q][wv] = n;
+        const bool again = __any(stop);
+        if (lane == 0) full[wv] = again;
+        __syncthreads();
+        // one list per group
+        int before = 0, count = 0, unfinished = 0;
+#pragma unroll
+        for (int w = 0; w < S; ++w) {
+            const int k = listed[q][w];
+            before += w < wv ? k : 0;
+            count += k;
+            unfinished |= full[w];
+        }
+        for (int k = l16; k < n; k += 16) list[q][before + k] = seg[wv][q][k];
+        __syncthreads();
+        // two boxes at a time; the last of an odd number is paired with a point beyond r_c
+        const float far_point = (float)m.R + 2.0f;
+        auto load = [&](int k) {
+            const int e = 2 * k + (l16 >> 3);
+            float4 p = make_float4(far_point, far_point, far_point, 0.0f);
+            int from = -1;
+            if (e < count) {
+                from = list[q][e] * kMeshSub + (l16 & 7);
+                p = pos[from];
+            }
+            p.w = __builtin_bit_cast(float, from);
+            return p;
+        };
+        const int batches = (count + 1) / 2;
+        float4 next = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        if (wv < batches) next = load(wv);
+        for (int k = wv; k < batches; k += S) {
+            src[wv][lane] = next;
+            const bool own = __any(__builtin_bit_cast(int, next.w) >> 4 == slot >> 4);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            if (k + S < batches) next = load(k + S);
+            float ax = 0.0f, ay = 0.0f, az = 0.0f;
+            if (own) {
+#pragma unroll 4
+                for (int u = 0; u < 16; ++u) {
+                    const float4 p = src[wv][q * 16 + u];
+                    const float dx = me.x - p.x, dy = me.y - p.y, dz = me.z - p.z;
+                    float f = mesh_near_f(m, near0, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+                    f = __builtin_bit_cast(int, p.w) == slot ? 0.0f : f;
+                    ax = fmaf(f, dx, ax);
+                    ay = fmaf(f, dy, ay);
+                    az = fmaf(f, dz, az);
+                }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const float4 p = src[wv][q * 16 + u];
+                    const float dx = me.x - p.x, dy = me.y - p.y, dz = me.z - p.z;
+                    const float f = mesh_near_f(m, near0, fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
+                    ax = fmaf(f, dx, ax);
+                    ay = fmaf(f, dy, ay);
+                    az = fmaf(f, dz, az);
+                    if (u % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            sx += (double)ax;
+            sy += (double)ay;
+            sz += (double)az;
+        }
+        fresh = !unfinished;
+        if (fresh) {
+            c0 += kMeshCand;
+            // further candidate columns of any group?
+            bool more = false;
+            const float w = 2.0f * m.rc;
+            if (lo[2] <= hi[2])
+                more = (floorf((hi[0] - lo[0] + w) * icw) + 2.0f) * (floorf((hi[1] - lo[1] + w) * icw) + 2.0f) > (float)c0;
+            if (!__any(more)) break;
+        }
+        __syncthreads();
     }
     part[wv][0][lane] = sx;
     part[wv][1][lane] = sy;
     part[wv][2][lane] = sz;
     __syncthreads();
-    if (wv != 0) return;
-    const int i = b.idx[slot];
+    if (wv != 0 || !here) return;
+    const int i = idx[slot];
     if (i < 0) return;
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
         double t = part[0][c][lane];
 #pragma unroll
         for (int w = 1; w < S; ++w) t += part[w][c][lane];
-        fix[c * fstride + i] = to_fixed(t + b.far[(long long)c * m.cap + slot], scale, status);
+        fix[c * fstride + i] = to_fixed(t + far[(long long)c * m.cap + slot], scale, status);
     }
 }
 
@@ -716,7 +787,7 @@ inline size_t mesh_layout(const MeshArgs& m, char* base, MeshBufs& b)
     take(&b.col, (ncol + 1) * 4);
     take(&b.temp, cap * 4);
     take(&b.idx, cap * 4);
-    take(&b.s, 3 * cap * 4);
+    take(&b.s, cap * 16);
     take(&b.box, 6 * (cap / kMeshSub) * 4);
     take(&b.far, 3 * cap * 8);
     take(&b.green, (size_t)kMeshM * m.ng * 8);
@@ -775,11 +846,13 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
         mesh_conv_kernel<2><<<dim3(lines((long long)nx * ny), lines(nz), 1), 256, tab, st>>>(m, b.t2, b.phi, b.green, m0, mc, m0 > 0);
     }
     mesh_gather_kernel<<<bricks, 256, lds, st>>>(m, b);
-    const int tiles = (m.cap / kMeshTile + 7) / 8 * 8;
-    if (m.cap / kMeshTile >= 8192)
-        mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b, fix, fstride, scale, status);
+    const int tiles = (m.cap / 64 + 7) / 8 * 8;
+    if (m.cap / 64 >= 8192)
+        mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, fix, fstride,
+                                                   scale, status);
     else
-        mesh_near_kernel<8><<<tiles, 512, 0, st>>>(m, b, fix, fstride, scale, status);
+        mesh_near_kernel<8><<<tiles, 512, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, fix, fstride,
+                                                   scale, status);
     return hipGetLastError();
 }
 

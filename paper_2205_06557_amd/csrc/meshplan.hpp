@@ -29,12 +29,13 @@ constexpr int kMeshNearDeg = 12;    // degree of the near part's polynomial in 1
 constexpr double kMeshBeta = 22.0;  // Kaiser-Bessel shape
 constexpr double kMeshRatio = 7.5;  // r_c / h
 constexpr double kMeshTop = 2.8;    // t_max r_c
-constexpr int kMeshSub = 16;        // sources per box of the near search
-constexpr int kMeshTile = 64;       // targets per tile
+constexpr int kMeshSub = 8;         // ions per box of the near search
+constexpr double kMeshCol = 27.0;   // ions per column over a height of its width
+constexpr int kMeshTile = 16;       // ions per group of targets
 
 // Constants of one system's split, passed to the kernels by value.
 struct MeshArgs {
-    int N, cap;                     // ions; sorted slots (columns padded to whole tiles)
+    int N, cap;                     // ions; sorted slots (columns padded to whole groups)
     int nc[3], n[3];                // grid cells and nodes (nc + 9) per axis
     int kx, ncx, ncy;               // column width in cells; columns along x and y
     int zsub, nzb;                  // sort bins per cell along z; bins per column
@@ -126,20 +127,13 @@ inline double mesh_i0(double x)
     return s;
 }
 
-// Volume swept by a box of sides (a, b, c) and a ball of radius r.
-inline double mesh_swept(double a, double b, double c, double r)
-{
-    const double pi = 3.14159265358979323846;
-    return a * b * c + 2.0 * r * (a * b + b * c + c * a) + pi * r * r * (a + b + c) + 4.0 / 3.0 * pi * r * r * r;
-}
-
 // Grid and columns for a near radius; false if the domain is outside what the
 // split is made for.
 inline bool mesh_dims(double N, double R, double H, double rc, MeshArgs& a)
 {
     const double pi = 3.14159265358979323846;
     const double n = N / (pi * R * R * H);
-    const double h = rc / kMeshRatio, b = std::cbrt(kMeshTile / n);
+    const double h = rc / kMeshRatio, b = std::cbrt(kMeshCol / n);
     a.h = h;
     a.inv_h = 1.0 / h;
     a.R = R;
@@ -161,36 +155,31 @@ inline bool mesh_dims(double N, double R, double H, double rc, MeshArgs& a)
     return true;
 }
 
-// The split of a system of N ions (dimensionless R, H).  Chooses r_c by a cost
-// model (microseconds, MI355X): near pairs at kNear per 64, the convolutions'
-// 64-bit matrix rate, and the grid's traffic.  False: use the direct sum.
+// The split of a system of N ions (dimensionless R, H).  False: use the direct
+// sum.
+//
+// r_c trades near pairs (r_c^3) against the grid (its nodes go as r_c^-3, the
+// convolutions as r_c^-4) and scales with the ion spacing: in units of
+// (27 / n)^(1/3), a pair sum took 0.80 ms at 1.4, 0.76 at 1.6, 0.79 at 1.7,
+// 0.93 at 1.9 and 0.95 at 2.0 for 2^17 ions; 1.68, 1.28, 1.25, 1.41 and 1.43
+// for 2^18; 6.1, 5.6, 4.9, 4.6 and 4.7 for 2^20.
 inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
 {
     const double diag = std::sqrt(4.0 * R * R + H * H);
     if (diag > 24.0 || N < 1024 || N > (1ll << 26)) return false;
     const double pi = 3.14159265358979323846;
-    const double n = (double)N / (pi * R * R * H), b = std::cbrt(kMeshTile / n);
-    double best = 0.0, rc = 0.0;
-    for (double q = 0.9; q <= 4.0; q *= 1.04) {
+    const double n = (double)N / (pi * R * R * H), b = std::cbrt(kMeshCol / n);
+    double rc = 0.0;
+    for (double q = 1.75; q <= 6.0 && rc == 0.0; q *= 1.04) {
         const double r = q * b;
-        if (r > 1.5 || r < 0.1 || r > 0.45 * diag) continue;
-        MeshArgs t{};
-        if (!mesh_dims((double)N, R, H, r, t)) continue;
-        const double v = (double)t.n[0] * t.n[1] * t.n[2];
-        if (v > 3.0e7) continue;
-        const double s = t.kx * t.h, dz = kMeshTile / (n * s * s);
-        const double pairs = (double)N * std::min((double)N, n * mesh_swept(2 * s, 2 * s, 1.25 * dz, r));
-        const double near = pairs / 64.0 * 0.050e-3;
-        const double conv = 2.0 * kMeshM * v * (t.n[0] + t.n[1] + t.n[2]) / 40.0e6 + v * kMeshM * 32.0 / 3.0e6;
-        const double cost = near + conv + v * 7.0 * 24.0 / 3.0e6;
-        if (rc == 0.0 || cost < best) {
-            best = cost;
-            rc = r;
-        }
+        if (r < 0.1) continue;
+        if (r > 2.5 || r > 0.45 * diag) return false;
+        // a larger r_c where the grid would have too many nodes
+        if (mesh_dims((double)N, R, H, r, a) && (double)a.n[0] * a.n[1] * a.n[2] <= 3.0e7) rc = r;
     }
-    if (rc == 0.0 || !mesh_dims((double)N, R, H, rc, a)) return false;
+    if (rc == 0.0) return false;
     a.N = (int)N;
-    const long long cap = (N + 63ll * a.ncx * a.ncy + 63) / 64 * 64;
+    const long long cap = (N + (kMeshTile - 1ll) * a.ncx * a.ncy + 63) / 64 * 64;
     if (cap > (1ll << 28)) return false;
     a.cap = (int)cap;
     // bricks of about 10 cells a side (smaller for small systems, so that the
