@@ -15,8 +15,8 @@
 //   mesh_order_kernel    slots of a bin put in ion order (arrival order depends
 //                        on scheduling, ion order does not); sorted positions
 //   mesh_box_kernel      bounding box of every 8 sorted ions
-//   mesh_spread_kernel   charges to the grid, one brick of cells per block, in
-//                        LDS as int64 fixed point (order-free)
+//   mesh_spread_kernel   charges to the grid, one brick of cells per block
+//                        (64-bit MFMA; bricks in LDS as int64, order-free)
 //   mesh_sum_kernel      overlapping brick margins added
 //   mesh_conv_kernel     Gaussian convolutions along x, y and z (64-bit MFMA)
 //   mesh_gather_kernel   far acceleration of every ion, from bricks in LDS
@@ -62,7 +62,7 @@ __device__ __forceinline__ int mesh_cell(double x, double lo, double inv_h, int 
 
 __device__ __forceinline__ int mesh_zbin(double z, const MeshArgs& m)
 {
-    return (int)fmin(fmax(floor((z + m.Hh) * (m.inv_h * m.zsub)), 0.0), (double)(m.nzb - 1));
+    return (int)fmin(fmax(floor((z + m.Hh) * (m.inv_h * kMeshZsub)), 0.0), (double)(m.nzb - 1));
 }
 
 // Sort bin of every ion; also marks every slot empty.
@@ -72,8 +72,8 @@ __global__ __launch_bounds__(256) void mesh_bin_kernel(const float* __restrict__
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < m.cap) b.temp[i] = -1;
     if (i >= m.N) return;
-    const int cx = mesh_cell(x[i], -m.R, m.inv_h, m.nc[0]) / m.kx;
-    const int cy = mesh_cell(x[plane + i], -m.R, m.inv_h, m.nc[1]) / m.kx;
+    const int cx = mesh_cell(x[i], -m.R, m.inv_h, m.nc[0]) / kMeshKx;
+    const int cy = mesh_cell(x[plane + i], -m.R, m.inv_h, m.nc[1]) / kMeshKx;
     const int key = (cy * m.ncx + cx) * m.nzb + mesh_zbin(x[2 * plane + i], m);
     b.key[i] = key;
     b.arr[i] = atomicAdd(&b.count[key], 1);
@@ -218,119 +218,126 @@ __device__ __forceinline__ double mesh_window(const MeshArgs& m, double u, int k
     return p;
 }
 
-// Slots of a brick's ions, column by column: start[k] .. start[k] + (pre[k+1] - pre[k]).
-struct BrickRuns {
-    int start[64], pre[65];
+// A brick is 4 x 4 columns of 4 x 4 cells and 7 cells along z; the ions of one
+// column reach 13 x 13 x 16 of its nodes.
+constexpr int kMeshReach = kMeshKx + kMeshP - 1;        // 13
+constexpr int kMeshThreads = 512;
+static_assert(kMeshReach <= 16 && kMeshBz + kMeshP - 1 == 16, "one MFMA tile spans a column's nodes");
+
+typedef double mesh4 __attribute__((ext_vector_type(4)));
+
+// Cells of a brick's column k and its ions' slots.
+struct MeshColumn {
+    int x, y, z;        // first cells
+    int s0, s1;         // slots
 };
 
-__device__ __forceinline__ void mesh_brick_runs(const MeshArgs& m, const MeshBufs& b, int bx, int by, int bz,
-                                                BrickRuns& r)
+__device__ __forceinline__ MeshColumn mesh_column(const MeshArgs& m, const MeshBufs& b, int k)
 {
-    const int g2 = m.g * m.g;
-    if (threadIdx.x < 64) {
-        int len = 0, s0 = 0;
-        if ((int)threadIdx.x < g2) {
-            const int cx = bx * m.g + threadIdx.x % m.g, cy = by * m.g + threadIdx.x / m.g;
-            if (cx < m.ncx && cy < m.ncy) {
-                const int c = cy * m.ncx + cx;
-                const int* rel = b.rel + (long long)c * (m.nzb + 1);
-                s0 = rel[min(bz * m.bz * m.zsub, m.nzb)];
-                len = rel[min((bz + 1) * m.bz * m.zsub, m.nzb)] - s0;
-                s0 += b.col[c];
-            }
-        }
-        int inc = len;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int u = __shfl_up(inc, d, 64);
-            if ((int)threadIdx.x >= d) inc += u;
-        }
-        r.start[threadIdx.x] = s0;
-        r.pre[threadIdx.x] = inc - len;
-        if (threadIdx.x == 63) r.pre[64] = inc;
+    MeshColumn c;
+    const int bx = blockIdx.x % m.nbx, by = blockIdx.x / m.nbx % m.nby, bz = blockIdx.x / (m.nbx * m.nby);
+    const int cx = bx * kMeshG + k % kMeshG, cy = by * kMeshG + k / kMeshG;
+    c.x = cx * kMeshKx;
+    c.y = cy * kMeshKx;
+    c.z = bz * kMeshBz;
+    c.s0 = c.s1 = 0;
+    if (cx < m.ncx && cy < m.ncy) {
+        const int col = cy * m.ncx + cx;
+        const int* rel = b.rel + (long long)col * (m.nzb + 1);
+        c.s0 = b.col[col] + rel[c.z * kMeshZsub];
+        c.s1 = b.col[col] + rel[min((c.z + kMeshBz) * kMeshZsub, m.nzb)];
     }
-    __syncthreads();
-}
-
-__device__ __forceinline__ int mesh_brick_slot(const BrickRuns& r, int g2, int k)
-{
-    int c = 0;
-    while (c + 1 < g2 && r.pre[c + 1] <= k) ++c;
-    return r.start[c] + (k - r.pre[c]);
+    return c;
 }
 
 // Fixed point of the grid charges: weights are at most 1, so a node holds
 // fewer than 2^26 of them.
-constexpr double kMeshScale = 137438953472.0;    // 2^37
+constexpr double kMeshScale = 68719476736.0;    // 2^36
 
-// Spreads the charges of one brick's ions onto the brick's nodes: a thread per
-// ion, int64 additions in LDS (exact, so the order in which ions arrive does
-// not matter).  Bound by the LDS atomics: 1,000 per ion.
-__global__ __launch_bounds__(256) void mesh_spread_kernel(MeshArgs m, MeshBufs b)
+// Spreads the charges of one brick's ions onto its nodes.  A wave takes a
+// column's ions 16 at a time, computes their weights on the column's nodes
+// (zero outside an ion's ten) and contracts over the ions,
+//   node[y][x][z] += sum_ions (w_x w_y) w_z,
+// 13 tiles of 16 x 16; a column's sums are added to the brick's in LDS as int64
+// (exact, so the order of the waves does not matter).  Adding every weight to
+// LDS instead, 1,000 additions an ion, was bound by the LDS's 2 additions per
+// clock: 135 us at 2^17 ions, 241 at 2^18 and 630 at 2^20, against 120, 171 and 505.
+__global__ __launch_bounds__(kMeshThreads) void mesh_spread_kernel(MeshArgs m, MeshBufs b)
 {
     extern __shared__ unsigned long long grid[];
-    __shared__ BrickRuns runs;
-    const int lx = m.bc + kMeshP - 1, lz = m.bz + kMeshP - 1, total = lx * lx * lz;
-    const int bx = blockIdx.x % m.nbx, by = blockIdx.x / m.nbx % m.nby, bz = blockIdx.x / (m.nbx * m.nby);
-    for (int k = threadIdx.x; k < total; k += 256) grid[k] = 0ull;
-    mesh_brick_runs(m, b, bx, by, bz, runs);
-    const int g2 = m.g * m.g, cnt = runs.pre[64];
-    for (int k = threadIdx.x; k < cnt; k += 256) {
-        const int t = mesh_brick_slot(runs, g2, k);
-        const float4 p = b.s[t];
-        const double px = p.x, py = p.y, pz = p.z;
-        const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]), cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]),
-                  cz = mesh_cell(pz, -m.Hh, m.inv_h, m.nc[2]);
-        const double ux = (px + m.R) * m.inv_h - cx, uy = (py + m.R) * m.inv_h - cy,
-                     uz = (pz + m.Hh) * m.inv_h - cz;
-        double wx[kMeshP], wy[kMeshP], dummy;
+    __shared__ double wt[kMeshThreads / 64][16][3][16];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c16 = lane & 15, q = lane >> 4;
+    for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) grid[k] = 0ull;
+    __syncthreads();
+    for (int k = wv; k < kMeshG * kMeshG; k += kMeshThreads / 64) {
+        const MeshColumn c = mesh_column(m, b, k);
+        if (c.s0 >= c.s1) continue;
+        mesh4 acc[kMeshReach];
 #pragma unroll
-        for (int j = 0; j < kMeshP; ++j) {
-            wx[j] = mesh_window<false>(m, ux, j, dummy);
-            wy[j] = mesh_window<false>(m, uy, j, dummy);
-        }
-        const int base = ((cz - bz * m.bz) * lx + (cy - by * m.bc)) * lx + (cx - bx * m.bc);
-#pragma unroll 1
-        for (int jz = 0; jz < kMeshP; ++jz) {
-            const double wz = mesh_window<false>(m, uz, jz, dummy) * kMeshScale;
-            int at = base + jz * lx * lx;
-#pragma unroll
-            for (int jy = 0; jy < kMeshP; ++jy) {
-                const double wzy = wz * wy[jy];
-#pragma unroll
-                for (int jx = 0; jx < kMeshP; ++jx) {
-                    // 1.5 2^52 + w has the rounded integer in its low bits
-                    const double f = fma(wzy, wx[jx], 6755399441055744.0);
-                    const unsigned long long w = __builtin_bit_cast(unsigned long long, f) - 0x4338000000000000ull;
-                    __hip_atomic_fetch_add(&grid[at + jx], w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-                }
-                at += lx;
+        for (int t = 0; t < kMeshReach; ++t) acc[t] = mesh4{0.0, 0.0, 0.0, 0.0};
+        for (int k0 = c.s0; k0 < c.s1; k0 += 16) {
+            __builtin_amdgcn_wave_barrier();
+            for (int e = lane; e < 16 * 48; e += 64) {
+                const int ion = e / 48, j = e - ion * 48, axis = j >> 4, node = j & 15;
+                const float4 p = b.s[min(k0 + ion, c.s1 - 1)];
+                const double v = axis == 0 ? p.x : axis == 1 ? p.y : p.z, lo = axis == 2 ? -m.Hh : -m.R;
+                const int cell = mesh_cell(v, lo, m.inv_h, axis == 2 ? m.nc[2] : m.nc[0]);
+                const int n = node - (cell - (axis == 0 ? c.x : axis == 1 ? c.y : c.z));
+                double dummy;
+                const double w = mesh_window<false>(m, (v - lo) * m.inv_h - cell, n, dummy);
+                wt[wv][ion][axis][node] = n >= 0 && n < kMeshP && k0 + ion < c.s1 ? w : 0.0;
             }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const double (*w)[16] = wt[wv][4 * s + q];
+                const double wx = w[0][c16], wz = w[2][c16];
+#pragma unroll
+                for (int t = 0; t < kMeshReach; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(wx * w[1][t], wz, acc[t], 0, 0, 0);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
+        unsigned long long* to = grid + (k / kMeshG * kMeshKx) * kMeshLx + k % kMeshG * kMeshKx + c16 * kMeshLx * kMeshLx;
+#pragma unroll
+        for (int t = 0; t < kMeshReach; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                if (4 * r + q < kMeshReach)
+                    __hip_atomic_fetch_add(&to[t * kMeshLx + 4 * r + q],
+                                           (unsigned long long)__double2ll_rn(acc[t][r] * kMeshScale),
+                                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
-    unsigned long long* o = b.brick + (long long)blockIdx.x * total;
-    for (int k = threadIdx.x; k < total; k += 256) o[k] = grid[k];
+    unsigned long long* o = b.brick + (long long)blockIdx.x * kMeshNodes;
+    for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) o[k] = grid[k];
 }
 
-// Grid charges: a node lies in at most two bricks along each axis.
+// Grid charges: a node lies in at most two bricks along x and y and three
+// along z.
 __global__ __launch_bounds__(256) void mesh_sum_kernel(MeshArgs m, MeshBufs b)
 {
     const long long v = (long long)blockIdx.x * 256 + threadIdx.x;
     const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
     if (v >= (long long)nx * ny * nz) return;
     const int x = (int)(v % nx), y = (int)(v / nx % ny), z = (int)(v / ((long long)nx * ny));
-    const int lx = m.bc + kMeshP - 1, lz = m.bz + kMeshP - 1;
-    const long long total = (long long)lx * lx * lz;
+    constexpr int bc = kMeshG * kMeshKx;
     long long s = 0;
-    for (int bz = z / m.bz, i = 0; i < 2; ++i, --bz) {
-        if (bz < 0 || bz >= m.nbz || z - bz * m.bz >= lz) continue;
-        for (int by = y / m.bc, j = 0; j < 2; ++j, --by) {
-            if (by < 0 || by >= m.nby || y - by * m.bc >= lx) continue;
-            for (int bx = x / m.bc, k = 0; k < 2; ++k, --bx) {
-                if (bx < 0 || bx >= m.nbx || x - bx * m.bc >= lx) continue;
-                s += (long long)b.brick[((long long)(bz * m.nby + by) * m.nbx + bx) * total +
-                                        ((z - bz * m.bz) * lx + (y - by * m.bc)) * lx + (x - bx * m.bc)];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int bz = z / kMeshBz - i, oz = z - bz * kMeshBz;
+        if (bz < 0 || bz >= m.nbz || oz >= kMeshLz) continue;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int by = y / bc - j, oy = y - by * bc;
+            if (by < 0 || by >= m.nby || oy >= kMeshLx) continue;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int bx = x / bc - k, ox = x - bx * bc;
+                if (bx < 0 || bx >= m.nbx || ox >= kMeshLx) continue;
+                s += (long long)b.brick[((long long)(bz * m.nby + by) * m.nbx + bx) * kMeshNodes +
+                                        (oz * kMeshLx + oy) * kMeshLx + ox];
             }
         }
     }
@@ -373,13 +380,18 @@ __global__ __launch_bounds__(256) void mesh_green_kernel(MeshArgs m, double i0_b
         green[(long long)blockIdx.x * m.ng + n] = ((part[0][n & 63] + part[1][n & 63]) + part[2][n & 63]) + part[3][n & 63];
 }
 
-// One axis of the Gaussian convolutions as a matrix product with the Toeplitz
-// matrix g[|i - k|], 64-bit MFMA.  A wave computes 64 nodes of 16 grid lines;
-// the four 16 x 16 tiles share each loaded line value.  AXIS 0 and 1 apply
-// Gaussian m0 + blockIdx.z; AXIS 2 sums over Gaussians m0 .. m0 + mc - 1 with
-// their weights (add: on top of what out holds).  v_mfma_f64_16x16x4_f64
-// operands, lane l: A[l % 16][l / 16], B[l / 16][l % 16], D[4 r + l / 16][l % 16].
-template <int AXIS>
+// One axis of the Gaussian convolutions: a product with the symmetric Toeplitz
+// matrix g[|i - k|], 64-bit MFMA.  The matrix is symmetric about its centre
+// too, so the sums and differences of a line's mirrored values,
+// e_k = v_k + v_(n-1-k) and o_k = v_k - v_(n-1-k), are carried by matrices of
+// half the size, g[|i - k|] +- g[n - 1 - i - k], and give the mirrored results
+// as (E +- O) / 2: half the products.  A wave computes NT x 16 such rows of 16
+// grid lines.  AXIS 0 and 1 apply Gaussian m0 + blockIdx.z; AXIS 2 sums over
+// Gaussians m0 .. m0 + mc - 1 with their weights (add: on top of what out
+// holds).  Bound by the matrix rate: 144 us for the three axes at 2^17 ions, where whole lines took 233.
+// v_mfma_f64_16x16x4_f64 operands, lane l: A[l % 16][l / 16],
+// B[l / 16][l % 16], D[4 r + l / 16][l % 16].
+template <int AXIS, int NT>
 __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double* __restrict__ in,
                                                         double* __restrict__ out,
                                                         const double* __restrict__ green, int m0, int mc, int add)
@@ -387,7 +399,7 @@ __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double
     typedef double d4 __attribute__((ext_vector_type(4)));
     extern __shared__ double tab[];
     const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
-    const int len = AXIS == 0 ? nx : AXIS == 1 ? ny : nz;
+    const int len = AXIS == 0 ? nx : AXIS == 1 ? ny : nz, half = (len + 1) / 2;
     const int lines = AXIS == 0 ? ny * nz : AXIS == 1 ? nx * nz : nx * ny;
     const long long vol = (long long)nx * ny * nz;
     const long long sk = AXIS == 0 ? 1 : AXIS == 1 ? nx : (long long)nx * ny;
@@ -396,31 +408,35 @@ __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double
     const int ln = min(line, lines - 1);
     const long long base = AXIS == 0 ? (long long)ln * nx
                          : AXIS == 1 ? (long long)(ln / nx) * nx * ny + ln % nx : ln;
-    const int i0 = blockIdx.y * 64, kq = lane >> 4;
-    d4 acc[4];
+    const int i0 = blockIdx.y * (16 * NT), kq = lane >> 4;
+    d4 even[NT], odd[NT];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[t] = d4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; t < NT; ++t) even[t] = odd[t] = d4{0.0, 0.0, 0.0, 0.0};
     const int first = AXIS == 2 ? 0 : blockIdx.z, count = AXIS == 2 ? mc : 1;
     for (int g = first; g < first + count; ++g) {
         const double w = AXIS == 2 ? m.w[m0 + g] : 1.0;
         __syncthreads();
-        for (int k = threadIdx.x; k < m.ng; k += 256) tab[k] = w * green[(long long)(m0 + g) * m.ng + k];
+        for (int k = threadIdx.x; k < m.ng; k += 256) tab[k] = 0.5 * w * green[(long long)(m0 + g) * m.ng + k];
         __syncthreads();
         const double* src = in + (AXIS == 0 ? 0 : g * vol) + base;
-        for (int k0 = 0; k0 < len; k0 += 16) {
-            double v[4];
+        for (int k0 = 0; k0 < half; k0 += 16) {
+            double e[4], o[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const int k = k0 + 4 * u + kq;
-                v[u] = k < len ? src[k * sk] : 0.0;
+                const int k = k0 + 4 * u + kq, mk = len - 1 - k;
+                const double v = k < half ? src[k * sk] : 0.0, x = k < mk ? src[mk * sk] : 0.0;
+                e[u] = v + x;                   // the centre of an odd line counts once
+                o[u] = v - x;
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const int k = k0 + 4 * u + kq;
 #pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const double a = tab[abs(i0 + 16 * t + (lane & 15) - k)];
-                    acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v[u], acc[t], 0, 0, 0);
+                for (int t = 0; t < NT; ++t) {
+                    const int i = i0 + 16 * t + (lane & 15);
+                    const double a = tab[abs(i - k)], c = tab[abs(len - 1 - i - k)];
+                    even[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a + c, e[u], even[t], 0, 0, 0);
+                    odd[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(a - c, o[u], odd[t], 0, 0, 0);
                 }
             }
         }
@@ -428,35 +444,68 @@ __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double
     if (line >= lines) return;
     double* dst = out + (AXIS == 2 ? 0 : first * vol) + base;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int i = i0 + 16 * t + 4 * r + kq;
-            if (i < len) dst[i * sk] = acc[t][r] + (AXIS == 2 && add ? dst[i * sk] : 0.0);
+            const int i = i0 + 16 * t + 4 * r + kq, mi = len - 1 - i;
+            if (i >= half) continue;
+            const double p = even[t][r] + odd[t][r], q = even[t][r] - odd[t][r];
+            dst[i * sk] = p + (AXIS == 2 && add ? dst[i * sk] : 0.0);
+            if (mi != i) dst[mi * sk] = q + (AXIS == 2 && add ? dst[mi * sk] : 0.0);
         }
+}
+
+// Launches one axis for Gaussians m0 .. m0 + mc - 1.
+template <int AXIS>
+inline void mesh_conv(const MeshArgs& m, const MeshBufs& b, const double* in, double* out, int m0, int mc, hipStream_t st)
+{
+    const int len = m.n[AXIS], tiles = ((len + 1) / 2 + 15) / 16;
+    const long long lines = (long long)m.n[0] * m.n[1] * m.n[2] / len;
+    const unsigned gx = (unsigned)((lines + 63) / 64), gz = AXIS == 2 ? 1 : mc;
+    const size_t lds = (size_t)m.ng * 8;
+    // several row tiles to a wave share the loaded lines; one where that would leave SIMDs idle
+    const int nt = (long long)gx * 4 * gz * ((tiles + 2) / 3) < 4096 ? 1 : tiles % 3 == 0 || tiles > 4 ? 3 : 2;
+    const dim3 grid(gx, (tiles + nt - 1) / nt, gz);
+    if (nt == 1)
+        mesh_conv_kernel<AXIS, 1><<<grid, 256, lds, st>>>(m, in, out, b.green, m0, mc, m0 > 0);
+    else if (nt == 2)
+        mesh_conv_kernel<AXIS, 2><<<grid, 256, lds, st>>>(m, in, out, b.green, m0, mc, m0 > 0);
+    else
+        mesh_conv_kernel<AXIS, 3><<<grid, 256, lds, st>>>(m, in, out, b.green, m0, mc, m0 > 0);
 }
 
 // Far part of every ion's raw pair sum, minus the gradient of the gridded
 // potential: a thread per ion, the brick's nodes in LDS.  The window's
 // derivative is taken of the normalised interpolant (sum w phi / sum w), which
 // makes a constant potential exactly force free: the mean potential is 1e4
-// times what matters here.
-__global__ __launch_bounds__(256) void mesh_gather_kernel(MeshArgs m, MeshBufs b)
+// times what matters here.  Bound by the LDS reads, one per node and ion (87 us
+// at 2^17 ions, 465 at 2^20).  The z weights as 64-bit MFMA products over a
+// column's ions, as in the spread, took 155 and 660 us: half of each tile is
+// nodes outside an ion's ten.
+__global__ __launch_bounds__(kMeshThreads) void mesh_gather_kernel(MeshArgs m, MeshBufs b)
 {
     extern __shared__ double node[];
-    __shared__ BrickRuns runs;
-    const int lx = m.bc + kMeshP - 1, lz = m.bz + kMeshP - 1, total = lx * lx * lz;
-    const int bx = blockIdx.x % m.nbx, by = blockIdx.x / m.nbx % m.nby, bz = blockIdx.x / (m.nbx * m.nby);
-    mesh_brick_runs(m, b, bx, by, bz, runs);
-    const int g2 = m.g * m.g, cnt = runs.pre[64];
-    if (cnt == 0) return;
-    for (int k = threadIdx.x; k < total; k += 256) {
-        const int x = bx * m.bc + k % lx, y = by * m.bc + k / lx % lx, z = bz * m.bz + k / (lx * lx);
+    __shared__ int start[kMeshG * kMeshG], pre[kMeshG * kMeshG + 1];
+    const int x0 = blockIdx.x % m.nbx * kMeshG * kMeshKx, y0 = blockIdx.x / m.nbx % m.nby * kMeshG * kMeshKx,
+              z0 = blockIdx.x / (m.nbx * m.nby) * kMeshBz;
+    if (threadIdx.x < kMeshG * kMeshG) {
+        const MeshColumn c = mesh_column(m, b, threadIdx.x);
+        start[threadIdx.x] = c.s0;
+        pre[threadIdx.x + 1] = c.s1 - c.s0;
+    }
+    if (threadIdx.x == 0) pre[0] = 0;
+    __syncthreads();
+    if (threadIdx.x == 0)
+        for (int c = 0; c < kMeshG * kMeshG; ++c) pre[c + 1] += pre[c];
+    for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) {
+        const int x = x0 + k % kMeshLx, y = y0 + k / kMeshLx % kMeshLx, z = z0 + k / (kMeshLx * kMeshLx);
         node[k] = x < m.n[0] && y < m.n[1] && z < m.n[2] ? b.phi[((long long)z * m.n[1] + y) * m.n[0] + x] : 0.0;
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < cnt; k += 256) {
-        const int t = mesh_brick_slot(runs, g2, k);
+    for (int k = threadIdx.x; k < pre[kMeshG * kMeshG]; k += kMeshThreads) {
+        int c = 0;
+        while (pre[c + 1] <= k) ++c;
+        const int t = start[c] + (k - pre[c]);
         const float4 p = b.s[t];
         const double px = p.x, py = p.y, pz = p.z;
         const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]), cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]),
@@ -478,13 +527,13 @@ __global__ __launch_bounds__(256) void mesh_gather_kernel(MeshArgs m, MeshBufs b
             dx[j] = fma(-qx, wx[j], dx[j]);
             dy[j] = fma(-qy, wy[j], dy[j]);
         }
-        const int base = ((cz - bz * m.bz) * lx + (cy - by * m.bc)) * lx + (cx - bx * m.bc);
+        const int base = ((cz - z0) * kMeshLx + (cy - y0)) * kMeshLx + (cx - x0);
         double fx = 0.0, fy = 0.0, fz = 0.0, pw = 0.0, sz = 0.0, tz = 0.0;
 #pragma unroll 1
         for (int jz = 0; jz < kMeshP; ++jz) {
             double dz;
             const double wz = mesh_window<true>(m, uz, jz, dz);
-            int at = base + jz * lx * lx;
+            int at = base + jz * (kMeshLx * kMeshLx);
             double a0 = 0.0, a1 = 0.0, a2 = 0.0;
 #pragma unroll
             for (int jy = 0; jy < kMeshP; ++jy) {
@@ -498,7 +547,7 @@ __global__ __launch_bounds__(256) void mesh_gather_kernel(MeshArgs m, MeshBufs b
                 a0 = fma(r0, wy[jy], a0);
                 a1 = fma(r1, dy[jy], a1);
                 a2 = fma(r1, wy[jy], a2);
-                at += lx;
+                at += kMeshLx;
             }
             fx = fma(a0, wz, fx);
             fy = fma(a1, wz, fy);
@@ -798,7 +847,7 @@ inline size_t mesh_layout(const MeshArgs& m, char* base, MeshBufs& b)
     b.mc = (int)std::min<size_t>(kMeshM, std::max<size_t>(1, ((size_t)kMeshScratchMb << 20) / (16 * v)));
     const int passes = (kMeshM + b.mc - 1) / b.mc;
     b.mc = (kMeshM + passes - 1) / passes;
-    const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * mesh_brick_nodes(m) * 8;
+    const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * kMeshNodes * 8;
     take(&b.t1, std::max(conv, brick));
     b.t2 = b.t1 ? b.t1 + (size_t)b.mc * v : nullptr;
     b.brick = (unsigned long long*)b.t1;
@@ -808,7 +857,7 @@ inline size_t mesh_layout(const MeshArgs& m, char* base, MeshBufs& b)
 // Clears the bin counts and computes the Green's tables (once per system).
 inline hipError_t mesh_start(const MeshArgs& m, const MeshBufs& b, hipStream_t st)
 {
-    const int lds = mesh_brick_nodes(m) * 8;
+    constexpr int lds = kMeshNodes * 8;
     hipError_t e = hipFuncSetAttribute((const void*)mesh_spread_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void*)mesh_gather_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -825,8 +874,7 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
                               unsigned long long* fix, long long fstride, double scale, int* status, hipStream_t st)
 {
     const int gi = (m.N + 255) / 256, gc = (m.cap + 255) / 256, ncol = m.ncx * m.ncy;
-    const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
-    const long long v = (long long)nx * ny * nz;
+    const long long v = (long long)m.n[0] * m.n[1] * m.n[2];
     mesh_bin_kernel<<<gc, 256, 0, st>>>(x, plane, m, b);
     mesh_scan_kernel<<<ncol, 256, 0, st>>>(m, b);
     mesh_cols_kernel<<<1, 1024, 0, st>>>(m, b);
@@ -834,18 +882,16 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
     mesh_order_kernel<<<gc, 256, 0, st>>>(x, plane, m, b);
     mesh_box_kernel<<<gc, 256, 0, st>>>(m, b);
     const int bricks = m.nbx * m.nby * m.nbz;
-    const size_t lds = (size_t)mesh_brick_nodes(m) * 8, tab = (size_t)m.ng * 8;
-    mesh_spread_kernel<<<bricks, 256, lds, st>>>(m, b);
+    constexpr size_t lds = kMeshNodes * 8;
+    mesh_spread_kernel<<<bricks, kMeshThreads, lds, st>>>(m, b);
     mesh_sum_kernel<<<(unsigned)((v + 255) / 256), 256, 0, st>>>(m, b);
-    auto lines = [](long long n) { return (unsigned)((n + 63) / 64); };
     for (int m0 = 0; m0 < kMeshM; m0 += b.mc) {
         const int mc = std::min(b.mc, kMeshM - m0);
-        // mesh_conv_kernel<2> reads t2 and, except on the first pass, adds to the potential
-        mesh_conv_kernel<0><<<dim3(lines((long long)ny * nz), lines(nx), mc), 256, tab, st>>>(m, b.q, b.t1, b.green, m0, mc, 0);
-        mesh_conv_kernel<1><<<dim3(lines((long long)nx * nz), lines(ny), mc), 256, tab, st>>>(m, b.t1, b.t2, b.green, m0, mc, 0);
-        mesh_conv_kernel<2><<<dim3(lines((long long)nx * ny), lines(nz), 1), 256, tab, st>>>(m, b.t2, b.phi, b.green, m0, mc, m0 > 0);
+        mesh_conv<0>(m, b, b.q, b.t1, m0, mc, st);
+        mesh_conv<1>(m, b, b.t1, b.t2, m0, mc, st);
+        mesh_conv<2>(m, b, b.t2, b.phi, m0, mc, st);
     }
-    mesh_gather_kernel<<<bricks, 256, lds, st>>>(m, b);
+    mesh_gather_kernel<<<bricks, kMeshThreads, lds, st>>>(m, b);
     const int tiles = (m.cap / 64 + 7) / 8 * 8;
     if (m.cap / 64 >= 8192)
         mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, fix, fstride,

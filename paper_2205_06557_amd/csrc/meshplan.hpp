@@ -30,16 +30,21 @@ constexpr double kMeshBeta = 22.0;  // Kaiser-Bessel shape
 constexpr double kMeshRatio = 7.5;  // r_c / h
 constexpr double kMeshTop = 2.8;    // t_max r_c
 constexpr int kMeshSub = 8;         // ions per box of the near search
-constexpr double kMeshCol = 27.0;   // ions per column over a height of its width
+constexpr double kMeshCol = 27.0;   // ions in the unit of volume that r_c is given in
 constexpr int kMeshTile = 16;       // ions per group of targets
+constexpr int kMeshKx = 4;          // column width in cells
+constexpr int kMeshZsub = 2;        // sort bins per cell along z
+constexpr int kMeshG = 4;           // a brick is kMeshG x kMeshG columns ...
+constexpr int kMeshBz = 7;          // ... and kMeshBz cells along z
+// nodes that the ions of a brick reach, per axis and in all
+constexpr int kMeshLx = kMeshG * kMeshKx + kMeshP - 1, kMeshLz = kMeshBz + kMeshP - 1;
+constexpr int kMeshNodes = kMeshLx * kMeshLx * kMeshLz;
 
 // Constants of one system's split, passed to the kernels by value.
 struct MeshArgs {
     int N, cap;                     // ions; sorted slots (columns padded to whole groups)
     int nc[3], n[3];                // grid cells and nodes (nc + 9) per axis
-    int kx, ncx, ncy;               // column width in cells; columns along x and y
-    int zsub, nzb;                  // sort bins per cell along z; bins per column
-    int g, bc, bz;                  // brick: g x g columns = bc x bc cells, bz cells along z
+    int ncx, ncy, nzb;              // columns along x and y; sort bins per column
     int nbx, nby, nbz;              // bricks per axis
     int ng;                         // entries of one Green's table (zero padded)
     double R, Hh, h, inv_h;         // domain radius and half height; grid spacing
@@ -48,13 +53,6 @@ struct MeshArgs {
     double win[kMeshWDeg + 1];      // window in powers of s = 1 - 2 z^2
     double w[kMeshM], th[kMeshM];   // weights; t_m h
 };
-
-// Grid nodes that the ions of one brick reach.
-inline int mesh_brick_nodes(const MeshArgs& a)
-{
-    const int lx = a.bc + kMeshP - 1;
-    return lx * lx * (a.bz + kMeshP - 1);
-}
 
 // Least squares of an m x n system (column major A, overwritten) by
 // Householder QR; columns scaled by the caller.
@@ -129,11 +127,9 @@ inline double mesh_i0(double x)
 
 // Grid and columns for a near radius; false if the domain is outside what the
 // split is made for.
-inline bool mesh_dims(double N, double R, double H, double rc, MeshArgs& a)
+inline bool mesh_dims(double R, double H, double rc, MeshArgs& a)
 {
-    const double pi = 3.14159265358979323846;
-    const double n = N / (pi * R * R * H);
-    const double h = rc / kMeshRatio, b = std::cbrt(kMeshCol / n);
+    const double h = rc / kMeshRatio;
     a.h = h;
     a.inv_h = 1.0 / h;
     a.R = R;
@@ -144,11 +140,9 @@ inline bool mesh_dims(double N, double R, double H, double rc, MeshArgs& a)
         if (a.nc[c] < 8 || a.nc[c] > 500) return false;
         a.n[c] = a.nc[c] + kMeshP - 1;
     }
-    a.kx = std::min(16, std::max(2, (int)std::lround(b / h)));
-    a.ncx = a.ncy = (a.nc[0] + a.kx - 1) / a.kx;
-    a.zsub = a.kx < 8 ? 2 : 1;
-    a.nzb = a.nc[2] * a.zsub;
-    a.cw = (float)(a.kx * h);
+    a.ncx = a.ncy = (a.nc[0] + kMeshKx - 1) / kMeshKx;
+    a.nzb = a.nc[2] * kMeshZsub;
+    a.cw = (float)(kMeshKx * h);
     a.rc = (float)rc;
     a.rc2 = a.rc * a.rc;
     a.irc2 = -2.0f / a.rc2;
@@ -160,9 +154,9 @@ inline bool mesh_dims(double N, double R, double H, double rc, MeshArgs& a)
 //
 // r_c trades near pairs (r_c^3) against the grid (its nodes go as r_c^-3, the
 // convolutions as r_c^-4) and scales with the ion spacing: in units of
-// (27 / n)^(1/3), a pair sum took 0.80 ms at 1.4, 0.76 at 1.6, 0.79 at 1.7,
-// 0.93 at 1.9 and 0.95 at 2.0 for 2^17 ions; 1.68, 1.28, 1.25, 1.41 and 1.43
-// for 2^18; 6.1, 5.6, 4.9, 4.6 and 4.7 for 2^20.
+// (27 / n)^(1/3), a step took 0.61 ms at 1.6, 0.65 at 1.68, 0.65 at 1.75 and
+// 0.66 at 1.82 for 2^17 ions; 1.11, 1.12, 1.14 and 1.10 for 2^18; 4.55, 4.44,
+// 4.28 and 4.39 for 2^20.
 inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
 {
     const double diag = std::sqrt(4.0 * R * R + H * H);
@@ -175,25 +169,17 @@ inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
         if (r < 0.1) continue;
         if (r > 2.5 || r > 0.45 * diag) return false;
         // a larger r_c where the grid would have too many nodes
-        if (mesh_dims((double)N, R, H, r, a) && (double)a.n[0] * a.n[1] * a.n[2] <= 3.0e7) rc = r;
+        if (mesh_dims(R, H, r, a) && (double)a.n[0] * a.n[1] * a.n[2] <= 3.0e7) rc = r;
     }
     if (rc == 0.0) return false;
     a.N = (int)N;
     const long long cap = (N + (kMeshTile - 1ll) * a.ncx * a.ncy + 63) / 64 * 64;
     if (cap > (1ll << 28)) return false;
     a.cap = (int)cap;
-    // bricks of about 10 cells a side (smaller for small systems, so that the
-    // spreading and gathering blocks fill the chip)
-    const int want = N >= (1 << 18) ? 10 : 6;
-    a.g = std::max(1, (want + a.kx / 2) / a.kx);
-    a.bc = a.g * a.kx;
-    while (a.bc < kMeshP - 1) a.bc = ++a.g * a.kx;       // a node lies in at most two bricks per axis
-    a.bz = std::max(kMeshP - 1, want);
-    a.nbx = (a.nc[0] + a.bc - 1) / a.bc;
-    a.nby = (a.nc[1] + a.bc - 1) / a.bc;
-    a.nbz = (a.nc[2] + a.bz - 1) / a.bz;
+    a.nbx = (a.ncx + kMeshG - 1) / kMeshG;
+    a.nby = (a.ncy + kMeshG - 1) / kMeshG;
+    a.nbz = (a.nc[2] + kMeshBz - 1) / kMeshBz;
     a.ng = std::max(a.n[0], a.n[2]) + 80;
-    if (mesh_brick_nodes(a) * 8 > 128 * 1024) return false;      // a brick's nodes are kept in LDS
 
     // Gaussians: force of L fitted to that of e^-r / r on [r_c, diag]
     constexpr int m = 160, M = kMeshM;

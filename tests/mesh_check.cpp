@@ -31,10 +31,10 @@ int main()
             ++plans;
             const double rc = a.rc, diag = std::sqrt(4 * R * R + H * H);
             NEED(a.N == N && a.cap % kMeshTile == 0 && a.cap >= N);
-            NEED(a.nc[0] * a.h >= 2 * R && a.nc[2] * a.h >= H && a.ncx * a.kx >= a.nc[0] && a.ncy * a.kx >= a.nc[1]);
-            NEED(a.nbx * a.bc >= a.nc[0] && a.nby * a.bc >= a.nc[1] && a.nbz * a.bz >= a.nc[2]);
-            NEED(a.bc >= kMeshP - 1 && a.bz >= kMeshP - 1 && a.g * a.kx == a.bc && a.g * a.g <= 64);
-            NEED(mesh_brick_nodes(a) * 8 <= 128 * 1024);
+            NEED(a.nc[0] * a.h >= 2 * R && a.nc[2] * a.h >= H && a.ncx * kMeshKx >= a.nc[0] && a.ncy * kMeshKx >= a.nc[1]);
+            NEED(a.nbx * kMeshG >= a.ncx && a.nby * kMeshG >= a.ncy && a.nbz * kMeshBz >= a.nc[2]);
+            // the nodes that any cell reaches lie in its brick's, and the grid holds them
+            NEED(a.n[0] == a.nc[0] + kMeshP - 1 && a.n[2] == a.nc[2] + kMeshP - 1);
             NEED(a.ng >= a.n[0] + 79 && a.ng >= a.n[2] + 79 && (a.ng + 63) / 64 <= 65535);
             auto fl = [&](double r) {
                 double f = 0;
