@@ -366,9 +366,12 @@ od_status od_batch_set_config(od_batch* b, int32_t persistent, int32_t jsplit, i
 od_status od_batch_get_config(od_batch* b, int32_t* persistent, int32_t* jsplit, int64_t* split_max_n,
                               int32_t* n_items);
 
-/* Pair kernel of the batch: OD_PAIR_SYMMETRIC (the default; OD_PAIR_AUTO
- * selects it too), each unordered pair once with int64 fixed-point totals
- * (see od_set_pair_kernel), or OD_PAIR_ONE_SIDED.  The persistent, jsplit and
+/* Pair kernel of the batch: OD_PAIR_AUTO (the default), each system's sum as
+ * od_set_pair_kernel's default has it alone (large ones as near pairs plus a
+ * far part on a grid, whose memory is taken by the first step); the others,
+ * and every system with OD_PAIR_SYMMETRIC, each unordered pair once with int64
+ * fixed-point totals; or OD_PAIR_ONE_SIDED.  The getter reports
+ * OD_PAIR_SYMMETRIC for both of the former.  The persistent, jsplit and
  * split_max_n settings apply to the one-sided kernel only.  Drops a captured
  * graph. */
 od_status od_batch_set_pair_kernel(od_batch* b, int32_t kind);
@@ -384,8 +387,9 @@ od_status od_batch_get_pair_kernel(od_batch* b, int32_t* kind);
  * at most 2^24).  Scheduling does not change the results (integer totals);
  * one_row and items_target change the FP32 partial sums that each item
  * flushes, so a system then differs from its run alone by rounding.  Drops a
- * captured graph.  The getter reports the target in effect and *n_items, the
- * length of the work list (any pointer may be NULL). */
+ * captured graph.  The settings concern the systems that are summed directly.
+ * The getter reports the target in effect and *n_items, the length of the work
+ * list with every system summed directly (any pointer may be NULL). */
 od_status od_batch_set_sym_config(od_batch* b, int32_t persistent, int32_t one_row, int64_t items_target);
 od_status od_batch_get_sym_config(od_batch* b, int32_t* persistent, int32_t* one_row, int64_t* items_target,
                                   int32_t* n_items);

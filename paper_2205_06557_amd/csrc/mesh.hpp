@@ -26,18 +26,19 @@
 // bit for bit.
 #pragma once
 
-#include <type_traits>
-
 #include "kernels.hpp"
 #include "meshplan.hpp"
 
 namespace odk {
 
-// Device buffers of one system's split (one arena, see mesh_bytes).
+// Device buffers of one system's split: its own (mesh_own) and the scratch of
+// a step (mesh_scratch), which systems that step one after another share.
 struct MeshBufs {
+    int* count;            // own: [bins] ions per bin; zero between steps
+    double* green;         // own: [M][ng] Green's tables
+    float* near0;          // own: constant term of the near polynomial (mesh_zero_kernel)
     int* key;              // [N] sort bin of each ion
     int* arr;              // [N] arrival number in the bin
-    int* count;            // [bins] ions per bin; zero between steps
     int* rel;              // [columns][nzb + 1] bin starts within the column
     int* col;              // [columns + 1] first slot of each column
     int* temp;             // [cap] ions in arrival order, -1 where a column is padded
@@ -45,8 +46,6 @@ struct MeshBufs {
     float4* s;             // [cap] sorted positions
     float* box;            // [6][cap / 8] min x, y, z, max x, y, z of 8 sorted ions
     double* far;           // [3][cap] far part by sorted slot
-    double* green;         // [M][ng] Green's tables
-    float* near0;          // constant term of the near polynomial (mesh_zero_kernel)
     double* q;             // grid charges
     double* phi;           // far potential on the grid
     double* t1;            // convolution scratch, mc grids each
@@ -820,38 +819,51 @@ void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* _
 // 2.06 ms per step at 2^18 ions and 6.61 against 6.56 at 2^20 with 160 MB.
 constexpr int kMeshScratchMb = 400;
 
-// Lays the buffers out in an arena at `base` (null: only the size, in bytes).
-inline size_t mesh_layout(const MeshArgs& m, char* base, MeshBufs& b)
-{
+// Cuts buffers from an arena at `base` (null: only adds up their size).
+struct MeshArena {
+    char* base;
     size_t at = 0;
-    auto take = [&](auto** p, size_t bytes) {
-        *p = (std::remove_reference_t<decltype(**p)>*)(base ? base + at : nullptr);
+    template <typename T>
+    void take(T** p, size_t bytes)
+    {
+        *p = (T*)(base ? base + at : nullptr);
         at += (bytes + 255) / 256 * 256;
-    };
+    }
+};
+
+inline size_t mesh_own(const MeshArgs& m, char* base, MeshBufs& b)
+{
+    MeshArena a{base};
+    a.take(&b.count, (size_t)m.ncx * m.ncy * m.nzb * 4);
+    a.take(&b.green, (size_t)kMeshM * m.ng * 8);
+    a.take(&b.near0, 4);
+    return a.at;
+}
+
+inline size_t mesh_scratch(const MeshArgs& m, char* base, MeshBufs& b)
+{
+    MeshArena a{base};
     const size_t ncol = (size_t)m.ncx * m.ncy, cap = (size_t)m.cap, v = (size_t)m.n[0] * m.n[1] * m.n[2];
-    take(&b.key, (size_t)m.N * 4);
-    take(&b.arr, (size_t)m.N * 4);
-    take(&b.count, ncol * m.nzb * 4);
-    take(&b.rel, ncol * (m.nzb + 1) * 4);
-    take(&b.col, (ncol + 1) * 4);
-    take(&b.temp, cap * 4);
-    take(&b.idx, cap * 4);
-    take(&b.s, cap * 16);
-    take(&b.box, 6 * (cap / kMeshSub) * 4);
-    take(&b.far, 3 * cap * 8);
-    take(&b.green, (size_t)kMeshM * m.ng * 8);
-    take(&b.near0, 4);
-    take(&b.q, v * 8);
-    take(&b.phi, v * 8);
+    a.take(&b.key, (size_t)m.N * 4);
+    a.take(&b.arr, (size_t)m.N * 4);
+    a.take(&b.rel, ncol * (m.nzb + 1) * 4);
+    a.take(&b.col, (ncol + 1) * 4);
+    a.take(&b.temp, cap * 4);
+    a.take(&b.idx, cap * 4);
+    a.take(&b.s, cap * 16);
+    a.take(&b.box, 6 * (cap / kMeshSub) * 4);
+    a.take(&b.far, 3 * cap * 8);
+    a.take(&b.q, v * 8);
+    a.take(&b.phi, v * 8);
     // convolution scratch: as many Gaussians at a time as fit
     b.mc = (int)std::min<size_t>(kMeshM, std::max<size_t>(1, ((size_t)kMeshScratchMb << 20) / (16 * v)));
     const int passes = (kMeshM + b.mc - 1) / b.mc;
     b.mc = (kMeshM + passes - 1) / passes;
     const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * kMeshNodes * 8;
-    take(&b.t1, std::max(conv, brick));
+    a.take(&b.t1, std::max(conv, brick));
     b.t2 = b.t1 ? b.t1 + (size_t)b.mc * v : nullptr;
     b.brick = (unsigned long long*)b.t1;
-    return at;
+    return a.at;
 }
 
 // Clears the bin counts and computes the Green's tables (once per system).

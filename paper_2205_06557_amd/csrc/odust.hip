@@ -186,20 +186,18 @@ void free_cutoff(od_system* s)
     s->cut = false;
 }
 
-// Systems up to this size sum their pairs directly.  Direct against split, ms
-// per step of one grain at R = 3, H = 6: 1.16 / 0.69 at 2^16, 4.1 / 1.15 at
-// 2^17, 16.0 / 2.1 at 2^18; 257 / 6.6 at 2^20 (two grains, H = 8).
+// Systems below this size sum their pairs directly.  Direct against split, us
+// per step of one grain at R = 3, H = 6: 322 / 345 at 2^15, 480 / 356 at
+// 40,960, 695 / 403 at 49,152, 1,119 / 431 at 2^16, 4,105 / 652 at 2^17; of a
+// cylinder with R = 0.6, H = 20, the grid's worst shape: 479 / 484 at 40,960,
+// 1,117 / 606 at 2^16.
 constexpr int64_t kMeshMinN = 81920;
 
-// Whether the system's pair sum can be split into near pairs and a far part
-// on a grid (mesh.hpp); plans it the first time.
-bool plan_mesh(od_system* s)
+// Whether a system's pair sum is split into near pairs and a far part on a
+// grid (mesh.hpp); plans it.
+bool plan_mesh(int prec, const odk::PairArgs& pa, const odk::PushArgs& pu, odk::MeshArgs& m)
 {
-    if (s->mesh_planned == 0)
-        s->mesh_planned = s->prec == OD_PREC_FP32 && s->N >= kMeshMinN && s->pa.ion_ion &&
-                                  odk::mesh_plan(s->N, s->pu.R, s->pu.H, s->ma)
-                              ? 1 : -1;
-    return s->mesh_planned > 0;
+    return prec == OD_PREC_FP32 && pa.N >= kMeshMinN && pa.ion_ion && odk::mesh_plan(pa.N, pu.R, pu.H, m);
 }
 
 void free_mesh(od_system* s)
@@ -236,13 +234,15 @@ od_status setup_items(od_system* s, hipStream_t st)
 // Sets up the split, or, where its memory is refused, the direct sum.
 od_status setup_mesh(od_system* s, hipStream_t st)
 {
-    s->mesh_mem = dev_alloc(s, odk::mesh_layout(s->ma, nullptr, s->mb));
+    const size_t own = odk::mesh_own(s->ma, nullptr, s->mb);
+    s->mesh_mem = dev_alloc(s, own + odk::mesh_scratch(s->ma, nullptr, s->mb));
     if (!s->mesh_mem) {
         (void)hipGetLastError();
         s->mesh_planned = -1;
         return setup_items(s, st);
     }
-    odk::mesh_layout(s->ma, (char*)s->mesh_mem, s->mb);
+    odk::mesh_own(s->ma, (char*)s->mesh_mem, s->mb);
+    odk::mesh_scratch(s->ma, (char*)s->mesh_mem + own, s->mb);
     HIPCHK(odk::mesh_start(s->ma, s->mb, st));
     s->mesh = true;
     return OD_OK;
@@ -250,30 +250,37 @@ od_status setup_mesh(od_system* s, hipStream_t st)
 
 bool use_mesh(const od_system* s) { return s->sym && s->pair_kind == OD_PAIR_AUTO && s->mesh_planned > 0; }
 
-// The split's memory (up to a few hundred MB) is taken by the first step that
-// needs it, not when the system is created: hipMalloc and hipFree of more than
-// 64 MB take 0.3 ms, and milliseconds in a row, which a program that only
-// draws initial states would pay for nothing.  A system with an allocator of
-// its caller's takes it at creation, where the allocator may be called.  When
-// the caller is capturing the stream the set-up runs on a stream of its own.
-od_status first_step_setup(od_system* s)
+// Runs a set-up on `stream`, or, when its caller is capturing that, on a
+// stream of its own.
+template <typename F>
+od_status outside_capture(hipStream_t stream, F setup)
 {
-    if (s->cut || !use_mesh(s) || s->mesh) return OD_OK;
     hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
-    if (s->stream) HIPCHK(hipStreamIsCapturing(s->stream, &cs));
+    if (stream) HIPCHK(hipStreamIsCapturing(stream, &cs));
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
     HIPCHK(hipThreadExchangeStreamCaptureMode(&mode));
-    hipStream_t st = s->stream;
+    hipStream_t st = stream;
     od_status r = OD_OK;
     if (cs != hipStreamCaptureStatusNone && hipStreamCreateWithFlags(&st, hipStreamNonBlocking) != hipSuccess)
         r = fail(OD_EDEVICE, "hipStreamCreateWithFlags failed");
-    if (r == OD_OK) r = setup_mesh(s, st);
-    if (st != s->stream) {
+    if (r == OD_OK) r = setup(st);
+    if (st != stream) {
         if (hipStreamSynchronize(st) != hipSuccess && r == OD_OK) r = fail(OD_EDEVICE, "setting up the pair sum failed");
         (void)hipStreamDestroy(st);
     }
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     return r;
+}
+
+// The split's memory (up to a few hundred MB) is taken by the first step that
+// needs it, not when the system is created: hipMalloc and hipFree of more than
+// 64 MB take 0.3 ms, and milliseconds in a row, which a program that only
+// draws initial states would pay for nothing.  A system with an allocator of
+// its caller's takes it at creation, where the allocator may be called.
+od_status first_step_setup(od_system* s)
+{
+    if (s->cut || !use_mesh(s) || s->mesh) return OD_OK;
+    return outside_capture(s->stream, [s](hipStream_t st) { return setup_mesh(s, st); });
 }
 
 size_t fix_bytes(const od_system* s) { return 3 * (size_t)s->Npad * sizeof(unsigned long long); }
@@ -865,7 +872,8 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         od_destroy(s);
         return fail(OD_EDEVICE, "init kernel launch failed: %s", hipGetErrorString(e));
     }
-    (void)plan_mesh(s);                 // while the device draws the initial state
+    // while the device draws the initial state
+    s->mesh_planned = plan_mesh(s->prec, s->pa, s->pu, s->ma) ? 1 : -1;
     st = read_status(s);
     if (st == OD_OK && (sim->flags & OD_FLAG_CONFINEMENT)) {
         // the grid's sums use the acceleration planes, which no step has

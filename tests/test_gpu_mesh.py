@@ -126,3 +126,43 @@ def test_split_reports_coincident_ions(B):
         s.step(1)
         with pytest.raises(B.OdError):
             s.sync()
+
+
+def _members():
+    c = W.chain8()
+    base = [W.single_grain_small(), W.two_grain_wake(), c, c.with_(mach=0.6)]
+    sizes = [3001, 82000, 90001, 86003]
+    return [w.with_(n_ions=n, system_id=k) for k, (w, n) in enumerate(zip(base, sizes))]
+
+
+@pytest.mark.parametrize("graph", [0, 2])
+def test_split_batch_members_equal_single_runs(B, graph):
+    """Members of a batch are split as they are when run alone, on whatever
+    stream and scratch they fall; one state has ions outside the domain."""
+    ws = _members()
+    with B.Batch(ws) as b:
+        if graph:
+            b.set_graph(graph)
+        b.step(3)
+        x, v, q, n = b.get_state(2)
+        out = x.copy()
+        out[:, :3] = 30.0 + np.arange(3)
+        b.set_state(2, out, v, q, n)
+        b.step(4)
+        b.sync()
+        for k, w in enumerate(ws):
+            with B.System(w) as s:
+                s.step(3)
+                if k == 2:
+                    for p, r in zip(s.get_state()[:3], (x, v, q)):
+                        assert np.array_equal(p, r)
+                    s.set_state(out, v, q, n)
+                s.step(4)
+                for p, r in zip(b.get_state(k)[:3], s.get_state()[:3]):
+                    assert np.array_equal(p, r), (k, w.n_ions)
+                assert np.array_equal(b.accelerations(k), s.accelerations())
+        b.set_pair_kernel(B.PAIR_SYMMETRIC)
+        b.step(1)
+        b.set_pair_kernel(B.PAIR_AUTO)
+        b.step(1)
+        b.sync()
