@@ -243,7 +243,7 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * one-sided kernel.  A pair closer than about 4e-6 of the mean ion spacing
  * overflows the range and is reported as OD_ENUMERIC.
  * OD_PAIR_AUTO (the default) takes the symmetric sum, the faster one at every
- * size, and for large systems (from 81,920 ions on, domains up to 24 r_De
+ * size, and for large systems (from 40,960 ions on, domains up to 24 r_De
  * across) evaluates it as near pairs, one by one, plus a smooth far part on a
  * grid in 64 bits.  That is the same all-pairs sum: the far part is within
  * 1e-7 of the rms acceleration of the direct sum in 64 bits, below the FP32

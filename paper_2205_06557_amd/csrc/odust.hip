@@ -191,7 +191,7 @@ void free_cutoff(od_system* s)
 // 40,960, 695 / 403 at 49,152, 1,119 / 431 at 2^16, 4,105 / 652 at 2^17; of a
 // cylinder with R = 0.6, H = 20, the grid's worst shape: 479 / 484 at 40,960,
 // 1,117 / 606 at 2^16.
-constexpr int64_t kMeshMinN = 81920;
+constexpr int64_t kMeshMinN = 40960;
 
 // Whether a system's pair sum is split into near pairs and a far part on a
 // grid (mesh.hpp); plans it.

@@ -37,7 +37,8 @@ def _against_oracle(s, w, nt=1500):
 
 
 @pytest.mark.parametrize("n_ions,R,H,grains", [
-    (81920, 3, 6, 1),              # the smallest split system
+    (40960, 3, 6, 1),              # the smallest split system
+    (81920, 3, 6, 1),
     ((1 << 17) + 1, 3, 6, 1),
     (100003, 1.5, 14, 1),          # long and thin
     (100003, 8, 2.5, 1),           # flat
@@ -131,7 +132,7 @@ def test_split_reports_coincident_ions(B):
 def _members():
     c = W.chain8()
     base = [W.single_grain_small(), W.two_grain_wake(), c, c.with_(mach=0.6)]
-    sizes = [3001, 82000, 90001, 86003]
+    sizes = [3001, 41000, 65537, 50003]
     return [w.with_(n_ions=n, system_id=k) for k, (w, n) in enumerate(zip(base, sizes))]
 
 
