@@ -33,8 +33,8 @@ struct alignas(128) BatchCtl {
     unsigned int lost_seg[kSlots * kPad32];   // lost-list segment lengths (all systems), [s * kPad32]
     unsigned int queue;                 // next pair work item
     unsigned int lost_ticket;           // reinjection blocks that have finished
-    int status;
-    int pad2_[29];
+    int err_sys, err_status;            // batch_status_kernel
+    int pad2_[28];
 };
 
 __device__ __forceinline__ int uniform_int(int v) { return __builtin_amdgcn_readfirstlane(v); }
@@ -176,6 +176,23 @@ __global__ __launch_bounds__(64) void reinject_batch_kernel(float* __restrict__ 
                                                             int2* __restrict__ lost, long long cap)
 {
     reinject_list<float>(LostList{bc->lost_seg, &bc->lost_ticket, lost, cap}, BatchSystems{xs, vs, plane, sys, ctls});
+}
+
+// First system with a status to report, and that status (one block).  The
+// calls that read results check it; fetched word by word, 24 systems' words
+// took 0.35 ms per call.
+__global__ __launch_bounds__(256) void batch_status_kernel(const Ctl* __restrict__ ctls, int ns, BatchCtl* bc)
+{
+    __shared__ int first;
+    if (threadIdx.x == 0) first = ns;
+    __syncthreads();
+    for (int s = threadIdx.x; s < ns; s += 256)
+        if (ctls[s].status) atomicMin(&first, s);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        bc->err_sys = first;
+        bc->err_status = first < ns ? ctls[first].status : 0;
+    }
 }
 
 __global__ __launch_bounds__(256) void init_batch_kernel(float* __restrict__ xs,
