@@ -254,7 +254,10 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * after od_set_state puts ions outside the domain, the direct sum is used.
  * OD_PAIR_SYMMETRIC always sums every pair directly.
  * The symmetric kernel needs 24 bytes per ion of accumulators.  FP64 systems
- * always use the one-sided kernel; a cutoff (od_set_cutoff) takes precedence
+ * have a sum of their own, which neither choice changes (each pair once too,
+ * in 64 bits with totals of two words, 48 bytes per ion; one-sided for a step
+ * whose closest pair they cannot hold): OD_PAIR_SYMMETRIC is refused for them
+ * and OD_PAIR_ONE_SIDED reported.  A cutoff (od_set_cutoff) takes precedence
  * over either.  In test-particle mode (OD_FLAG_NO_ION_ION) the symmetric
  * setting runs no pair kernel at all: the step's tail adds the grain, drive
  * and confinement terms (the one-sided setting adds them in a pair kernel

@@ -55,7 +55,8 @@ struct alignas(128) Ctl {
     int status;
     unsigned int ticket;                   // slots of the tail whose blocks have all finished
     unsigned int lost_ticket;              // reinjection blocks that have finished
-    int pad[5];
+    int pad[3];
+    long long pair_bad;                    // FP64: step + 1 of a pair sum that its words cannot hold
 };
 static_assert(offsetof(Ctl, n_exit) % 128 == 0 && offsetof(Ctl, n_coll) % 128 == 0 &&
                   offsetof(Ctl, ticket_slot) % 128 == 0 && offsetof(Ctl, lost_seg) % 128 == 0,

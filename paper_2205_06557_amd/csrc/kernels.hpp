@@ -260,98 +260,6 @@ void pair_forces_f32(const float* __restrict__ xs,
                               o + Npad, o + 2 * Npad, k == 0, tile, red);
 }
 
-// Forces, FP64 throughout (precision mode OD_PREC_FP64).
-// FP64 pair terms of one target against a staged tile of TJ sources;
-// Self: the tile holds the target itself (source index `self`), whose term
-// is dropped.
-template <int TJ, bool Self>
-__device__ __forceinline__ void f64_tile(const double4* __restrict__ tile, double xi, double yi, double zi,
-                                         int self, double& sx, double& sy, double& sz)
-{
-    for (int k = 0; k < TJ; ++k) {
-        const double4 q = tile[k];
-        const double dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
-        const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-        const double ri = rsq_f64(r2);
-        const double r = r2 * ri;
-        const double e = exp_neg_f64(r);
-        double f = fma(r, e, e) * (ri * ri * ri);         // (1 + r) e^-r / r^3
-        if (Self) f = (k == self) ? 0.0 : f;
-        sx += f * dx;
-        sy += f * dy;
-        sz += f * dz;
-    }
-}
-
-template <int BLOCK, int TJ>
-__global__ __launch_bounds__(BLOCK) void pair_forces_f64(const double* __restrict__ xs,
-                                                         double* __restrict__ acc,
-                                                         PairArgs p, DustSet ds,
-                                                         Ctl* __restrict__ ctl)
-{
-    static_assert(BLOCK == TJ, "the block's own tile is the one source tile holding its targets");
-    __shared__ double4 tile[TJ];
-    __shared__ double red[BLOCK / 64][kMaxDust][3];
-    const int Npad = p.Npad;
-    const double* X = xs;
-    const double* Y = xs + Npad;
-    const double* Z = xs + 2 * Npad;
-    const int i0 = blockIdx.x * BLOCK;
-    const int i = i0 + threadIdx.x;
-    const double xi = X[i], yi = Y[i], zi = Z[i];
-    double sx = 0.0, sy = 0.0, sz = 0.0;
-    if (p.ion_ion) {
-        for (int j0 = 0; j0 < Npad; j0 += TJ) {
-            __syncthreads();
-            for (int t = threadIdx.x; t < TJ; t += BLOCK) {
-                double4 q;
-                q.x = X[j0 + t]; q.y = Y[j0 + t]; q.z = Z[j0 + t]; q.w = 0.0;
-                tile[t] = q;
-            }
-            __syncthreads();
-            if (j0 == i0)      // the block's own tile holds the self-pair
-                f64_tile<TJ, true>(tile, xi, yi, zi, threadIdx.x, sx, sy, sz);
-            else
-                f64_tile<TJ, false>(tile, xi, yi, zi, threadIdx.x, sx, sy, sz);
-        }
-    }
-    const bool live = i < p.N;
-    double gx = p.Cd * sx, gy = p.Cd * sy, gz = p.Cd * sz + p.Ez;
-    if (p.cf.on) {
-        double ex, ey, ez;
-        conf_field(p.cf, xi, yi, zi, ex, ey, ez);
-        gx += ex; gy += ey; gz += ez;
-    }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int d = 0; d < ds.nd; ++d) {
-        const double rx = xi - ds.pos[d][0], ry = yi - ds.pos[d][1], rz = zi - ds.pos[d][2];
-        const double r2 = rx * rx + ry * ry + rz * rz;
-        const double r = sqrt(r2);
-        const double ir3 = 1.0 / (r2 * r);
-        const double kq = p.Kq * ctl->Q[d] * ir3;
-        gx += kq * rx; gy += kq * ry; gz += kq * rz;
-        double f = live ? -(1.0 + r) * exp(-r) * ir3 : 0.0;
-        double fx = wave_sum(f * rx), fy = wave_sum(f * ry), fz = wave_sum(f * rz);
-        if (lane == 0) {
-            red[wv][d][0] = fx;
-            red[wv][d][1] = fy;
-            red[wv][d][2] = fz;
-        }
-    }
-    if (live) {
-        acc[i] = gx;
-        acc[Npad + i] = gy;
-        acc[2 * Npad + i] = gz;
-    }
-    __syncthreads();
-    for (int t = threadIdx.x; t < ds.nd * 3; t += BLOCK) {
-        const int d = t / 3, c = t % 3;
-        double s = 0.0;
-        for (int w = 0; w < BLOCK / 64; ++w) s += red[w][d][c];
-        atomicAdd(&ctl->part[blockIdx.x % kSlots][d][c], to_fixed(s, kForceScale, &ctl->status));
-    }
-}
-
 // ---------------------------------------------------------------------------
 // Boundary sampling helpers (Appendix B), dimensionless, FP64.
 

@@ -29,6 +29,7 @@
 #include "kernels.hpp"
 #include "cutoff.hpp"
 #include "pairsym.hpp"
+#include "pairsym64.hpp"
 #include "mesh.hpp"
 #include "worksplit.hpp"
 
@@ -125,7 +126,7 @@ struct od_system {
     // all-pairs sum with each pair evaluated once
     int pair_kind = OD_PAIR_AUTO;
     bool sym = false;
-    unsigned long long* acc_fix = nullptr;  // [3][Npad] int64 fixed-point pair sums
+    unsigned long long* acc_fix = nullptr;  // [3][Npad] int64 fixed-point pair sums (FP64: two words, [6][Npad])
     odk::SymItem* sym_items = nullptr;
     int n_sym_items = 0;
     // the same sum split into near pairs and a gridded far part (large systems)
@@ -283,7 +284,10 @@ od_status first_step_setup(od_system* s)
     return outside_capture(s->stream, [s](hipStream_t st) { return setup_mesh(s, st); });
 }
 
-size_t fix_bytes(const od_system* s) { return 3 * (size_t)s->Npad * sizeof(unsigned long long); }
+size_t fix_bytes(const od_system* s)
+{
+    return (s->prec == OD_PREC_FP32 ? 3 : 6) * (size_t)s->Npad * sizeof(unsigned long long);
+}
 
 // Sets up the symmetric pair sum: its fixed-point totals, and the work items
 // of the direct sum unless the split takes its place.  In test-particle mode
@@ -303,6 +307,29 @@ od_status setup_sym(od_system* s, void* room)
     if (st == OD_OK && s->custom_alloc) st = first_step_setup(s);
     if (st == OD_OK) HIPCHK(hipStreamSynchronize(s->stream));
     return st;
+}
+
+// 2^22 of the high word's units to a typical sum, n^(2/3) (n ions per r_De^3);
+// a total takes at most a flush per 64 ions and a few more.
+odk::Sym64 sym64_args(const od_system* s)
+{
+    const double n = 1.0 / (4.0 * kPI * s->pa.Cd);
+    return {s->acc_fix, s->Npad, std::exp2(std::round(22.0 - (2.0 / 3.0) * std::log2(n))),
+            0x1p62 / (double)(s->Npad / 64 + 64), &s->ctl->pair_bad};
+}
+
+// Totals and work items of an FP64 system's sum; where their memory is refused
+// it is summed one-sided.
+od_status setup_sym64(od_system* s, void* room)
+{
+    if (!s->pa.ion_ion) return OD_OK;
+    s->fix_in_mem = room != nullptr;
+    s->acc_fix = (unsigned long long*)(room ? room : dev_alloc(s, fix_bytes(s)));
+    if (s->acc_fix && setup_items(s, s->stream) != OD_OK) free_sym(s);
+    (void)hipGetLastError();
+    if (s->acc_fix) HIPCHK(hipMemsetAsync(s->acc_fix, 0, fix_bytes(s), s->stream));
+    HIPCHK(hipStreamSynchronize(s->stream));
+    return OD_OK;
 }
 
 // Chooses the all-pairs kernel for the system's kind: the symmetric one
@@ -703,9 +730,14 @@ od_status launch_step(od_system* s, bool timed)
             if (s->prec == OD_PREC_FP32)
                 odk::pair_forces_f32<kPairBlock, kPairTile><<<gp * s->nsplit, kPairBlock, 0, s->stream>>>(
                     (const float*)s->x, (float*)s->a, s->pa, s->ds, s->ctl, s->nsplit);
-            else
+            else {
+                const odk::Sym64 f = sym64_args(s);
+                if (s->n_sym_items > 0)
+                    odk::pair_sym64_kernel<<<s->n_sym_items, 256, 0, s->stream>>>(
+                        (const double*)s->x, (int)s->Npad, (int)s->N, s->sym_items, f, s->ctl);
                 odk::pair_forces_f64<kPairBlock, kPairTile><<<gp, kPairBlock, 0, s->stream>>>(
-                    (const double*)s->x, (double*)s->a, s->pa, s->ds, s->ctl);
+                    (const double*)s->x, (double*)s->a, s->pa, s->ds, f, s->ctl);
+            }
         } else if (k == 1 && s->sym && !s->cut && inl) {
             odk::step_tail_inl_kernel<float, true><<<gt, 256, 0, s->stream>>>(
                 (float*)s->x, (float*)s->v, (float*)s->a, s->acc_fix, s->ev, 1, s->pa, s->pu, s->ds, s->fa,
@@ -832,7 +864,7 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
     size_t at[7] = {0};
     for (int k = 0; k < 6; ++k) at[k + 1] = at[k] + (sizes[k] + 255) / 256 * 256;
     // with room for the default pair sum
-    const size_t fix = s->prec == OD_PREC_FP32 ? fix_bytes(s) : 0;
+    const size_t fix = fix_bytes(s);
     bool roomy = true;
     s->mem = dev_alloc(s, at[6] + fix);
     if (!s->mem) {
@@ -895,7 +927,8 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         s->fa = c.fa;
     }
     if (st == OD_OK)
-        st = apply_pair_kind(s, roomy && fix ? base + at[6] : nullptr);
+        st = s->prec == OD_PREC_FP32 ? apply_pair_kind(s, roomy ? base + at[6] : nullptr)
+                                     : setup_sym64(s, roomy ? base + at[6] : nullptr);
     if (st != OD_OK) {
         od_destroy(s);
         return st;
@@ -1180,6 +1213,7 @@ od_status od_set_state(od_system* s, const void* x, const void* v, const double*
     if (q)
         for (int d = 0; d < s->nd; ++d) h.Q[d] = q[d] / kQE;
     h.step = step;
+    h.pair_bad = 0;
     HIPCHK(hipMemcpyAsync(s->ctl, &h, sizeof h, hipMemcpyHostToDevice, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
     return OD_OK;
