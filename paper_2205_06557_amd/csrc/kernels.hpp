@@ -749,15 +749,7 @@ __device__ __forceinline__ void tail_block(T* __restrict__ X, T* __restrict__ Y,
     if (live) {
         T y[3], w[3];
         push_core<T>(x, v, a, i, n, pu, ds, ctl, collide, y, w, code, coll, lost);
-        if (INL && lost) {          // new boundary ion (Appendix B), here
-            double o[6];
-            reinject(pu, (uint64_t)i, n, o);
-            for (int c = 0; c < 3; ++c) {
-                y[c] = (T)o[c];
-                w[c] = (T)o[3 + c];
-            }
-        }
-        // else a lost ion is overwritten by the reinjection kernel
+        // a lost ion is overwritten by its reinjection
         X[i] = y[0]; Y[i] = y[1]; Z[i] = y[2];
         VX[i] = w[0]; VY[i] = w[1]; VZ[i] = w[2];
         ev[i] = code | (coll ? kEvCollBit : 0);
@@ -806,7 +798,20 @@ __device__ __forceinline__ void tail_block(T* __restrict__ X, T* __restrict__ Y,
     // one per wave).
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (wv != 0) return;            // the ticket and the finalize need one wave
+    // New boundary ions (Appendix B) come last: their FP64 sampling, a few
+    // microseconds, then runs beside the ticket and the finalize of wave 0
+    // instead of before them.
+    auto replace_lost = [&]() {
+        if (!INL || !lost) return;
+        double o[6];
+        reinject(pu, (uint64_t)i, n, o);
+        X[i] = (T)o[0]; Y[i] = (T)o[1]; Z[i] = (T)o[2];
+        VX[i] = (T)o[3]; VY[i] = (T)o[4]; VZ[i] = (T)o[5];
+    };
+    if (wv != 0) {                  // the ticket and the finalize need one wave
+        replace_lost();
+        return;
+    }
     int is_last = 0;
     if (lane == 0) {
         if (nblk <= kSlots) {
@@ -821,6 +826,7 @@ __device__ __forceinline__ void tail_block(T* __restrict__ X, T* __restrict__ Y,
         __threadfence();
         finalize_wave(fa, ds, ctl);
     }
+    replace_lost();
 }
 
 // The tail of one system: block b handles ions [256 b, 256 b + 256); lost
