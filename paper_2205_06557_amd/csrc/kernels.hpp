@@ -272,29 +272,39 @@ __device__ inline double inflow(double m, double s)
     return m * 0.5 * erfc(-m / (s * 1.4142135623730950488)) + s * npdf(m / s);
 }
 
-// Flux-weighted normal speed on a face: the v >= 0 whose flux tail
-// int_v^inf v' phi(v') dv' equals uu times the total inflow.  Newton on the
-// tail (slope -v phi(v)) inside a shrinking bracket, bisection when a Newton
-// step would not land strictly inside it; stops when a step is below
-// 1e-13 s, or when the tail equals the goal to within the rounding of its
-// own evaluation, 8 ulp of the magnitudes of its terms (where the flux
-// density is tiny the root is resolved no further than that).
-__device__ double flux_speed(double uu, double m, double s)
+// Upper-tail quantile of the standard normal to 3e-3 (Abramowitz and Stegun
+// 26.2.22), p in (0, 1).
+__device__ inline float normal_quantile(float p)
 {
-    const double goal = uu * inflow(m, s);
+    const float t = sqrtf(-2.0f * logf(fmaxf(fminf(p, 1.0f - p), 1e-37f)));
+    const float x = t - fmaf(0.27061f, t, 2.30753f) / fmaf(fmaf(0.04481f, t, 0.99229f), t, 1.0f);
+    return p < 0.5f ? x : -x;
+}
+
+// Root of a decreasing flux tail inside (0, hi), from v: tail(v, slope, curv,
+// mag) gives the tail minus the goal, its slope, the ratio of its second
+// derivative to its slope and the magnitude of its terms.  Halley's iteration
+// inside a shrinking bracket, bisection when a step would not land strictly
+// inside it; stops when a step is below 1e-13 s, or when the tail equals the
+// goal to within the rounding of its own evaluation, 8 ulp of the magnitudes
+// of its terms (where the flux density is tiny the root is resolved no further
+// than that).  Three evaluations from the starts below at the drifts in use;
+// Newton steps from a fixed start took 6 to 16 and, where the last step was
+// lost in the bracket's rounding, up to 60.
+template <typename F>
+__device__ double tail_root(F tail, double v, double hi, double s)
+{
     double lo = 0.0;
-    double hi = fmax(m, 0.0) + 40.0 * s;
-    double v = fmax(m, 0.0) + s;
     for (int it = 0; it < 400; ++it) {
-        const double t = (v - m) / s;
-        const double t1 = m * 0.5 * erfc(t * 0.70710678118654752440), t2 = s * npdf(t);
-        const double g = (t1 + t2) - goal;
-        if (fabs(g) <= 8.0 * 2.220446049250313e-16 * (fabs(t1) + t2)) break;
+        double slope, curv, mag;
+        const double g = tail(v, slope, curv, mag);
+        if (fabs(g) <= 8.0 * 2.220446049250313e-16 * mag) break;
         if (g > 0.0) lo = v; else hi = v;
-        const double slope = -v * npdf(t) / s;
         double nv = 0.5 * (lo + hi);
         if (slope < 0.0) {
-            const double cand = v - g / slope;
+            const double h = g / slope, den = 1.0 - 0.5 * h * curv;
+            const double cand = v - (den > 0.3 && den < 3.0 ? h / den : h);
+            if (fabs(cand - v) <= 1e-13 * s) return cand;
             if (cand > lo && cand < hi) nv = cand;
         }
         const bool done = fabs(nv - v) <= 1e-13 * s;
@@ -302,6 +312,34 @@ __device__ double flux_speed(double uu, double m, double s)
         if (done) break;
     }
     return v;
+}
+
+// Flux-weighted normal speed on a face: the v >= 0 whose flux tail
+// int_v^inf v' phi(v') dv' equals uu times the total inflow.  Starts from the
+// quantile of the normal that the flux distribution is close to for m > s, or
+// of the Rayleigh distribution that it is for m = 0.
+__device__ double flux_speed(double uu, double m, double s)
+{
+    const double goal = uu * inflow(m, s);
+    const double hi = fmax(m, 0.0) + 40.0 * s;
+    double v;
+    if (m < s) {
+        const float c = (float)(m > 0.0 ? 0.5 * m : m), q = (float)s;
+        v = (double)(c + sqrtf(fmaf(c, c, -2.0f * q * q * logf(fmaxf((float)uu, 1e-37f)))));
+    } else {
+        const float k = (float)(s / m), p = (float)(uu < 0.5 ? uu : 1.0 - uu);
+        const float q = normal_quantile(p);
+        v = m + s * (double)(k + (uu < 0.5 ? q : -q) * (1.0f - 0.5f * k * k));
+    }
+    if (!(v > 0.0 && v < hi)) v = fmax(m, 0.0) + s;
+    return tail_root([&](double x, double& slope, double& curv, double& mag) {
+        const double t = (x - m) / s, e = npdf(t);
+        const double t1 = m * 0.5 * erfc(t * 0.70710678118654752440), t2 = s * e;
+        slope = -x * e / s;
+        curv = 1.0 / x - t / s;
+        mag = fabs(t1) + t2;
+        return (t1 + t2) - goal;
+    }, v, hi, s);
 }
 
 // Field-driven collisional flow (constant-frequency charge exchange in a
@@ -323,37 +361,34 @@ __device__ inline double fd_A(double x, double ufd, double sig)
 
 // Flux-weighted inward speed at the bottom (top = false, v_z = s) or top
 // (v_z = -s) face for the field-driven distribution: the s >= 0 whose flux
-// tail is uu times the face's inflow.  Safeguarded Newton as flux_speed.
+// tail is uu times the face's inflow.  At the bottom the start is the root for
+// sig = 0, where the tail is (1 + x) e^-x in x = v / ufd: the first terms of
+// its inverse in w = sqrt(-2 ln uu).
 __device__ double fd_speed(double uu, double ufd, double sig, bool top)
 {
     const double k = 0.70710678118654752440;
-    // tail at v, its slope and the magnitude of its terms (rounding scale)
-    auto tail = [&](double v, double& slope, double& mag) {
-        const double A = fd_A(top ? -v : v, ufd, sig);
+    // tail at v, its derivatives and the magnitude of its terms (rounding scale)
+    auto tail = [&](double v, double& slope, double& curv, double& mag) {
+        const double A = fd_A(top ? -v : v, ufd, sig), e = npdf(v / sig);
         slope = -v * A / ufd;
-        const double t1 = (top ? ufd - v : v + ufd) * A, t2 = sig * npdf(v / sig);
+        const double dA = e / sig - A / ufd;           // A' at v, or at -v
+        curv = 1.0 / v + (top ? -dA : dA) / A;
+        const double t1 = (top ? ufd - v : v + ufd) * A, t2 = sig * e;
         const double t3 = ufd * 0.5 * erfc(v / sig * k);
         mag = fabs(t1) + t2 + t3;
         return top ? (t1 + t2) - t3 : (t1 + t2) + t3;
     };
-    double slope, mag;
-    const double goal = uu * tail(0.0, slope, mag);
-    double lo = 0.0, hi = 40.0 * sig + (top ? 0.0 : 50.0 * ufd);
-    double v = top ? sig : ufd + sig;
-    for (int it = 0; it < 400; ++it) {
-        const double g = tail(v, slope, mag) - goal;
-        if (fabs(g) <= 8.0 * 2.220446049250313e-16 * mag) break;   // as flux_speed
-        if (g > 0.0) lo = v; else hi = v;
-        double nv = 0.5 * (lo + hi);
-        if (slope < 0.0) {
-            const double cand = v - g / slope;
-            if (cand > lo && cand < hi) nv = cand;
-        }
-        const bool done = fabs(nv - v) <= 1e-13 * sig;
-        v = nv;
-        if (done) break;
+    double slope, curv, mag;
+    const double goal = uu * tail(0.0, slope, curv, mag);
+    const double hi = 40.0 * sig + (top ? 0.0 : 50.0 * ufd);
+    double v = sig;
+    if (!top) {
+        const float w = sqrtf(-2.0f * logf(fmaxf((float)uu, 1e-37f)));
+        v = ufd * (double)(w * fmaf(w, fmaf(w, 1.0f / 36.0f, 1.0f / 3.0f), 1.0f));
     }
-    return v;
+    if (!(v > 0.0 && v < hi)) v = top ? sig : ufd + sig;
+    return tail_root([&](double x, double& sl, double& cu, double& mg) { return tail(x, sl, cu, mg) - goal; }, v, hi,
+                     sig);
 }
 
 // New position and velocity of a lost ion, from blocks (i, n, REINJ, 0/1).
