@@ -14,7 +14,7 @@ namespace {
 
 constexpr double kSymItemsTarget = 65536.0;    // work items of the symmetric sum
 constexpr double kSymMinGroupedItems = 2048.0; // fewer grouped items: one target row per item
-constexpr double kSymMinItems = 512.0;         // fewer one-tile items: one item per 64-ion sub-tile
+constexpr double kSymMinItems = 1024.0;        // fewer one-tile items: one item per 64-ion sub-tile
 
 // Work items of the symmetric sum of one system of T tiles: groups of
 // kSymRows target tile rows, each group with runs of at most C source tiles
@@ -22,8 +22,10 @@ constexpr double kSymMinItems = 512.0;         // fewer one-tile items: one item
 // kSymItemsTarget items.  Where grouping leaves fewer than kSymMinGroupedItems
 // items (small systems, too few to fill the chip), one target row per item
 // instead; where even one tile pair per item leaves fewer than kSymMinItems
-// (a few thousand ions), each tile pair is cut into its four 64-ion source
-// sub-tiles, so that a step's pair sum is not one long chain per block.  The
+// (up to 11,500 ions), each tile pair is cut into its four 64-ion source
+// sub-tiles, so that a step's pair sum is not one long chain per block (whole
+// tiles against sub-tiles: 37 / 32 us at 8,192 ions, 46 / 38 at 10,000, 55 /
+// 63 at 12,345).  The
 // split depends on T only, so a system's sums are grouped the same way alone
 // and in a batch.  one_row: one target row per item at every size; target:
 // the number of items aimed at (batch options; both change the FP32 partial
