@@ -206,7 +206,7 @@ def cutoff_bench(args):
         "series": series,
         "roofline": {"bound": "alu", "achieved": achieved_within / 1e12, "peak": PEAK_FP32 / 1e12,
                      "unit": "TFLOP/s", "frac": achieved_within / PEAK_FP32, "traffic": None,
-                     "kernel": "slab sort + pair_cut",
+                     "kernel": "sort + pair_cut",
                      "flop_per_pair": FLOP_PER_CUT_PAIR,
                      "flop_convention": "ordered ion pairs closer than r_cut (the method's work), "
                                         "estimated from sampled targets",

@@ -181,19 +181,20 @@ od_status od_get_units(od_system* sys, double* units_host);
  * force is minus the gradient of that energy.  Grain terms and the sum of
  * Eq. (1) stay complete.  Distances in m; r_cut <= 0 returns to the
  * all-pairs sum.  FP32 systems only (OD_EINVAL otherwise); needs
- * 0 <= r_switch < r_cut.  Each step then sorts the ions into slabs along z
- * (width about r_cut / 16, or r_cut / 8 where that would pass 1024 slabs;
- * at most 1024) and evaluates each pair of
- * blocks of 256 sorted ions within reach once (both reactions, int64 fixed
- * point as the symmetric all-pairs kernel).
- * Allocates the sort buffers (about 44 bytes per ion plus 4 bytes per slab
- * and block of 256 ions) with the system's allocator; synchronises the
- * system's stream. */
+ * 0 <= r_switch < r_cut.  Each step then sorts the ions into layers along z
+ * and along a curve over each layer's cross section, and evaluates each pair
+ * of blocks of 256 sorted ions within reach once (both reactions, int64 fixed
+ * point as the symmetric all-pairs kernel; groups of 64 by 64 that lie beyond
+ * r_cut are left out).
+ * Allocates the sort buffers (about 52 bytes per ion) with the system's
+ * allocator; synchronises the system's stream. */
 od_status od_set_cutoff(od_system* sys, double r_switch, double r_cut);
 
-/* Cutoff bookkeeping of the last step: *nslab slabs and *pairs_evaluated,
- * the ordered ion pairs the cutoff kernel covered (each pair of 256-ion
- * blocks counted both ways, padding included).  OD_ESTATE without a cutoff.
+/* Cutoff bookkeeping of the last step: *nslab slabs along z (width about
+ * r_cut / 16, or r_cut / 8 where that would pass 1024 slabs; at most 1024) and
+ * *pairs_evaluated, the ordered ion pairs that blocks of 256 ions in the order
+ * of the slabs cover within reach (each pair of blocks counted both ways,
+ * padding included): an upper bound of what the kernel evaluates.  OD_ESTATE without a cutoff.
  * Synchronises. */
 od_status od_get_cutoff_info(od_system* sys, int32_t* nslab, int64_t* pairs_evaluated);
 
@@ -316,7 +317,7 @@ od_status od_rng_block(uint64_t seed, uint64_t system, const uint64_t* ctr_host,
 /* Kernel timing with HIP events on the system's stream (measurement
  * surface, no paper passage).  While enabled, od_step brackets every launch;
  * od_get_kernel_times synchronises and returns, per kernel class {0 pair
- * forces (with a cutoff: the slab sort and its epilogue too), 1 the step's
+ * forces (with a cutoff: the sort and its epilogue too), 1 the step's
  * tail (acceleration of the symmetric sum, push, absorption, exit, and the
  * charge and force bookkeeping of the step in its last block), 2 reinjection
  * (systems above 16,384 ions; smaller ones reinject inside the tail), 3 not

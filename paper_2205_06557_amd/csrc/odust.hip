@@ -12,7 +12,7 @@
 //             last-step record, running sums, step counter, status word).
 // All per-step state stays on the device; a step is three launches (pair sum;
 // the per-ion tail, whose last block finalizes the step; reinjection of the
-// ions the tail listed; a cutoff adds the slab sort and its epilogue, the
+// ions the tail listed; a cutoff adds the sort and its epilogue, the
 // split sum of large systems its sort and grid kernels) and needs no host
 // synchronisation.
 #include <hip/hip_runtime.h>
@@ -113,15 +113,13 @@ struct od_system {
     odk::PushArgs pu{};
     odk::FinalArgs fa{};
     std::vector<double> conf_grid;      // dimensionless confinement potentials
-    // ion-ion cutoff (FP32): slab sort buffers
+    // ion-ion cutoff (FP32): sort buffers
     bool cut = false;
     odk::CutArgs ca{};
-    float* xs_sorted = nullptr;         // [3][Npad] positions in slab order
+    float* xs_sorted = nullptr;         // [3][Npad] positions in sorted order
     int* idx_sorted = nullptr;          // [Npad] ion of each sorted slot
-    int* slab = nullptr;                // [Npad] slab of each ion
-    int* table = nullptr;               // [nslab][nblk] per-block counts, then offsets
-    int* slab_total = nullptr;          // [nslab]
-    int* slab_start = nullptr;          // [nslab + 1]
+    odk::CutBufs cb{};
+    void* cut_mem = nullptr;            // the buffers of cb
     unsigned long long* cut_fix = nullptr;  // [3][Npad] fixed-point sums by sorted slot
     // all-pairs sum with each pair evaluated once
     int pair_kind = OD_PAIR_AUTO;
@@ -176,14 +174,12 @@ void free_cutoff(od_system* s)
 {
     dev_free(s, s->xs_sorted);
     dev_free(s, s->idx_sorted);
-    dev_free(s, s->slab);
-    dev_free(s, s->table);
-    dev_free(s, s->slab_total);
-    dev_free(s, s->slab_start);
+    dev_free(s, s->cut_mem);
     dev_free(s, s->cut_fix);
     s->cut_fix = nullptr;
     s->xs_sorted = nullptr;
-    s->idx_sorted = s->slab = s->table = s->slab_total = s->slab_start = nullptr;
+    s->idx_sorted = nullptr;
+    s->cut_mem = nullptr;
     s->cut = false;
 }
 
@@ -708,14 +704,20 @@ od_status launch_step(od_system* s, bool timed)
             const float* x = (const float*)s->x;
             const int64_t P = s->Npad;
             const int nb = s->ca.nblk;
-            odk::slab_count_kernel<<<nb, 256, 0, s->stream>>>(x + 2 * P, (int)s->N, s->ca, s->slab, s->table);
-            odk::slab_scan_kernel<<<s->ca.nslab, 256, 0, s->stream>>>(s->table, nb, s->slab_total);
-            odk::slab_start_kernel<<<1, odk::kMaxSlabs, 0, s->stream>>>(s->slab_total, s->ca.nslab, s->slab_start);
-            odk::slab_scatter_kernel<<<nb, 256, 0, s->stream>>>(
-                x, x + P, x + 2 * P, (int)s->N, s->ca, s->slab, s->table, s->slab_start, s->xs_sorted,
-                s->xs_sorted + P, s->xs_sorted + 2 * P, s->idx_sorted);
-            odk::pair_cut_kernel<kPairBlock><<<nb, kPairBlock, 0, s->stream>>>(
-                s->xs_sorted, s->slab_start, s->cut_fix, s->pa, s->ca, s->ctl);
+            const int N = (int)s->N;
+            odk::cut_bin_kernel<<<nb, 256, 0, s->stream>>>(x, P, N, s->ca, s->cb);
+            odk::cut_scan_kernel<<<s->ca.nlay, 256, 0, s->stream>>>(s->ca, s->cb);
+            odk::cut_start_kernel<<<2, 256, 0, s->stream>>>(s->ca, s->cb);
+            odk::cut_place_kernel<<<nb, 256, 0, s->stream>>>(N, s->ca, s->cb);
+            odk::cut_order_kernel<<<nb, 256, 0, s->stream>>>(x, P, N, s->ca, s->cb, s->xs_sorted, s->idx_sorted);
+            odk::cut_box_kernel<<<nb, 256, 0, s->stream>>>(s->xs_sorted, P, N, s->ca, s->cb);
+            // Several blocks to a tile, for small systems to fill the chip and
+            // large ones to fill its last wave: 49,152 blocks against 2,048 and
+            // 8,192 took 0.20 / 0.24 / 0.20 ms at 2^14 ions, 3.4 / 4.6 / 3.6 at
+            // 2^17, 14.7 / 17.9 / 15.4 at 2^19.
+            const int gy = std::max(1, std::min(64, 49152 / nb));
+            odk::pair_cut_kernel<kPairBlock><<<dim3(nb, gy), kPairBlock, 0, s->stream>>>(
+                s->xs_sorted, s->cb, s->cut_fix, s->pa, s->ca, s->ctl);
             odk::pair_cut_epilogue<<<nb, 256, 0, s->stream>>>(s->xs_sorted, s->idx_sorted, s->cut_fix,
                                                                (float*)s->a, s->pa, s->ds, s->ctl);
         } else if (k == 0 && s->mesh && s->direct_steps == 0) {
@@ -1040,9 +1042,8 @@ od_status od_set_cutoff(od_system* s, double r_switch, double r_cut)
     if (s->prec != OD_PREC_FP32) return fail(OD_EINVAL, "the cutoff path runs in FP32 only");
     if (!(r_switch >= 0.0) || !(r_switch < r_cut)) return fail(OD_EINVAL, "need 0 <= r_switch < r_cut");
     const double H = s->sim.H / s->lam, rc = r_cut / s->lam, rs = r_switch / s->lam;
-    // Slabs of about r_cut / 16, so that the blocks within reach overshoot the
-    // cutoff sphere by little; where that many would pass kMaxSlabs, r_cut / 8
-    // (timed faster there than the capped finer width).  reach = ceil(r_cut / width).
+    // Slabs in which od_get_cutoff_info counts: about r_cut / 16 thick, or
+    // r_cut / 8 where that many would pass kMaxSlabs.  reach = ceil(r_cut / width).
     const double per = std::floor(16.0 * H / rc) <= odk::kMaxSlabs ? 16.0 : 8.0;
     const int nslab = (int)std::min<double>(odk::kMaxSlabs, std::max(1.0, std::floor(per * H / rc)));
     const int reach = (int)std::ceil(rc * nslab / H);
@@ -1051,16 +1052,32 @@ od_status od_set_cutoff(od_system* s, double r_switch, double r_cut)
     const size_t P = (size_t)s->Npad;
     s->xs_sorted = (float*)dev_alloc(s, 3 * P * sizeof(float));
     s->idx_sorted = (int*)dev_alloc(s, P * sizeof(int));
-    s->slab = (int*)dev_alloc(s, P * sizeof(int));
-    s->table = (int*)dev_alloc(s, (size_t)nslab * nblk * sizeof(int));
-    s->slab_total = (int*)dev_alloc(s, (size_t)nslab * sizeof(int));
-    s->slab_start = (int*)dev_alloc(s, (size_t)(nslab + 1) * sizeof(int));
+    // Sort layers as thick as a cube of 64 ions, cells of at most 0.7 of that
+    // (64 a side at most): at 2^19 ions of the long domain, layers of 0.25 and
+    // of 0.5 r_De leave 0.82 and 0.75 of the pair work with 16 cells a side,
+    // 0.84 and 0.78 with 8.
+    const double R = s->pu.R, cube = std::cbrt(64.0 * kPI * R * R * H / (double)s->N);
+    const int nlay = (int)std::min(65536.0, std::max(1.0, std::floor(H / cube)));
+    int side = 1;
+    while (side < 64 && 2.0 * R / side > 0.7 * cube) side *= 2;
+    while (side > 1 && (double)nlay * side * side > 4194304.0) side /= 2;
+    const size_t bins = (size_t)nlay * side * side;
+    const size_t ints[8] = {P, P, P, bins, bins + nlay, (size_t)nlay + 1, (size_t)nslab, (size_t)nslab + 1};
+    size_t at[10] = {0};
+    for (int k = 0; k < 8; ++k) at[k + 1] = at[k] + (ints[k] * sizeof(int) + 255) / 256 * 256;
+    at[9] = at[8] + 24 * (size_t)nblk * sizeof(float);
+    s->cut_mem = dev_alloc(s, at[9]);
     s->cut_fix = (unsigned long long*)dev_alloc(s, 3 * P * sizeof(unsigned long long));
-    if (!s->xs_sorted || !s->idx_sorted || !s->slab || !s->table || !s->slab_total || !s->slab_start ||
-        !s->cut_fix) {
+    if (!s->xs_sorted || !s->idx_sorted || !s->cut_mem || !s->cut_fix) {
         free_cutoff(s);
-        return fail(OD_ENOMEM, "device allocation of the slab sort failed");
+        return fail(OD_ENOMEM, "device allocation of the cutoff's sort failed");
     }
+    {
+        char* m = (char*)s->cut_mem;
+        auto part = [&](int k) { return (int*)(m + at[k]); };
+        s->cb = {part(0), part(1), part(2), part(3), part(4), part(5), part(6), part(7), (float*)(m + at[8])};
+    }
+    HIPCHK(hipMemset(s->cut_mem, 0, at[9]));
     HIPCHK(hipMemset(s->cut_fix, 0, 3 * P * sizeof(unsigned long long)));
     // padding slots of the sorted copy sit far away and are never overwritten
     const size_t npad = P - (size_t)s->N;
@@ -1076,6 +1093,14 @@ od_status od_set_cutoff(od_system* s, double r_switch, double r_cut)
     s->ca.reach = std::max(reach, 1);
     s->ca.z0 = (float)(-0.5 * H);
     s->ca.inv_w = (float)(nslab / H);
+    s->ca.nlay = nlay;
+    s->ca.lreach = (int)std::min<double>(nlay, std::ceil(rc * nlay / H * (1.0 + 1e-5)));
+    s->ca.side = side;
+    s->ca.inv_l = (float)(nlay / H);
+    s->ca.x0 = (float)-R;
+    s->ca.inv_c = (float)(side / (2.0 * R));
+    s->ca.skip2 = (float)(rc * rc * (1.0 + 1e-5));
+    s->ca.plain2 = (float)(rs * rs * (1.0 - 1e-5));
     s->ca.rsw = (float)rs;
     s->ca.inv_sw = (float)(1.0 / (rc - rs));
     s->cut = true;
@@ -1088,7 +1113,7 @@ od_status od_get_cutoff_info(od_system* s, int32_t* nslab, int64_t* pairs_evalua
     if (!s->cut) return fail(OD_ESTATE, "no cutoff is set");
     const int ns = s->ca.nslab;
     std::vector<int> start(ns + 1);
-    HIPCHK(hipMemcpyAsync(start.data(), s->slab_start, (ns + 1) * sizeof(int), hipMemcpyDeviceToHost, s->stream));
+    HIPCHK(hipMemcpyAsync(start.data(), s->cb.slab_start, (ns + 1) * sizeof(int), hipMemcpyDeviceToHost, s->stream));
     HIPCHK(hipStreamSynchronize(s->stream));
     if (nslab) *nslab = ns;
     if (pairs_evaluated) {
