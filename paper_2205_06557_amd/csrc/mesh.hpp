@@ -268,7 +268,8 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_spread_kernel(MeshArgs m, M
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c16 = lane & 15, q = lane >> 4;
     for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) grid[k] = 0ull;
     __syncthreads();
-    for (int k = wv; k < kMeshG * kMeshG; k += kMeshThreads / 64) {
+    const int waves = kMeshThreads / 64;
+    for (int k = blockIdx.y * waves + wv; k < kMeshG * kMeshG; k += gridDim.y * waves) {
         const MeshColumn c = mesh_column(m, b, k);
         if (c.s0 >= c.s1) continue;
         mesh4 acc[kMeshReach];
@@ -309,7 +310,7 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_spread_kernel(MeshArgs m, M
                                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
     __syncthreads();
-    unsigned long long* o = b.brick + (long long)blockIdx.x * kMeshNodes;
+    unsigned long long* o = b.brick + ((long long)blockIdx.x * gridDim.y + blockIdx.y) * kMeshNodes;
     for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) o[k] = grid[k];
 }
 
@@ -335,8 +336,9 @@ __global__ __launch_bounds__(256) void mesh_sum_kernel(MeshArgs m, MeshBufs b)
             for (int k = 0; k < 2; ++k) {
                 const int bx = x / bc - k, ox = x - bx * bc;
                 if (bx < 0 || bx >= m.nbx || ox >= kMeshLx) continue;
-                s += (long long)b.brick[((long long)(bz * m.nby + by) * m.nbx + bx) * kMeshNodes +
-                                        (oz * kMeshLx + oy) * kMeshLx + ox];
+                const unsigned long long* q = b.brick + ((long long)(bz * m.nby + by) * m.nbx + bx) * m.parts * kMeshNodes +
+                                              (oz * kMeshLx + oy) * kMeshLx + ox;
+                for (int p = 0; p < m.parts; ++p) s += (long long)q[(long long)p * kMeshNodes];
             }
         }
     }
@@ -501,7 +503,8 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_gather_kernel(MeshArgs m, M
         node[k] = x < m.n[0] && y < m.n[1] && z < m.n[2] ? b.phi[((long long)z * m.n[1] + y) * m.n[0] + x] : 0.0;
     }
     __syncthreads();
-    for (int k = threadIdx.x; k < pre[kMeshG * kMeshG]; k += kMeshThreads) {
+    const int group = (threadIdx.x >> 6) * gridDim.y + blockIdx.y;
+    for (int k = group * 64 + (threadIdx.x & 63); k < pre[kMeshG * kMeshG]; k += gridDim.y * kMeshThreads) {
         int c = 0;
         while (pre[c + 1] <= k) ++c;
         const int t = start[c] + (k - pre[c]);
@@ -859,7 +862,7 @@ inline size_t mesh_scratch(const MeshArgs& m, char* base, MeshBufs& b)
     b.mc = (int)std::min<size_t>(kMeshM, std::max<size_t>(1, ((size_t)kMeshScratchMb << 20) / (16 * v)));
     const int passes = (kMeshM + b.mc - 1) / b.mc;
     b.mc = (kMeshM + passes - 1) / passes;
-    const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * kMeshNodes * 8;
+    const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * m.parts * kMeshNodes * 8;
     a.take(&b.t1, std::max(conv, brick));
     b.t2 = b.t1 ? b.t1 + (size_t)b.mc * v : nullptr;
     b.brick = (unsigned long long*)b.t1;
@@ -895,7 +898,7 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
     mesh_box_kernel<<<gc, 256, 0, st>>>(m, b);
     const int bricks = m.nbx * m.nby * m.nbz;
     constexpr size_t lds = kMeshNodes * 8;
-    mesh_spread_kernel<<<bricks, kMeshThreads, lds, st>>>(m, b);
+    mesh_spread_kernel<<<dim3(bricks, m.parts), kMeshThreads, lds, st>>>(m, b);
     mesh_sum_kernel<<<(unsigned)((v + 255) / 256), 256, 0, st>>>(m, b);
     for (int m0 = 0; m0 < kMeshM; m0 += b.mc) {
         const int mc = std::min(b.mc, kMeshM - m0);
@@ -903,7 +906,7 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
         mesh_conv<1>(m, b, b.t1, b.t2, m0, mc, st);
         mesh_conv<2>(m, b, b.t2, b.phi, m0, mc, st);
     }
-    mesh_gather_kernel<<<bricks, kMeshThreads, lds, st>>>(m, b);
+    mesh_gather_kernel<<<dim3(bricks, m.gparts), kMeshThreads, lds, st>>>(m, b);
     const int tiles = (m.cap / 64 + 7) / 8 * 8;
     if (m.cap / 64 >= 8192)
         mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, fix, fstride,

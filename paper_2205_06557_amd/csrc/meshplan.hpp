@@ -46,6 +46,7 @@ struct MeshArgs {
     int nc[3], n[3];                // grid cells and nodes (nc + 9) per axis
     int ncx, ncy, nzb;              // columns along x and y; sort bins per column
     int nbx, nby, nbz;              // bricks per axis
+    int parts, gparts;              // blocks per brick that spread its charges, that gather its forces
     int ng;                         // entries of one Green's table (zero padded)
     double R, Hh, h, inv_h;         // domain radius and half height; grid spacing
     float rc, rc2, irc2, cw;        // near radius, its square, -2 / rc^2; column width
@@ -152,6 +153,28 @@ inline bool mesh_dims(double R, double H, double rc, MeshArgs& a)
 // The split of a system of N ions (dimensionless R, H).  False: use the direct
 // sum.
 //
+// Blocks per brick, at most `most`: a compute unit holds one block, a last
+// round that is nearly empty costs as much as a full one, a block has 0.08 of
+// a brick's work to do whatever its part (the brick's nodes in and out of
+// LDS), and a tenth of the bricks lie in the corners outside the cylinder.
+// More than one only where that should gain a tenth.  One against the blocks
+// chosen, us per pair sum: 336 / 281 at 40,960 ions (128 bricks), 405 / 382 at
+// 2^16 (144), 638 / 612 at 2^17 (300); 489 / 507 with four at 98,304 (275).
+inline int mesh_parts(const MeshArgs& a, int most)
+{
+    const double bricks = 0.9 * a.nbx * a.nby * a.nbz;
+    int best = 1;
+    double cost = 0.9 * std::ceil(bricks / 256.0) * 1.08;
+    for (int p = 2; p <= most; ++p) {
+        const double c = std::ceil(bricks * p / 256.0) * (1.0 / p + 0.08);
+        if (c < cost) {
+            cost = c;
+            best = p;
+        }
+    }
+    return best;
+}
+
 // r_c trades near pairs (r_c^3) against the grid (its nodes go as r_c^-3, the
 // convolutions as r_c^-4) and scales with the ion spacing: in units of
 // (27 / n)^(1/3), a step took 0.61 ms at 1.6, 0.65 at 1.68, 0.65 at 1.75 and
@@ -179,6 +202,8 @@ inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
     a.nbx = (a.ncx + kMeshG - 1) / kMeshG;
     a.nby = (a.ncy + kMeshG - 1) / kMeshG;
     a.nbz = (a.nc[2] + kMeshBz - 1) / kMeshBz;
+    a.parts = mesh_parts(a, 2);
+    a.gparts = mesh_parts(a, 4);
     a.ng = std::max(a.n[0], a.n[2]) + 80;
 
     // Gaussians: force of L fitted to that of e^-r / r on [r_c, diag]
