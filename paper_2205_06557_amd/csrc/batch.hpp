@@ -135,7 +135,8 @@ void pair_sym_batch_kernel(const float* __restrict__ xs, long long plane, const 
 // fix), else the one-sided kernel's acceleration planes.  Block 0 also
 // rewinds the pair kernel's work queue (that kernel has finished).
 template <bool FIX>
-__global__ __launch_bounds__(256) void step_tail_batch_kernel(float* __restrict__ xs, float* __restrict__ vs,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8)))
+void step_tail_batch_kernel(float* __restrict__ xs, float* __restrict__ vs,
                                                               float* __restrict__ as, long long plane,
                                                               unsigned long long* __restrict__ fix,
                                                               uint8_t* __restrict__ ev, const SysDesc* sys,

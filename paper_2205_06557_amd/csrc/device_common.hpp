@@ -167,11 +167,30 @@ __device__ inline double exp_neg_f64(double r)
 }
 
 // ---------------------------------------------------------------------------
-// Wave64 reduction of a double (butterfly over xor masks).
-__device__ inline double wave_sum(double v)
+// Wave64 sum of a 64-bit value: butterfly over the xor masks 32 and 16, then
+// rotations by 8, 4, 2 and 1 within rows of 16 lanes, which after the steps
+// before them bring the same values as the masks 8 to 1, without LDS.
+template <int ROT>
+__device__ inline unsigned long long row_rotate(unsigned long long b)
 {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m, 64);
+    const unsigned int lo = __builtin_amdgcn_mov_dpp((int)(unsigned int)b, 0x120 + ROT, 0xf, 0xf, true);
+    const unsigned int hi = __builtin_amdgcn_mov_dpp((int)(unsigned int)(b >> 32), 0x120 + ROT, 0xf, 0xf, true);
+    return (unsigned long long)hi << 32 | lo;
+}
+
+template <typename V>
+__device__ inline V wave_sum(V v)
+{
+    static_assert(sizeof(V) == 8, "64-bit values");
+    auto rot = [](auto r, V x) {
+        return __builtin_bit_cast(V, row_rotate<decltype(r)::value>(__builtin_bit_cast(unsigned long long, x)));
+    };
+    v += __shfl_xor(v, 32, 64);
+    v += __shfl_xor(v, 16, 64);
+    v += rot(std::integral_constant<int, 8>{}, v);
+    v += rot(std::integral_constant<int, 4>{}, v);
+    v += rot(std::integral_constant<int, 2>{}, v);
+    v += rot(std::integral_constant<int, 1>{}, v);
     return v;
 }
 
