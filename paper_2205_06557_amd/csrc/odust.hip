@@ -134,6 +134,8 @@ struct od_system {
     odk::MeshBufs mb{};
     void* mesh_mem = nullptr;
     bool fix_in_mem = false;            // acc_fix lies in mem
+    void* fix64 = nullptr;              // FP64: room for acc_fix in mem, or null
+    bool sym64_set = false;             // FP64: acc_fix and the items set up, or refused
     int direct_steps = 0;               // steps to sum directly first: the state has ions outside the domain
     // device memory: one allocation (mem), cut into the buffers below
     void* mem = nullptr;
@@ -269,6 +271,26 @@ od_status outside_capture(hipStream_t stream, F setup)
     return r;
 }
 
+size_t fix_bytes(const od_system* s)
+{
+    return (s->prec == OD_PREC_FP32 ? 3 : 6) * (size_t)s->Npad * sizeof(unsigned long long);
+}
+
+// Totals and work items of an FP64 system's sum, set up by the first step (at
+// creation it would cost 0.1 ms, a third of it); where their memory is refused
+// the system is summed one-sided.
+od_status setup_sym64(od_system* s, hipStream_t st)
+{
+    s->sym64_set = true;
+    s->fix_in_mem = s->fix64 != nullptr;
+    s->acc_fix = (unsigned long long*)(s->fix64 ? s->fix64 : dev_alloc(s, fix_bytes(s)));
+    if (s->acc_fix && setup_items(s, st) != OD_OK) free_sym(s);
+    (void)hipGetLastError();
+    if (s->acc_fix) HIPCHK(hipMemsetAsync(s->acc_fix, 0, fix_bytes(s), st));
+    HIPCHK(hipStreamSynchronize(st));
+    return OD_OK;
+}
+
 // The split's memory (up to a few hundred MB) is taken by the first step that
 // needs it, not when the system is created: hipMalloc and hipFree of more than
 // 64 MB take 0.3 ms, and milliseconds in a row, which a program that only
@@ -276,13 +298,10 @@ od_status outside_capture(hipStream_t stream, F setup)
 // its caller's takes it at creation, where the allocator may be called.
 od_status first_step_setup(od_system* s)
 {
+    if (s->prec == OD_PREC_FP64 && s->pa.ion_ion && !s->sym64_set)
+        return outside_capture(s->stream, [s](hipStream_t st) { return setup_sym64(s, st); });
     if (s->cut || !use_mesh(s) || s->mesh) return OD_OK;
     return outside_capture(s->stream, [s](hipStream_t st) { return setup_mesh(s, st); });
-}
-
-size_t fix_bytes(const od_system* s)
-{
-    return (s->prec == OD_PREC_FP32 ? 3 : 6) * (size_t)s->Npad * sizeof(unsigned long long);
 }
 
 // Sets up the symmetric pair sum: its fixed-point totals, and the work items
@@ -312,20 +331,6 @@ odk::Sym64 sym64_args(const od_system* s)
     const double n = 1.0 / (4.0 * kPI * s->pa.Cd);
     return {s->acc_fix, s->Npad, std::exp2(std::round(22.0 - (2.0 / 3.0) * std::log2(n))),
             0x1p62 / (double)(s->Npad / 64 + 64), &s->ctl->pair_bad};
-}
-
-// Totals and work items of an FP64 system's sum; where their memory is refused
-// it is summed one-sided.
-od_status setup_sym64(od_system* s, void* room)
-{
-    if (!s->pa.ion_ion) return OD_OK;
-    s->fix_in_mem = room != nullptr;
-    s->acc_fix = (unsigned long long*)(room ? room : dev_alloc(s, fix_bytes(s)));
-    if (s->acc_fix && setup_items(s, s->stream) != OD_OK) free_sym(s);
-    (void)hipGetLastError();
-    if (s->acc_fix) HIPCHK(hipMemsetAsync(s->acc_fix, 0, fix_bytes(s), s->stream));
-    HIPCHK(hipStreamSynchronize(s->stream));
-    return OD_OK;
 }
 
 // Chooses the all-pairs kernel for the system's kind: the symmetric one
@@ -929,8 +934,11 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         s->fa = c.fa;
     }
     if (st == OD_OK)
-        st = s->prec == OD_PREC_FP32 ? apply_pair_kind(s, roomy ? base + at[6] : nullptr)
-                                     : setup_sym64(s, roomy ? base + at[6] : nullptr);
+        st = apply_pair_kind(s, roomy ? base + at[6] : nullptr);
+    if (st == OD_OK && s->prec == OD_PREC_FP64) {
+        s->fix64 = roomy ? base + at[6] : nullptr;
+        if (s->custom_alloc) st = first_step_setup(s);
+    }
     if (st != OD_OK) {
         od_destroy(s);
         return st;
