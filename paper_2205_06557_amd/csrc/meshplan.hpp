@@ -159,7 +159,8 @@ inline bool mesh_dims(double R, double H, double rc, MeshArgs& a)
 // LDS), and a tenth of the bricks lie in the corners outside the cylinder.
 // More than one only where that should gain a tenth.  One against the blocks
 // chosen, us per pair sum: 336 / 281 at 40,960 ions (128 bricks), 405 / 382 at
-// 2^16 (144), 638 / 612 at 2^17 (300); 489 / 507 with four at 98,304 (275).
+// 2^16 (144), 638 / 597 at 2^17 (300; 612 with four to gather); 489 / 507 with four at
+// 98,304 (275).
 inline int mesh_parts(const MeshArgs& a, int most)
 {
     const double bricks = 0.9 * a.nbx * a.nby * a.nbz;
@@ -203,7 +204,7 @@ inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
     a.nby = (a.ncy + kMeshG - 1) / kMeshG;
     a.nbz = (a.nc[2] + kMeshBz - 1) / kMeshBz;
     a.parts = mesh_parts(a, 2);
-    a.gparts = mesh_parts(a, 4);
+    a.gparts = mesh_parts(a, 3);
     a.ng = std::max(a.n[0], a.n[2]) + 80;
 
     // Gaussians: force of L fitted to that of e^-r / r on [r_c, diag]
