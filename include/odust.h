@@ -249,10 +249,11 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * grid in 64 bits.  That is the same all-pairs sum: the far part is within
  * 1e-7 of the rms acceleration of the direct sum in 64 bits, below the FP32
  * rounding of the direct kernel's pair terms, and is bitwise reproducible too
- * (8x faster at 2^18 ions, 39x at 2^20).  Its memory, about 100 MB at 2^17 and
- * 500 MB at 2^20 ions, is taken by the first step, or at creation where the
- * system has an allocator of its own; where it is refused, and for the step
- * after od_set_state puts ions outside the domain, the direct sum is used.
+ * (2.6x faster at 2^16 ions, 14x at 2^18, 59x at 2^20).  Its memory, about
+ * 100 MB at 2^17 and 500 MB at 2^20 ions, is taken by the first step, or at
+ * creation where the system has an allocator of its own; where it is refused,
+ * and for the step after od_set_state puts ions outside the domain, the direct
+ * sum is used.
  * OD_PAIR_SYMMETRIC always sums every pair directly.
  * The symmetric kernel needs 24 bytes per ion of accumulators.  FP64 systems
  * have a sum of their own, which neither choice changes (each pair once too,

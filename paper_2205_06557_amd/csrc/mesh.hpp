@@ -604,7 +604,8 @@ __global__ void mesh_zero_kernel(MeshArgs m, float* near0)
 // Bound by FP32 issue (31 slots a pair), so what counts is how few pairs
 // beyond r_c are evaluated: 3.3 times the pairs within r_c with groups of 16
 // and boxes of 8, 5.8 with 64 and 16 and wider columns, whose sources could be
-// scalar loads: at 2^20 ions 2.9 ms with r_c = 0.39, where the wider search took 3.7 ms with 0.33.
+// scalar loads: at 2^20 ions 2.9 ms with r_c = 0.39, where the wider search
+// took 3.7 ms with 0.33; 1.86 ms with the present r_c of 0.29.
 constexpr int kMeshList = 64;       // boxes a wave lists per group in a round
 constexpr int kMeshCand = 64;       // candidate columns per group of a round
 
@@ -818,8 +819,9 @@ void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* _
     }
 }
 
-// Convolution scratch.  All 14 Gaussians at once where they fit: 2.09 against
-// 2.06 ms per step at 2^18 ions and 6.61 against 6.56 at 2^20 with 160 MB.
+// Convolution scratch: with 120, 200, 400 and 1,200 MB (fewer passes over the
+// 14 Gaussians) a pair sum took 1.15, 1.13, 1.11 and 1.11 ms at 2^18 ions, 5.18,
+// 4.40, 4.26 and 4.27 at 2^20.
 constexpr int kMeshScratchMb = 400;
 
 // Cuts buffers from an arena at `base` (null: only adds up their size).
