@@ -136,34 +136,52 @@ __device__ inline double rsq_f64(double x)
     return fma(y * e, fma(e, 0.375, 0.5), y);
 }
 
-// e^(-r) for r >= 0 (large r clamped, where the result is 0 in FP64):
-// Cody-Waite reduction r = n ln2 - f with ln 2 split into a 32-bit head
-// (n * head exact) and its remainder, |f| <= ln2 / 2, then the Taylor
-// polynomial of e^f to degree 13 (remainder below 1e-17) by Horner, scaled
-// by 2^n (measured on gfx950 within 1.3 ulp).
-__device__ inline double exp_neg_f64(double r)
+// 2^(j / 64), correctly rounded.
+__constant__ const double kExp2Tab[64] = {
+    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0,
+    0x1.0874518759bc8p+0, 0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0,
+    0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0, 0x1.172b83c7d517bp+0,
+    0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
+    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0,
+    0x1.2d285a6e4030bp+0, 0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0,
+    0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0, 0x1.3dea64c123422p+0,
+    0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
+    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0,
+    0x1.56f4736b527dap+0, 0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0,
+    0x1.6247eb03a5585p+0, 0x1.6623882552225p+0, 0x1.6a09e667f3bcdp+0,
+    0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
+    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0,
+    0x1.868d99b4492edp+0, 0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0,
+    0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0, 0x1.9c49182a3f090p+0,
+    0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0,
+    0x1.bcc1e904bc1d2p+0, 0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0,
+    0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0, 0x1.d5818dcfba487p+0,
+    0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
+    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0,
+    0x1.fa7c1819e90d8p+0,
+};
+
+// e^-r for 0 <= r, clamped at 700 (below 1e-304): r = -(n ln 2) / 64 + f with n
+// rounded by adding 1.5 * 2^52, ln 2 / 64 split into a 32-bit head (n * head
+// exact) and its remainder, |f| <= ln 2 / 128, 2^(n / 64) from the table (in
+// LDS) and its exponent, e^f - 1 to degree 5 (remainder below 4e-17).
+__device__ __forceinline__ double exp_neg_tab(double r, const double* __restrict__ tab)
 {
-    const double kLog2e = 1.4426950408889634;
-    const double kLn2Hi = 0.6931471803691238;         // ln 2 to 32 significant bits
-    const double kLn2Lo = 1.9082149292705877e-10;     // ln 2 - kLn2Hi
-    const double x = -fmin(r, 800.0);
-    const double n = rint(x * kLog2e);
-    const double f = fma(-n, kLn2Lo, fma(-n, kLn2Hi, x));
-    double p = 1.6059043836821613e-10;                // 1/13!
-    p = fma(p, f, 2.08767569878681e-09);              // 1/12!
-    p = fma(p, f, 2.505210838544172e-08);             // 1/11!
-    p = fma(p, f, 2.755731922398589e-07);             // 1/10!
-    p = fma(p, f, 2.7557319223985893e-06);            // 1/9!
-    p = fma(p, f, 2.48015873015873e-05);              // 1/8!
-    p = fma(p, f, 0.0001984126984126984);             // 1/7!
-    p = fma(p, f, 0.001388888888888889);              // 1/6!
-    p = fma(p, f, 0.008333333333333333);              // 1/5!
-    p = fma(p, f, 0.041666666666666664);              // 1/4!
-    p = fma(p, f, 0.16666666666666666);               // 1/3!
+    const double magic = 6755399441055744.0;
+    const double x = -fmin(r, 700.0);
+    const double t = fma(x, 92.33248261689366, magic);
+    const double n = t - magic;
+    const int k = (int)(unsigned int)__builtin_bit_cast(unsigned long long, t);
+    const double f = fma(n, -0x1.62e42fee00000p-7, fma(n, -0x1.a39ef35793c76p-39, x));
+    double p = fma(f, 1.0 / 120.0, 1.0 / 24.0);
+    p = fma(p, f, 1.0 / 6.0);
     p = fma(p, f, 0.5);
     p = fma(p, f, 1.0);
-    p = fma(p, f, 1.0);
-    return ldexp(p, (int)n);
+    const unsigned long long b = __builtin_bit_cast(unsigned long long, tab[k & 63]);
+    const int hi = (int)(b >> 32) + ((k & ~63) << 14);
+    const double s = __builtin_bit_cast(double, (unsigned long long)(unsigned int)hi << 32 | (unsigned int)b);
+    return fma(s * f, p, s);
 }
 
 // ---------------------------------------------------------------------------

@@ -1038,9 +1038,9 @@ __global__ __launch_bounds__(256) void init_kernel(T* __restrict__ xs, T* __rest
 // Bound by FP64 issue.  A block takes kConfRow nodes of one k and a slice of
 // the ions: an ion's loads and its distance from the node's axis serve all of
 // them, and the slices keep every SIMD busy (one node per block left each with
-// four waves).  The term costs 30 FP64 instructions (rsq_f64, exp_neg_f64)
-// instead of about 100 with the library's exp, sqrt and division: 476 -> 208 us
-// at 2^17 ions.  part[slice][node] receives the slice sums, which the host
+// four waves).  The term costs 23 FP64 instructions (rsq_f64, exp_neg_tab); at
+// 2^17 ions 187 us, 208 with a polynomial exponential (30 instructions), 476
+// with one node per block and the library's exp, sqrt and division (about 100).  part[slice][node] receives the slice sums, which the host
 // adds in slice order.  Grid: ((nx + 1) (nz + 1) / kConfRow, slices).
 constexpr int kConfRow = 3;
 
@@ -1050,7 +1050,10 @@ __global__ __launch_bounds__(256) void conf_grid_kernel(const T* __restrict__ X,
                                                         const T* __restrict__ Z, int N, double R, double Hh,
                                                         int nx, int nz, double* __restrict__ part)
 {
+    __shared__ double tab[64];
     __shared__ double red[4][kConfRow];
+    if (threadIdx.x < 64) tab[threadIdx.x] = kExp2Tab[threadIdx.x];
+    __syncthreads();
     const int g0 = blockIdx.x * kConfRow, nodes = gridDim.x * kConfRow;
     const double gx = R * (double)(g0 / (nz + 1)) / (double)nx;
     double gz[kConfRow], s[kConfRow];
@@ -1067,7 +1070,7 @@ __global__ __launch_bounds__(256) void conf_grid_kernel(const T* __restrict__ X,
             const double dz = z - gz[q];
             const double d2 = fma(dz, dz, h2);
             const double ri = rsq_f64(d2);
-            const double t = exp_neg_f64(d2 * ri) * ri;
+            const double t = exp_neg_tab(d2 * ri, tab) * ri;
             s[q] += d2 > 0.0 ? t : 0.0;
         }
     }

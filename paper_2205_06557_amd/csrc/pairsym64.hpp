@@ -17,54 +17,6 @@
 
 namespace odk {
 
-// 2^(j / 64), correctly rounded.
-__constant__ const double kExp2Tab[64] = {
-    0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0,
-    0x1.0874518759bc8p+0, 0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0,
-    0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0, 0x1.172b83c7d517bp+0,
-    0x1.1a35beb6fcb75p+0, 0x1.1d4873168b9aap+0, 0x1.2063b88628cd6p+0,
-    0x1.2387a6e756238p+0, 0x1.26b4565e27cddp+0, 0x1.29e9df51fdee1p+0,
-    0x1.2d285a6e4030bp+0, 0x1.306fe0a31b715p+0, 0x1.33c08b26416ffp+0,
-    0x1.371a7373aa9cbp+0, 0x1.3a7db34e59ff7p+0, 0x1.3dea64c123422p+0,
-    0x1.4160a21f72e2ap+0, 0x1.44e086061892dp+0, 0x1.486a2b5c13cd0p+0,
-    0x1.4bfdad5362a27p+0, 0x1.4f9b2769d2ca7p+0, 0x1.5342b569d4f82p+0,
-    0x1.56f4736b527dap+0, 0x1.5ab07dd485429p+0, 0x1.5e76f15ad2148p+0,
-    0x1.6247eb03a5585p+0, 0x1.6623882552225p+0, 0x1.6a09e667f3bcdp+0,
-    0x1.6dfb23c651a2fp+0, 0x1.71f75e8ec5f74p+0, 0x1.75feb564267c9p+0,
-    0x1.7a11473eb0187p+0, 0x1.7e2f336cf4e62p+0, 0x1.82589994cce13p+0,
-    0x1.868d99b4492edp+0, 0x1.8ace5422aa0dbp+0, 0x1.8f1ae99157736p+0,
-    0x1.93737b0cdc5e5p+0, 0x1.97d829fde4e50p+0, 0x1.9c49182a3f090p+0,
-    0x1.a0c667b5de565p+0, 0x1.a5503b23e255dp+0, 0x1.a9e6b5579fdbfp+0,
-    0x1.ae89f995ad3adp+0, 0x1.b33a2b84f15fbp+0, 0x1.b7f76f2fb5e47p+0,
-    0x1.bcc1e904bc1d2p+0, 0x1.c199bdd85529cp+0, 0x1.c67f12e57d14bp+0,
-    0x1.cb720dcef9069p+0, 0x1.d072d4a07897cp+0, 0x1.d5818dcfba487p+0,
-    0x1.da9e603db3285p+0, 0x1.dfc97337b9b5fp+0, 0x1.e502ee78b3ff6p+0,
-    0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0,
-    0x1.fa7c1819e90d8p+0,
-};
-
-// e^-r for 0 <= r, clamped at 700 (below 1e-304): r = -(n ln 2) / 64 + f with n
-// rounded by adding 1.5 * 2^52, ln 2 / 64 split into a 32-bit head (n * head
-// exact) and its remainder, |f| <= ln 2 / 128, 2^(n / 64) from the table (in
-// LDS) and its exponent, e^f - 1 to degree 5 (remainder below 4e-17).
-__device__ __forceinline__ double exp_neg_tab(double r, const double* __restrict__ tab)
-{
-    const double magic = 6755399441055744.0;
-    const double x = -fmin(r, 700.0);
-    const double t = fma(x, 92.33248261689366, magic);
-    const double n = t - magic;
-    const int k = (int)(unsigned int)__builtin_bit_cast(unsigned long long, t);
-    const double f = fma(n, -0x1.62e42fee00000p-7, fma(n, -0x1.a39ef35793c76p-39, x));
-    double p = fma(f, 1.0 / 120.0, 1.0 / 24.0);
-    p = fma(p, f, 1.0 / 6.0);
-    p = fma(p, f, 0.5);
-    p = fma(p, f, 1.0);
-    const unsigned long long b = __builtin_bit_cast(unsigned long long, tab[k & 63]);
-    const int hi = (int)(b >> 32) + ((k & ~63) << 14);
-    const double s = __builtin_bit_cast(double, (unsigned long long)(unsigned int)hi << 32 | (unsigned int)b);
-    return fma(s * f, p, s);
-}
-
 // (1 + r) e^-r / r^3 for the difference d.
 __device__ __forceinline__ double sym64_f(double dx, double dy, double dz, const double* __restrict__ tab)
 {
@@ -224,16 +176,12 @@ __global__ __launch_bounds__(256) void pair_sym64_kernel(const double* __restric
 // is dropped.
 template <int TJ, bool Self>
 __device__ __forceinline__ void f64_tile(const double4* __restrict__ tile, double xi, double yi, double zi,
-                                         int self, double& sx, double& sy, double& sz)
+                                         int self, const double* __restrict__ tab, double& sx, double& sy, double& sz)
 {
     for (int k = 0; k < TJ; ++k) {
         const double4 q = tile[k];
         const double dx = xi - q.x, dy = yi - q.y, dz = zi - q.z;
-        const double r2 = fma(dx, dx, fma(dy, dy, dz * dz));
-        const double ri = rsq_f64(r2);
-        const double r = r2 * ri;
-        const double e = exp_neg_f64(r);
-        double f = fma(r, e, e) * (ri * ri * ri);         // (1 + r) e^-r / r^3
+        double f = sym64_f(dx, dy, dz, tab);
         if (Self) f = (k == self) ? 0.0 : f;
         sx += f * dx;
         sy += f * dy;
@@ -252,6 +200,7 @@ __global__ __launch_bounds__(BLOCK) void pair_forces_f64(const double* __restric
                                                          Ctl* __restrict__ ctl)
 {
     static_assert(BLOCK == TJ, "the block's own tile is the one source tile holding its targets");
+    __shared__ double tab[64];
     __shared__ double4 tile[TJ];
     __shared__ double red[BLOCK / 64][kMaxDust][3];
     const int Npad = p.Npad;
@@ -273,6 +222,7 @@ __global__ __launch_bounds__(BLOCK) void pair_forces_f64(const double* __restric
         sy = t[1];
         sz = t[2];
     } else if (p.ion_ion) {
+        if (threadIdx.x < 64) tab[threadIdx.x] = kExp2Tab[threadIdx.x];
         for (int j0 = 0; j0 < Npad; j0 += TJ) {
             __syncthreads();
             for (int t = threadIdx.x; t < TJ; t += BLOCK) {
@@ -282,9 +232,9 @@ __global__ __launch_bounds__(BLOCK) void pair_forces_f64(const double* __restric
             }
             __syncthreads();
             if (j0 == i0)      // the block's own tile holds the self-pair
-                f64_tile<TJ, true>(tile, xi, yi, zi, threadIdx.x, sx, sy, sz);
+                f64_tile<TJ, true>(tile, xi, yi, zi, threadIdx.x, tab, sx, sy, sz);
             else
-                f64_tile<TJ, false>(tile, xi, yi, zi, threadIdx.x, sx, sy, sz);
+                f64_tile<TJ, false>(tile, xi, yi, zi, threadIdx.x, tab, sx, sy, sz);
         }
     }
     if (s.fix)
