@@ -35,7 +35,7 @@ namespace odk {
 // a step (mesh_scratch), which systems that step one after another share.
 struct MeshBufs {
     int* count;            // own: [bins] ions per bin; zero between steps
-    double* green;         // own: [M][ng] Green's tables
+    double* green;         // own: [m.M][ng] Green's tables
     float* near0;          // own: constant term of the near polynomial (mesh_zero_kernel)
     int* key;              // [N] sort bin of each ion
     int* arr;              // [N] arrival number in the bin
@@ -840,7 +840,7 @@ inline size_t mesh_own(const MeshArgs& m, char* base, MeshBufs& b)
 {
     MeshArena a{base};
     a.take(&b.count, (size_t)m.ncx * m.ncy * m.nzb * 4);
-    a.take(&b.green, (size_t)kMeshM * m.ng * 8);
+    a.take(&b.green, (size_t)m.M * m.ng * 8);
     a.take(&b.near0, 4);
     return a.at;
 }
@@ -861,9 +861,9 @@ inline size_t mesh_scratch(const MeshArgs& m, char* base, MeshBufs& b)
     a.take(&b.q, v * 8);
     a.take(&b.phi, v * 8);
     // convolution scratch: as many Gaussians at a time as fit
-    b.mc = (int)std::min<size_t>(kMeshM, std::max<size_t>(1, ((size_t)kMeshScratchMb << 20) / (16 * v)));
-    const int passes = (kMeshM + b.mc - 1) / b.mc;
-    b.mc = (kMeshM + passes - 1) / passes;
+    b.mc = (int)std::min<size_t>(m.M, std::max<size_t>(1, ((size_t)kMeshScratchMb << 20) / (16 * v)));
+    const int passes = (m.M + b.mc - 1) / b.mc;
+    b.mc = (m.M + passes - 1) / passes;
     const size_t conv = 2 * (size_t)b.mc * v * 8, brick = (size_t)m.nbx * m.nby * m.nbz * m.parts * kMeshNodes * 8;
     a.take(&b.t1, std::max(conv, brick));
     b.t2 = b.t1 ? b.t1 + (size_t)b.mc * v : nullptr;
@@ -881,7 +881,7 @@ inline hipError_t mesh_start(const MeshArgs& m, const MeshBufs& b, hipStream_t s
     if (e == hipSuccess) e = hipMemsetAsync(b.count, 0, (size_t)m.ncx * m.ncy * m.nzb * 4, st);
     if (e != hipSuccess) return e;
     mesh_zero_kernel<<<1, 64, 0, st>>>(m, b.near0);
-    mesh_green_kernel<<<dim3(kMeshM, (m.ng + 63) / 64), 256, 0, st>>>(m, mesh_i0(kMeshBeta), b.green);
+    mesh_green_kernel<<<dim3(m.M, (m.ng + 63) / 64), 256, 0, st>>>(m, mesh_i0(kMeshBeta), b.green);
     return hipGetLastError();
 }
 
@@ -902,8 +902,8 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
     constexpr size_t lds = kMeshNodes * 8;
     mesh_spread_kernel<<<dim3(bricks, m.parts), kMeshThreads, lds, st>>>(m, b);
     mesh_sum_kernel<<<(unsigned)((v + 255) / 256), 256, 0, st>>>(m, b);
-    for (int m0 = 0; m0 < kMeshM; m0 += b.mc) {
-        const int mc = std::min(b.mc, kMeshM - m0);
+    for (int m0 = 0; m0 < m.M; m0 += b.mc) {
+        const int mc = std::min(b.mc, m.M - m0);
         mesh_conv<0>(m, b, b.q, b.t1, m0, mc, st);
         mesh_conv<1>(m, b, b.t1, b.t2, m0, mc, st);
         mesh_conv<2>(m, b, b.t2, b.phi, m0, mc, st);

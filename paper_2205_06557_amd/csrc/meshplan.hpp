@@ -11,9 +11,10 @@
 // axis, each Gaussian applied as three one-dimensional convolutions (a
 // Gaussian is a product over the axes) with the window's transform divided
 // out, and the potential's gradient taken with the window's derivative.
-// With r_c / h = 7.5 cells and window shape 22 the far part is within 1e-7 of
+// With r_c / h = 7.5 cells and window shape 22 the grid adds less than 1e-7 of
 // the rms acceleration (2^14 .. 2^20 ions, measured against 64-bit direct
-// sums), below the FP32 rounding of the pair terms.
+// sums); the fit adds 5e-8 to 2.3e-7, growing with diag / r_c at a given number
+// of Gaussians (mesh_plan).
 #pragma once
 
 #include <algorithm>
@@ -23,7 +24,9 @@
 namespace odk {
 
 constexpr int kMeshP = 10;          // window nodes per axis
-constexpr int kMeshM = 14;          // Gaussians
+constexpr int kMeshM = 20;          // Gaussians at most ...
+constexpr int kMeshMinM = 14;       // ... and at least
+constexpr double kMeshFit = 3.2e-6; // |F - F_L| r r_c that a fit may leave beyond r_c
 constexpr int kMeshWDeg = 18;       // degree of the window polynomial in 1 - 2 z^2
 constexpr int kMeshNearDeg = 12;    // degree of the near part's polynomial in 1 - 2 r^2 / r_c^2
 constexpr double kMeshBeta = 22.0;  // Kaiser-Bessel shape
@@ -52,7 +55,8 @@ struct MeshArgs {
     float rc, rc2, irc2, cw;        // near radius, its square, -2 / rc^2; column width
     float near[kMeshNearDeg + 1];   // f_L(r) = -L'/r in powers of 1 - 2 r^2 / r_c^2
     double win[kMeshWDeg + 1];      // window in powers of s = 1 - 2 z^2
-    double w[kMeshM], th[kMeshM];   // weights; t_m h
+    int M;                          // Gaussians in use
+    double w[kMeshM], th[kMeshM];   // weights; t_m h (zero beyond M)
 };
 
 // Least squares of an m x n system (column major A, overwritten) by
@@ -124,6 +128,45 @@ inline double mesh_i0(double x)
         if (t < 1e-18 * s) break;
     }
     return s;
+}
+
+// M Gaussians w e^(-t^2 r^2) whose force is fitted to that of e^-r / r on
+// [r_c, diag].  Returns the largest |F - F_L| r r_c there (1 at
+// r_c = r << 1 for F itself), infinity if the fit failed.
+inline double mesh_fit(double rc, double diag, int M, double* t, double* w)
+{
+    constexpr int m = 160;
+    double t2[kMeshM];
+    const double t0 = std::max(0.2, 0.6 / diag), t1 = kMeshTop / rc;
+    for (int j = 0; j < M; ++j) {
+        t[j] = t0 * std::pow(t1 / t0, (double)j / (M - 1));
+        t2[j] = t[j] * t[j];
+    }
+    std::vector<double> A((size_t)m * M), rhs(m), sc(M, 0.0);
+    for (int i = 0; i < m; ++i) {
+        const double r = rc * std::pow(diag * 1.01 / rc, (double)i / (m - 1));
+        // weighted by r; r_c itself heavily, because pairs a little beyond it
+        // are evaluated at r_c, where the near part has to vanish
+        const double wt = i == 0 ? 1.0e4 : 1.0;
+        rhs[i] = wt * (1.0 + r) * std::exp(-r) / r;
+        for (int j = 0; j < M; ++j) A[(size_t)j * m + i] = wt * 2.0 * t2[j] * r * r * std::exp(-t2[j] * r * r);
+    }
+    for (int j = 0; j < M; ++j) {
+        for (int i = 0; i < m; ++i) sc[j] = std::max(sc[j], std::fabs(A[(size_t)j * m + i]));
+        for (int i = 0; i < m; ++i) A[(size_t)j * m + i] /= sc[j];
+    }
+    mesh_lstsq(A, rhs, m, M, w);
+    double worst = 0.0;
+    for (int j = 0; j < M; ++j) w[j] /= sc[j];
+    for (int i = 0; i < m; ++i) {
+        const double r = rc * std::pow(diag / rc, (double)i / (m - 1));
+        double f = -(1.0 + r) * std::exp(-r) / (r * r * r);
+        for (int j = 0; j < M; ++j) f += w[j] * 2.0 * t2[j] * std::exp(-t2[j] * r * r);
+        const double e = std::fabs(f) * r * r * rc;
+        if (!std::isfinite(e)) return HUGE_VAL;
+        worst = std::max(worst, e);
+    }
+    return worst;
 }
 
 // Grid and columns for a near radius; false if the domain is outside what the
@@ -207,46 +250,27 @@ inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
     a.gparts = mesh_parts(a, 3);
     a.ng = std::max(a.n[0], a.n[2]) + 80;
 
-    // Gaussians: force of L fitted to that of e^-r / r on [r_c, diag]
-    constexpr int m = 160, M = kMeshM;
-    const double t0 = std::max(0.2, 0.6 / diag), t1 = kMeshTop / rc;
-    double t2[M];
-    for (int j = 0; j < M; ++j) {
-        const double t = t0 * std::pow(t1 / t0, (double)j / (M - 1));
-        t2[j] = t * t;
-        a.th[j] = t * a.h;
-    }
-    std::vector<double> A((size_t)m * M), rhs(m), sc(M, 0.0);
-    for (int i = 0; i < m; ++i) {
-        const double r = rc * std::pow(diag * 1.01 / rc, (double)i / (m - 1));
-        // weighted by r; r_c itself heavily, because pairs a little beyond it
-        // are evaluated at r_c, where the near part has to vanish
-        const double wt = i == 0 ? 1.0e4 : 1.0;
-        rhs[i] = wt * (1.0 + r) * std::exp(-r) / r;
-        for (int j = 0; j < M; ++j) A[(size_t)j * m + i] = wt * 2.0 * t2[j] * r * r * std::exp(-t2[j] * r * r);
-    }
-    for (int j = 0; j < M; ++j) {
-        for (int i = 0; i < m; ++i) sc[j] = std::max(sc[j], std::fabs(A[(size_t)j * m + i]));
-        for (int i = 0; i < m; ++i) A[(size_t)j * m + i] /= sc[j];
-    }
-    mesh_lstsq(A, rhs, m, M, a.w);
-    for (int j = 0; j < M; ++j) {
-        a.w[j] /= sc[j];
-        if (!std::isfinite(a.w[j])) return false;
-    }
-    // a domain whose force the Gaussians do not reproduce to this keeps the direct sum
-    for (int i = 0; i < m; ++i) {
-        const double r = rc * std::pow(diag / rc, (double)i / (m - 1));
-        double f = -(1.0 + r) * std::exp(-r) / (r * r * r);
-        for (int j = 0; j < M; ++j) f += a.w[j] * 2.0 * t2[j] * std::exp(-t2[j] * r * r);
-        if (!(std::fabs(f) * r * r * rc < 2.5e-5)) return false;
+    // As few Gaussians as fit to kMeshFit.  The fit's error of the acceleration,
+    // relative to the rms over uniform ions, is then 4e-8 to 2.3e-7, below the
+    // 3e-7 of the direct FP32 sum; 14 throughout left 1.3e-7 at 2^20 ions,
+    // 3.4e-7 at 2^21, 9.8e-7 at 2^22 and 2.3e-6 at 2^23 (R = 3, H = 6 to 8),
+    // against 1.3e-7, 1.1e-7 (15), 1.2e-7 (16) and 9.8e-8 (17).  A domain that
+    // the most do not fit to it keeps the direct sum.
+    double t[kMeshM];
+    bool fits = false;
+    for (a.M = kMeshMinM; a.M <= kMeshM && !fits; ++a.M) fits = mesh_fit(rc, diag, a.M, t, a.w) < kMeshFit;
+    --a.M;
+    if (!fits) return false;
+    for (int j = 0; j < kMeshM; ++j) {
+        a.th[j] = j < a.M ? t[j] * a.h : 0.0;
+        if (j >= a.M) a.w[j] = 0.0;
     }
     // near part: f_L in powers of s = 1 - 2 r^2 / r_c^2
     std::vector<double> mono;
     mesh_cheb([&](double s) {
         const double y = 0.5 * (1.0 - s) * rc * rc;
         double f = 0.0;
-        for (int j = 0; j < M; ++j) f += a.w[j] * 2.0 * t2[j] * std::exp(-t2[j] * y);
+        for (int j = 0; j < a.M; ++j) f += a.w[j] * 2.0 * (t[j] * t[j]) * std::exp(-(t[j] * t[j]) * y);
         return f;
     }, kMeshNearDeg, mono);
     for (int k = 0; k <= kMeshNearDeg; ++k) a.near[k] = (float)mono[k];
