@@ -252,9 +252,11 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * most 2.3e-7 at every size), where the direct FP32 kernel has 1.8e-7 at 2^18
  * and 3.0e-7 at 2^20 (2.6x faster at 2^16 ions, 14x at 2^18, 59x at 2^20).  Its memory, about
  * 100 MB at 2^17 and 500 MB at 2^20 ions, is taken by the first step, or at
- * creation where the system has an allocator of its own; where it is refused,
- * and for the step after od_set_state puts ions outside the domain, the direct
- * sum is used.
+ * creation where the system has an allocator of its own; where it is refused
+ * the direct sum is used.  It is used too for a step that begins with ions
+ * outside the domain, where od_set_state may put them; the device finds that
+ * out, so a step that the caller captured in a graph of its own stays right
+ * when it is replayed after od_set_state.
  * OD_PAIR_SYMMETRIC always sums every pair directly.
  * The symmetric kernel needs 24 bytes per ion of accumulators.  FP64 systems
  * have a sum of their own, which neither choice changes (each pair once too,

@@ -22,20 +22,40 @@
 //   mesh_gather_kernel   far acceleration of every ion, from bricks in LDS
 //   mesh_near_kernel     near pairs; totals to the fixed-point planes that the
 //                        step's tail reads
+//   mesh_direct_kernel   the direct sum instead, where the ions do not suit the
+//                        grid: some lie outside the domain (od_set_state may
+//                        put them there; they leave it in that step)
+// Which of the two it is, mesh_bin_kernel and mesh_scan_kernel find out on the
+// device, so that it holds for every replay of a captured step too; the
+// kernels of the other return at once.
 // Every sum has a fixed order or is an integer sum: results are reproducible
 // bit for bit.
 #pragma once
 
 #include "kernels.hpp"
 #include "meshplan.hpp"
+#include "pairsym.hpp"
 
 namespace odk {
+
+// One system's direct sum, for the steps that call for it.
+struct MeshDirect {
+    const long long* cost;      // MeshBufs::cost
+    const float* x;             // positions and totals, their planes equally far apart
+    unsigned long long* fix;
+    SymRuns runs;
+    int N;
+    double scale;
+    int* status;
+};
 
 // Device buffers of one system's split: its own (mesh_own) and the scratch of
 // a step (mesh_scratch), which systems that step one after another share.
 struct MeshBufs {
     int* count;            // own: [bins] ions per bin; zero between steps
     double* green;         // own: [m.M][ng] Green's tables
+    long long* cost;       // own: [2] above zero: this step is summed directly; the next one's, while it is found out
+    MeshDirect* direct;    // own: see mesh_direct_kernel
     float* near0;          // own: constant term of the near polynomial (mesh_zero_kernel)
     int* key;              // [N] sort bin of each ion
     int* arr;              // [N] arrival number in the bin
@@ -64,25 +84,38 @@ __device__ __forceinline__ int mesh_zbin(double z, const MeshArgs& m)
     return (int)fmin(fmax(floor((z + m.Hh) * (m.inv_h * kMeshZsub)), 0.0), (double)(m.nzb - 1));
 }
 
-// Sort bin of every ion; also marks every slot empty.
+constexpr long long kMeshNever = 1ll << 62;
+
+// Asked where a kernel waits for other loads anyway.
+__device__ __forceinline__ bool mesh_skip(const long long* cost) { return cost[0] > 0; }
+
+// Sort bin of every ion; also marks every slot empty, and whether ions lie
+// outside the domain (by more than the rounding of one on its surface).
 __global__ __launch_bounds__(256) void mesh_bin_kernel(const float* __restrict__ x, long long plane, MeshArgs m,
                                                        MeshBufs b)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < m.cap) b.temp[i] = -1;
     if (i >= m.N) return;
-    const int cx = mesh_cell(x[i], -m.R, m.inv_h, m.nc[0]) / kMeshKx;
-    const int cy = mesh_cell(x[plane + i], -m.R, m.inv_h, m.nc[1]) / kMeshKx;
-    const int key = (cy * m.ncx + cx) * m.nzb + mesh_zbin(x[2 * plane + i], m);
+    const double px = x[i], py = x[plane + i], pz = x[2 * plane + i];
+    if (fmax(fabs(px), fabs(py)) > m.R * (1.0 + 1e-6) || fabs(pz) > m.Hh * (1.0 + 1e-6)) b.cost[1] = kMeshNever;
+    const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]) / kMeshKx;
+    const int cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]) / kMeshKx;
+    const int key = (cy * m.ncx + cx) * m.nzb + mesh_zbin(pz, m);
     b.key[i] = key;
     b.arr[i] = atomicAdd(&b.count[key], 1);
 }
 
 // One block per column: bin starts relative to the column; clears the counts.
+// Block 0 passes the step's mark on.
 __global__ __launch_bounds__(256) void mesh_scan_kernel(MeshArgs m, MeshBufs b)
 {
     __shared__ int wsum[4];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        b.cost[0] = b.cost[1];
+        b.cost[1] = 0;
+    }
     int* cnt = b.count + (long long)blockIdx.x * m.nzb;
     int* rel = b.rel + (long long)blockIdx.x * (m.nzb + 1);
     int carry = 0;
@@ -158,7 +191,7 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
                                                          MeshBufs b)
 {
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= b.col[m.ncx * m.ncy]) return;
+    if (mesh_skip(b.cost) | (t >= b.col[m.ncx * m.ncy])) return;
     const int i = b.temp[t];
     if (i < 0) {
         b.idx[t] = -1;
@@ -179,7 +212,7 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
 __global__ __launch_bounds__(256) void mesh_box_kernel(MeshArgs m, MeshBufs b)
 {
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (t >= b.col[m.ncx * m.ncy]) return;     // a multiple of 16
+    if (mesh_skip(b.cost) | (t >= b.col[m.ncx * m.ncy])) return;     // a multiple of 16
     const bool live = b.idx[t] >= 0;
     const int ns = m.cap / kMeshSub;
     const float4 p = b.s[t];
@@ -265,8 +298,10 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_spread_kernel(MeshArgs m, M
 {
     extern __shared__ unsigned long long grid[];
     __shared__ double wt[kMeshThreads / 64][16][3][16];
+    const bool skip = mesh_skip(b.cost);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c16 = lane & 15, q = lane >> 4;
     for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) grid[k] = 0ull;
+    if (skip) return;
     __syncthreads();
     const int waves = kMeshThreads / 64;
     for (int k = blockIdx.y * waves + wv; k < kMeshG * kMeshG; k += gridDim.y * waves) {
@@ -395,10 +430,12 @@ __global__ __launch_bounds__(256) void mesh_green_kernel(MeshArgs m, double i0_b
 template <int AXIS, int NT>
 __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double* __restrict__ in,
                                                         double* __restrict__ out,
-                                                        const double* __restrict__ green, int m0, int mc, int add)
+                                                        const double* __restrict__ green, const long long* cost,
+                                                        int m0, int mc, int add)
 {
     typedef double d4 __attribute__((ext_vector_type(4)));
     extern __shared__ double tab[];
+    const bool skip = mesh_skip(cost);
     const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
     const int len = AXIS == 0 ? nx : AXIS == 1 ? ny : nz, half = (len + 1) / 2;
     const int lines = AXIS == 0 ? ny * nz : AXIS == 1 ? nx * nz : nx * ny;
@@ -418,6 +455,7 @@ __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double
         const double w = AXIS == 2 ? m.w[m0 + g] : 1.0;
         __syncthreads();
         for (int k = threadIdx.x; k < m.ng; k += 256) tab[k] = 0.5 * w * green[(long long)(m0 + g) * m.ng + k];
+        if (skip) return;
         __syncthreads();
         const double* src = in + (AXIS == 0 ? 0 : g * vol) + base;
         for (int k0 = 0; k0 < half; k0 += 16) {
@@ -468,11 +506,11 @@ inline void mesh_conv(const MeshArgs& m, const MeshBufs& b, const double* in, do
     const int nt = (long long)gx * 4 * gz * ((tiles + 2) / 3) < 4096 ? 1 : tiles % 3 == 0 || tiles > 4 ? 3 : 2;
     const dim3 grid(gx, (tiles + nt - 1) / nt, gz);
     if (nt == 1)
-        mesh_conv_kernel<AXIS, 1><<<grid, 256, lds, st>>>(m, in, out, b.green, m0, mc, m0 > 0);
+        mesh_conv_kernel<AXIS, 1><<<grid, 256, lds, st>>>(m, in, out, b.green, b.cost, m0, mc, m0 > 0);
     else if (nt == 2)
-        mesh_conv_kernel<AXIS, 2><<<grid, 256, lds, st>>>(m, in, out, b.green, m0, mc, m0 > 0);
+        mesh_conv_kernel<AXIS, 2><<<grid, 256, lds, st>>>(m, in, out, b.green, b.cost, m0, mc, m0 > 0);
     else
-        mesh_conv_kernel<AXIS, 3><<<grid, 256, lds, st>>>(m, in, out, b.green, m0, mc, m0 > 0);
+        mesh_conv_kernel<AXIS, 3><<<grid, 256, lds, st>>>(m, in, out, b.green, b.cost, m0, mc, m0 > 0);
 }
 
 // Far part of every ion's raw pair sum, minus the gradient of the gridded
@@ -487,6 +525,7 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_gather_kernel(MeshArgs m, M
 {
     extern __shared__ double node[];
     __shared__ int start[kMeshG * kMeshG], pre[kMeshG * kMeshG + 1];
+    const bool skip = mesh_skip(b.cost);
     const int x0 = blockIdx.x % m.nbx * kMeshG * kMeshKx, y0 = blockIdx.x / m.nbx % m.nby * kMeshG * kMeshKx,
               z0 = blockIdx.x / (m.nbx * m.nby) * kMeshBz;
     if (threadIdx.x < kMeshG * kMeshG) {
@@ -495,6 +534,7 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_gather_kernel(MeshArgs m, M
         pre[threadIdx.x + 1] = c.s1 - c.s0;
     }
     if (threadIdx.x == 0) pre[0] = 0;
+    if (skip) return;
     __syncthreads();
     if (threadIdx.x == 0)
         for (int c = 0; c < kMeshG * kMeshG; ++c) pre[c + 1] += pre[c];
@@ -613,7 +653,7 @@ template <int S>
 __global__ __launch_bounds__(64 * S) __attribute__((amdgpu_waves_per_eu(6, 8)))
 void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* __restrict__ box,
                       const int* __restrict__ rel_, const int* __restrict__ col, const int* __restrict__ idx,
-                      const double* __restrict__ far, const float* __restrict__ near0_,
+                      const double* __restrict__ far, const float* __restrict__ near0_, const long long* cost,
                       unsigned long long* __restrict__ fix, long long fstride, double scale, int* status)
 {
     __shared__ int seg[S][4][kMeshList];            // boxes listed by each wave
@@ -623,11 +663,12 @@ void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* _
     __shared__ int2 cand[4][kMeshCand];
     __shared__ float4 src[S][64];
     __shared__ double part[S][3][64];
+    const bool skip = mesh_skip(cost);
     const int total = col[m.ncx * m.ncy];
     // consecutive tiles share sources: give each of the 8 XCDs a run of them
     const int tiles = (total + 63) / 64, per = (tiles + 7) / 8;
     const int tile = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || tile >= tiles) return;
+    if (skip | ((int)(blockIdx.x >> 3) >= per) | (tile >= tiles)) return;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int q = lane >> 4, l16 = lane & 15;
     const int slot = tile * 64 + lane;
@@ -819,6 +860,33 @@ void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* _
     }
 }
 
+// Direct sums of the systems whose step calls for it, as pair_sym_kernel has
+// them (the same items, so the same totals).  A launch of one round of blocks
+// that take the items in turn: every other step pays for it with 2 to 5 us (312
+// -> 317 us per step at 40,960 ions, 424 -> 426 at 2^16, 619 -> 621 at 2^17).
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kSymWaves, 8)))
+void mesh_direct_kernel(const MeshDirect* __restrict__ table, int systems, long long plane)
+{
+    __shared__ float4 src[4][128];
+    __shared__ float jpart[4][3][BLOCK];
+    for (int k = 0; k < systems; ++k) {
+        if (!mesh_skip(table[k].cost)) continue;
+        const MeshDirect d = table[k];
+        SymPlace at{0, 0};
+        SymItem it;
+        for (int n = blockIdx.x; sym_item_at(d.runs, n, at, it); n += gridDim.x)
+            sym_dispatch<BLOCK>(d.x, d.x + plane, d.x + 2 * plane, d.N, it.rows, it.I, it.J0, it.J1, 0, 4, d.fix,
+                                plane, d.scale, d.status, src, jpart, PlainPair{});
+    }
+}
+
+inline hipError_t mesh_direct_launch(const MeshDirect* table, int systems, long long plane, int cus, hipStream_t st)
+{
+    mesh_direct_kernel<256><<<cus * kSymWaves, 256, 0, st>>>(table, systems, plane);
+    return hipGetLastError();
+}
+
 // Convolution scratch: with 120, 200, 400 and 1,200 MB (fewer passes over the
 // 14 Gaussians) a pair sum took 1.15, 1.13, 1.11 and 1.11 ms at 2^18 ions, 5.18,
 // 4.40, 4.26 and 4.27 at 2^20.
@@ -842,6 +910,8 @@ inline size_t mesh_own(const MeshArgs& m, char* base, MeshBufs& b)
     a.take(&b.count, (size_t)m.ncx * m.ncy * m.nzb * 4);
     a.take(&b.green, (size_t)m.M * m.ng * 8);
     a.take(&b.near0, 4);
+    a.take(&b.cost, 2 * sizeof(long long));
+    a.take(&b.direct, sizeof(MeshDirect));
     return a.at;
 }
 
@@ -871,7 +941,7 @@ inline size_t mesh_scratch(const MeshArgs& m, char* base, MeshBufs& b)
     return a.at;
 }
 
-// Clears the bin counts and computes the Green's tables (once per system).
+// Clears the bin counts and marks and computes the Green's tables (once per system).
 inline hipError_t mesh_start(const MeshArgs& m, const MeshBufs& b, hipStream_t st)
 {
     constexpr int lds = kMeshNodes * 8;
@@ -879,6 +949,7 @@ inline hipError_t mesh_start(const MeshArgs& m, const MeshBufs& b, hipStream_t s
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void*)mesh_gather_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e == hipSuccess) e = hipMemsetAsync(b.count, 0, (size_t)m.ncx * m.ncy * m.nzb * 4, st);
+    if (e == hipSuccess) e = hipMemsetAsync(b.cost, 0, 2 * sizeof(long long), st);
     if (e != hipSuccess) return e;
     mesh_zero_kernel<<<1, 64, 0, st>>>(m, b.near0);
     mesh_green_kernel<<<dim3(m.M, (m.ng + 63) / 64), 256, 0, st>>>(m, mesh_i0(kMeshBeta), b.green);
@@ -911,11 +982,11 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
     mesh_gather_kernel<<<dim3(bricks, m.gparts), kMeshThreads, lds, st>>>(m, b);
     const int tiles = (m.cap / 64 + 7) / 8 * 8;
     if (m.cap / 64 >= 8192)
-        mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, fix, fstride,
-                                                   scale, status);
+        mesh_near_kernel<4><<<tiles, 256, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, b.cost, fix,
+                                                   fstride, scale, status);
     else
-        mesh_near_kernel<8><<<tiles, 512, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, fix, fstride,
-                                                   scale, status);
+        mesh_near_kernel<8><<<tiles, 512, 0, st>>>(m, b.s, b.box, b.rel, b.col, b.idx, b.far, b.near0, b.cost, fix,
+                                                   fstride, scale, status);
     return hipGetLastError();
 }
 

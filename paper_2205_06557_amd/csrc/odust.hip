@@ -106,6 +106,7 @@ struct od_system {
     int64_t N = 0, Npad = 0;
     size_t esz = 4;
     int nsplit = 1;
+    int cus = 1;                        // compute units of the device
     // units
     double lam = 0, wpi = 0, cs = 0;
     odk::DustSet ds{};
@@ -136,7 +137,6 @@ struct od_system {
     bool fix_in_mem = false;            // acc_fix lies in mem
     void* fix64 = nullptr;              // FP64: room for acc_fix in mem, or null
     bool sym64_set = false;             // FP64: acc_fix and the items set up, or refused
-    int direct_steps = 0;               // steps to sum directly first: the state has ions outside the domain
     // device memory: one allocation (mem), cut into the buffers below
     void* mem = nullptr;
     void* x = nullptr;
@@ -242,7 +242,15 @@ od_status setup_mesh(od_system* s, hipStream_t st)
     }
     odk::mesh_own(s->ma, (char*)s->mesh_mem, s->mb);
     odk::mesh_scratch(s->ma, (char*)s->mesh_mem + own, s->mb);
-    HIPCHK(odk::mesh_start(s->ma, s->mb, st));
+    const odk::MeshDirect d{s->mb.cost, (const float*)s->x, s->acc_fix, sym_runs((int)(s->Npad / kPairBlock)),
+                            (int)s->N, s->pa.sym_scale, &s->ctl->status};
+    hipError_t e = odk::mesh_start(s->ma, s->mb, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(s->mb.direct, &d, sizeof d, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = hipStreamSynchronize(st);
+    if (e != hipSuccess) {
+        free_mesh(s);
+        return fail(OD_EDEVICE, "setting up the pair sum failed: %s", hipGetErrorString(e));
+    }
     s->mesh = true;
     return OD_OK;
 }
@@ -318,7 +326,7 @@ od_status setup_sym(od_system* s, void* room)
         s->sym = true;
     }
     od_status st = OD_OK;
-    if (!use_mesh(s) || s->direct_steps > 0) st = setup_items(s, s->stream);
+    if (!use_mesh(s)) st = setup_items(s, s->stream);
     if (st == OD_OK && s->custom_alloc) st = first_step_setup(s);
     if (st == OD_OK) HIPCHK(hipStreamSynchronize(s->stream));
     return st;
@@ -725,9 +733,10 @@ od_status launch_step(od_system* s, bool timed)
                 s->xs_sorted, s->cb, s->cut_fix, s->pa, s->ca, s->ctl);
             odk::pair_cut_epilogue<<<nb, 256, 0, s->stream>>>(s->xs_sorted, s->idx_sorted, s->cut_fix,
                                                                (float*)s->a, s->pa, s->ds, s->ctl);
-        } else if (k == 0 && s->mesh && s->direct_steps == 0) {
+        } else if (k == 0 && s->mesh) {
             HIPCHK(odk::mesh_launch(s->ma, s->mb, (const float*)s->x, s->Npad, s->acc_fix, s->Npad, s->pa.sym_scale,
                                     &s->ctl->status, s->stream));
+            HIPCHK(odk::mesh_direct_launch(s->mb.direct, 1, s->Npad, s->cus, s->stream));
         } else if (k == 0 && s->sym) {
             if (s->n_sym_items > 0)     // none in test-particle mode
                 odk::pair_sym_kernel<kPairBlock><<<s->n_sym_items, kPairBlock, 0, s->stream>>>(
@@ -854,7 +863,8 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         (void)hipGetDevice(&dev);
         (void)hipGetDeviceProperties(&prop, dev);
         const int64_t nib = s->Npad / kPairBlock;
-        const int64_t want = 4 * (int64_t)std::max(prop.multiProcessorCount, 1);
+        s->cus = std::max(prop.multiProcessorCount, 1);
+        const int64_t want = 4 * (int64_t)s->cus;
         s->nsplit = s->prec == OD_PREC_FP32
                         ? (int)std::min<int64_t>(kMaxSplitSingle, std::max<int64_t>(1, (want + nib - 1) / nib))
                         : 1;
@@ -955,11 +965,6 @@ od_status od_step(od_system* s, int64_t n_steps)
     if (left > 0) {
         const od_status st = first_step_setup(s);
         if (st != OD_OK) return st;
-    }
-    for (; s->direct_steps > 0 && left > 0; --left) {
-        od_status st = launch_step(s, s->timing);
-        if (st != OD_OK) return st;
-        --s->direct_steps;
     }
     if (s->graph_steps > 0 && !s->timing) {
         if (!s->gexec && left >= s->graph_steps) {
@@ -1206,12 +1211,9 @@ od_status od_set_state(od_system* s, const void* x, const void* v, const double*
         for (int64_t k = 0; k < 3 * N; ++k)
             if (!std::isfinite(val(p, k))) return fail(OD_ENUMERIC, "non-finite state value at %lld", (long long)k);
     }
-    bool outside = false;
     if (x) {
-        const double Ro = s->pu.R * (1.0 + 1e-6), Ho = 0.5 * s->pu.H * (1.0 + 1e-6);
         for (int64_t i = 0; i < N; ++i) {
             const double px = val(x, i), py = val(x, N + i), pz = val(x, 2 * N + i);
-            outside = outside || std::fabs(px) > Ro || std::fabs(py) > Ro || std::fabs(pz) > Ho;
             for (int d = 0; d < s->nd; ++d) {
                 const double a0 = px - s->ds.pos[d][0], a1 = py - s->ds.pos[d][1], a2 = pz - s->ds.pos[d][2];
                 if (a0 * a0 + a1 * a1 + a2 * a2 <= s->ds.rad2[d])
@@ -1224,12 +1226,6 @@ od_status od_set_state(od_system* s, const void* x, const void* v, const double*
             if (!std::isfinite(q[d])) return fail(OD_ENUMERIC, "non-finite charge");
     HIPCHK(hipStreamSynchronize(s->stream));
     drop_graph(s);
-    // ions outside the domain leave it in the next step; until then the grid cannot hold them
-    if (x) s->direct_steps = outside ? 1 : 0;
-    if (outside && s->sym) {
-        const od_status st = setup_items(s, s->stream);
-        if (st != OD_OK) return st;
-    }
     const size_t row = (size_t)N * s->esz;
     const size_t drow = (size_t)s->Npad * s->esz;
     for (int c = 0; c < 3; ++c) {

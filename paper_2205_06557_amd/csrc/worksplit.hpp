@@ -30,28 +30,32 @@ constexpr double kSymMinItems = 1024.0;        // fewer one-tile items: one item
 // and in a batch.  one_row: one target row per item at every size; target:
 // the number of items aimed at (batch options; both change the FP32 partial
 // sums that each item flushes).
-std::vector<odk::SymItem> sym_items_of(int T, bool one_row = false, double target = kSymItemsTarget)
+inline int sym_count(const odk::SymRuns& s)
+{
+    odk::SymPlace at{0, 0};
+    odk::SymItem it{};
+    (void)odk::sym_item_at(s, 1 << 30, at, it);
+    return at.before;
+}
+
+inline odk::SymRuns sym_runs(int T, bool one_row = false, double target = kSymItemsTarget)
 {
     constexpr int R = odk::kSymRows;
     const double pairs = 0.5 * (double)T * (T + 1);
+    const odk::SymRuns groups{T, R, (int)std::max((double)R, std::ceil(pairs / (R * target)))};
+    if (!one_row && (double)sym_count(groups) >= kSymMinGroupedItems) return groups;
+    return {T, 1, (int)std::max(1.0, std::ceil(pairs / target))};
+}
+
+std::vector<odk::SymItem> sym_items_of(int T, bool one_row = false, double target = kSymItemsTarget)
+{
+    const odk::SymRuns runs = sym_runs(T, one_row, target);
+    const bool sub = runs.rows == 1 && runs.C == 1 && 0.5 * (double)T * (T + 1) < kSymMinItems;
     std::vector<odk::SymItem> v;
-    const int C = (int)std::max((double)R, std::ceil(pairs / (R * target)));
-    int I = 0;
-    for (; I + R <= T; I += R)
-        for (int J0 = I; J0 < T; J0 += C) v.push_back({I, J0, std::min(J0 + C, T), R, 0, 4});
-    for (; I < T; ++I) v.push_back({I, I, T, 1, 0, 4});
-    if ((double)v.size() >= kSymMinGroupedItems && !one_row) return v;
-    v.clear();
-    const int C1 = (int)std::max(1.0, std::ceil(pairs / target));
-    const bool sub = C1 == 1 && pairs < kSymMinItems;
-    for (I = 0; I < T; ++I)
-        for (int J0 = I; J0 < T; J0 += C1) {
-            if (!sub) {
-                v.push_back({I, J0, std::min(J0 + C1, T), 1, 0, 4});
-                continue;
-            }
-            for (int st = 0; st < 4; ++st) v.push_back({I, J0, J0 + 1, 1, st, st + 1});
-        }
+    odk::SymPlace at{0, 0};
+    odk::SymItem it{};
+    for (int k = 0; odk::sym_item_at(runs, k, at, it); ++k)
+        for (int st = 0; st < 4; st += sub ? 1 : 4) v.push_back({it.I, it.J0, it.J1, it.rows, st, sub ? st + 1 : 4});
     return v;
 }
 
