@@ -254,9 +254,11 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * 100 MB at 2^17 and 500 MB at 2^20 ions, is taken by the first step, or at
  * creation where the system has an allocator of its own; where it is refused
  * the direct sum is used.  It is used too for a step that begins with ions
- * outside the domain, where od_set_state may put them; the device finds that
- * out, so a step that the caller captured in a graph of its own stays right
- * when it is replayed after od_set_state.
+ * outside the domain, where od_set_state may put them, or with so many close
+ * together that the split would take longer (at 2^16 ions in a cylinder of
+ * radius 3 and height 6 r_De, about 2,000 within 0.4 r_De); the device finds
+ * that out, so a step that the caller captured in a graph of its own stays
+ * right when it is replayed after od_set_state.
  * OD_PAIR_SYMMETRIC always sums every pair directly.
  * The symmetric kernel needs 24 bytes per ion of accumulators.  FP64 systems
  * have a sum of their own, which neither choice changes (each pair once too,

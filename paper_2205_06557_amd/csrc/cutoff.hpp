@@ -94,13 +94,14 @@ __global__ __launch_bounds__(256) void cut_bin_kernel(const float* __restrict__ 
     __shared__ int hist[kMaxSlabs];
     for (int s = threadIdx.x; s < c.nslab; s += 256) hist[s] = 0;
     __syncthreads();
-    const int i = blockIdx.x * 256 + threadIdx.x;
+    const int i = blockIdx.x * 256 + threadIdx.x, at = min(i, N - 1);
+    const float z = x[2 * plane + at];
+    const int cx = cut_bin(x[at], c.x0, c.inv_c, c.side), cy = cut_bin(x[plane + at], c.x0, c.inv_c, c.side);
+    const int key = cut_bin(z, c.z0, c.inv_l, c.nlay) * c.side * c.side + hilbert(c.side, cx, cy);
+    const int arr = arrive(b.count, key, i < N);
     if (i < N) {
-        const float z = x[2 * plane + i];
-        const int cx = cut_bin(x[i], c.x0, c.inv_c, c.side), cy = cut_bin(x[plane + i], c.x0, c.inv_c, c.side);
-        const int key = cut_bin(z, c.z0, c.inv_l, c.nlay) * c.side * c.side + hilbert(c.side, cx, cy);
         b.key[i] = key;
-        b.arr[i] = atomicAdd(&b.count[key], 1);
+        b.arr[i] = arr;
         atomicAdd(&hist[cut_bin(z, c.z0, c.inv_w, c.nslab)], 1);
     }
     __syncthreads();
@@ -174,10 +175,9 @@ __global__ __launch_bounds__(256) void cut_order_kernel(const float* __restrict_
     const int t = blockIdx.x * 256 + threadIdx.x;
     if (t >= N) return;
     const int i = b.temp[t];
-    int n, rank = 0;
+    int n;
     const int first = cut_first(c, b, b.key[i], n);
-    for (int k = 0; k < n; ++k) rank += b.temp[first + k] < i;
-    const int to = first + rank;
+    const int to = first + count_below(b.temp + first, n, i);
     idx[to] = i;
     xs[to] = x[i];
     xs[plane + to] = x[plane + i];

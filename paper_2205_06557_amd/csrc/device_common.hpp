@@ -184,6 +184,42 @@ __device__ __forceinline__ double exp_neg_tab(double r, const double* __restrict
     return fma(s * f, p, s);
 }
 
+// Arrival number of each active lane's key: count[key]++ for every one of them,
+// with one atomic for the lanes of a wave that share a key, as far as shared
+// keys are found in the first lanes.  Where most ions fall into few bins, an
+// atomic per ion on one address, 12 ns each, is what a sort would take.
+__device__ __forceinline__ int arrive(int* __restrict__ count, int key, bool active)
+{
+    const int lane = threadIdx.x & 63;
+    int lead = lane, add = active ? 1 : 0, rank = 0;
+    unsigned long long todo = __ballot(active);
+    while (todo) {
+        const int first = __ffsll(todo) - 1;
+        const unsigned long long same = __ballot(active && key == __shfl(key, first, 64)) & todo;
+        if (__popcll(same) == 1) break;
+        if (same >> lane & 1) {
+            lead = first;
+            rank = __popcll(same & ((1ull << lane) - 1ull));
+            add = lane == first ? __popcll(same) : 0;
+        }
+        todo &= ~same;
+    }
+    int at = 0;
+    if (add) at = atomicAdd(&count[key], add);
+    return __shfl(at, lead, 64) + rank;
+}
+
+// How many of v[0 .. n) are below x, with loads in flight.
+__device__ __forceinline__ int count_below(const int* __restrict__ v, int n, int x)
+{
+    int below = 0, k = 0;
+    for (; k + 16 <= n; k += 16)
+#pragma unroll
+        for (int u = 0; u < 16; ++u) below += v[k + u] < x;
+    for (; k < n; ++k) below += v[k] < x;
+    return below;
+}
+
 // ---------------------------------------------------------------------------
 // Wave64 sum of a 64-bit value: butterfly over the xor masks 32 and 16, then
 // rotations by 8, 4, 2 and 1 within rows of 16 lanes, which after the steps

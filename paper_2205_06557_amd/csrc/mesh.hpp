@@ -10,7 +10,8 @@
 //   mesh_bin_kernel      sort bin of every ion: column of kx x kx cells, slice
 //                        along z; arrival number within the bin (atomic)
 //   mesh_scan_kernel     per column, prefix sum over its bins
-//   mesh_cols_kernel     prefix over columns, each padded to whole groups of 16
+//   mesh_cols_kernel     prefix over columns, each padded to whole groups of 16;
+//                        what the split would cost with the ions where they are
 //   mesh_place_kernel    ion index to its bin's slots, in arrival order
 //   mesh_order_kernel    slots of a bin put in ion order (arrival order depends
 //                        on scheduling, ion order does not); sorted positions
@@ -24,10 +25,11 @@
 //                        step's tail reads
 //   mesh_direct_kernel   the direct sum instead, where the ions do not suit the
 //                        grid: some lie outside the domain (od_set_state may
-//                        put them there; they leave it in that step)
-// Which of the two it is, mesh_bin_kernel and mesh_scan_kernel find out on the
-// device, so that it holds for every replay of a captured step too; the
-// kernels of the other return at once.
+//                        put them there; they leave it in that step), or so many
+//                        lie so close together that the split would cost more
+// Which of the two it is, the first three find out on the device, so that it
+// holds for every replay of a captured step too; the kernels of the other
+// return at once.
 // Every sum has a fixed order or is an integer sum: results are reproducible
 // bit for bit.
 #pragma once
@@ -41,6 +43,7 @@ namespace odk {
 // One system's direct sum, for the steps that call for it.
 struct MeshDirect {
     const long long* cost;      // MeshBufs::cost
+    long long cost_max;
     const float* x;             // positions and totals, their planes equally far apart
     unsigned long long* fix;
     SymRuns runs;
@@ -54,7 +57,7 @@ struct MeshDirect {
 struct MeshBufs {
     int* count;            // own: [bins] ions per bin; zero between steps
     double* green;         // own: [m.M][ng] Green's tables
-    long long* cost;       // own: [2] above zero: this step is summed directly; the next one's, while it is found out
+    long long* cost;       // own: [3] near pairs, mark of ions outside the domain, fullest column; see mesh_skip
     MeshDirect* direct;    // own: see mesh_direct_kernel
     float* near0;          // own: constant term of the near polynomial (mesh_zero_kernel)
     int* key;              // [N] sort bin of each ion
@@ -84,10 +87,11 @@ __device__ __forceinline__ int mesh_zbin(double z, const MeshArgs& m)
     return (int)fmin(fmax(floor((z + m.Hh) * (m.inv_h * kMeshZsub)), 0.0), (double)(m.nzb - 1));
 }
 
-constexpr long long kMeshNever = 1ll << 62;
+constexpr long long kMeshNever = 1ll << 61;
 
-// Asked where a kernel waits for other loads anyway.
-__device__ __forceinline__ bool mesh_skip(const long long* cost) { return cost[0] > 0; }
+// Whether the step is summed directly.  Asked where a kernel waits for other
+// loads anyway.
+__device__ __forceinline__ bool mesh_skip(const long long* cost, long long most) { return cost[0] + cost[2] > most; }
 
 // Sort bin of every ion; also marks every slot empty, and whether ions lie
 // outside the domain (by more than the rounding of one on its surface).
@@ -96,14 +100,17 @@ __global__ __launch_bounds__(256) void mesh_bin_kernel(const float* __restrict__
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < m.cap) b.temp[i] = -1;
-    if (i >= m.N) return;
-    const double px = x[i], py = x[plane + i], pz = x[2 * plane + i];
+    const bool live = i < m.N;
+    const int at = live ? i : 0;
+    const double px = x[at], py = x[plane + at], pz = x[2 * plane + at];
     if (fmax(fabs(px), fabs(py)) > m.R * (1.0 + 1e-6) || fabs(pz) > m.Hh * (1.0 + 1e-6)) b.cost[1] = kMeshNever;
     const int cx = mesh_cell(px, -m.R, m.inv_h, m.nc[0]) / kMeshKx;
     const int cy = mesh_cell(py, -m.R, m.inv_h, m.nc[1]) / kMeshKx;
     const int key = (cy * m.ncx + cx) * m.nzb + mesh_zbin(pz, m);
+    const int arr = arrive(b.count, key, live);
+    if (!live) return;
     b.key[i] = key;
-    b.arr[i] = atomicAdd(&b.count[key], 1);
+    b.arr[i] = arr;
 }
 
 // One block per column: bin starts relative to the column; clears the counts.
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(256) void mesh_scan_kernel(MeshArgs m, MeshBufs b)
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         b.cost[0] = b.cost[1];
-        b.cost[1] = 0;
+        b.cost[1] = b.cost[2] = 0;
     }
     int* cnt = b.count + (long long)blockIdx.x * m.nzb;
     int* rel = b.rel + (long long)blockIdx.x * (m.nzb + 1);
@@ -142,10 +149,52 @@ __global__ __launch_bounds__(256) void mesh_scan_kernel(MeshArgs m, MeshBufs b)
     if (threadIdx.x == 0) rel[m.nzb] = carry;
 }
 
-// First slot of each column (one block).
+// What the split would cost with the ions where they are: pairs of the ions of
+// every column, in slabs as high as a brick, with those of the columns and slabs
+// within r_c, and the fullest of them.  Cell k of this thread, then every
+// `threads` further on.
+__device__ __forceinline__ void mesh_cost(const MeshArgs& m, const MeshBufs& b, int k, int threads)
+{
+    const int ns = (m.nzb + kMeshSlab - 1) / kMeshSlab, cells = m.ncx * m.ncy * ns;
+    auto ions = [&](int c, int z0, int z1) {
+        const int* rel = b.rel + (long long)c * (m.nzb + 1);
+        return rel[min(z1 * kMeshSlab, m.nzb)] - rel[max(z0, 0) * kMeshSlab];
+    };
+    constexpr int reach = (int)(kMeshRatio / kMeshKx + 1.0);
+    long long near = 0, top = 0;
+    for (; k < cells; k += threads) {
+        const int c = k / ns, z = k - c * ns, cx = c % m.ncx, cy = c / m.ncx, n = ions(c, z, z + 1);
+        // without branches, so that the loads are in flight together
+        int w = 0;
+#pragma unroll
+        for (int dy = -reach; dy <= reach; ++dy)
+#pragma unroll
+            for (int dx = -reach; dx <= reach; ++dx) {
+                const int x = min(max(cx + dx, 0), m.ncx - 1), y = min(max(cy + dy, 0), m.ncy - 1);
+                const int q = ions(y * m.ncx + x, z - 1, z + 2);
+                w += x == cx + dx && y == cy + dy ? q : 0;
+            }
+        near += (long long)n * w;
+        top = max(top, (long long)(n * (kMeshColumnNs / kMeshPairNs)));
+    }
+    near = wave_sum(near);
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) top = max(top, __shfl_xor(top, d, 64));
+    if ((threadIdx.x & 63) == 0 && near > 0) {
+        atomicAdd((unsigned long long*)&b.cost[0], (unsigned long long)near);
+        atomicMax((unsigned long long*)&b.cost[2], (unsigned long long)top);
+    }
+}
+
+// Block 0: first slot of each column; the others: the step's cost.
 __global__ __launch_bounds__(1024) void mesh_cols_kernel(MeshArgs m, MeshBufs b)
 {
     __shared__ int wsum[16];
+    if (blockIdx.x > 0) {
+        // one wave of each: the loads are scattered, and few of them to a compute unit at a time
+        if (threadIdx.x < 64) mesh_cost(m, b, (blockIdx.x - 1) * 64 + threadIdx.x, (gridDim.x - 1) * 64);
+        return;
+    }
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int ncol = m.ncx * m.ncy;
     int carry = 0;
@@ -191,7 +240,7 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
                                                          MeshBufs b)
 {
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (mesh_skip(b.cost) | (t >= b.col[m.ncx * m.ncy])) return;
+    if (mesh_skip(b.cost, m.cost_max) | (t >= b.col[m.ncx * m.ncy])) return;
     const int i = b.temp[t];
     if (i < 0) {
         b.idx[t] = -1;
@@ -202,8 +251,7 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
     const int c = key / m.nzb, z = key - c * m.nzb;
     const int* rel = b.rel + (long long)c * (m.nzb + 1);
     const int s0 = b.col[c] + rel[z], s1 = b.col[c] + rel[z + 1];
-    int to = s0;
-    for (int k = s0; k < s1; ++k) to += b.temp[k] < i;
+    const int to = s0 + count_below(b.temp + s0, s1 - s0, i);
     b.idx[to] = i;
     b.s[to] = make_float4(x[i], x[plane + i], x[2 * plane + i], 0.0f);
 }
@@ -212,7 +260,7 @@ __global__ __launch_bounds__(256) void mesh_order_kernel(const float* __restrict
 __global__ __launch_bounds__(256) void mesh_box_kernel(MeshArgs m, MeshBufs b)
 {
     const int t = blockIdx.x * 256 + threadIdx.x;
-    if (mesh_skip(b.cost) | (t >= b.col[m.ncx * m.ncy])) return;     // a multiple of 16
+    if (mesh_skip(b.cost, m.cost_max) | (t >= b.col[m.ncx * m.ncy])) return;     // a multiple of 16
     const bool live = b.idx[t] >= 0;
     const int ns = m.cap / kMeshSub;
     const float4 p = b.s[t];
@@ -298,7 +346,7 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_spread_kernel(MeshArgs m, M
 {
     extern __shared__ unsigned long long grid[];
     __shared__ double wt[kMeshThreads / 64][16][3][16];
-    const bool skip = mesh_skip(b.cost);
+    const bool skip = mesh_skip(b.cost, m.cost_max);
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, c16 = lane & 15, q = lane >> 4;
     for (int k = threadIdx.x; k < kMeshNodes; k += kMeshThreads) grid[k] = 0ull;
     if (skip) return;
@@ -435,7 +483,7 @@ __global__ __launch_bounds__(256) void mesh_conv_kernel(MeshArgs m, const double
 {
     typedef double d4 __attribute__((ext_vector_type(4)));
     extern __shared__ double tab[];
-    const bool skip = mesh_skip(cost);
+    const bool skip = mesh_skip(cost, m.cost_max);
     const int nx = m.n[0], ny = m.n[1], nz = m.n[2];
     const int len = AXIS == 0 ? nx : AXIS == 1 ? ny : nz, half = (len + 1) / 2;
     const int lines = AXIS == 0 ? ny * nz : AXIS == 1 ? nx * nz : nx * ny;
@@ -525,7 +573,7 @@ __global__ __launch_bounds__(kMeshThreads) void mesh_gather_kernel(MeshArgs m, M
 {
     extern __shared__ double node[];
     __shared__ int start[kMeshG * kMeshG], pre[kMeshG * kMeshG + 1];
-    const bool skip = mesh_skip(b.cost);
+    const bool skip = mesh_skip(b.cost, m.cost_max);
     const int x0 = blockIdx.x % m.nbx * kMeshG * kMeshKx, y0 = blockIdx.x / m.nbx % m.nby * kMeshG * kMeshKx,
               z0 = blockIdx.x / (m.nbx * m.nby) * kMeshBz;
     if (threadIdx.x < kMeshG * kMeshG) {
@@ -663,7 +711,7 @@ void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* _
     __shared__ int2 cand[4][kMeshCand];
     __shared__ float4 src[S][64];
     __shared__ double part[S][3][64];
-    const bool skip = mesh_skip(cost);
+    const bool skip = mesh_skip(cost, m.cost_max);
     const int total = col[m.ncx * m.ncy];
     // consecutive tiles share sources: give each of the 8 XCDs a run of them
     const int tiles = (total + 63) / 64, per = (tiles + 7) / 8;
@@ -871,7 +919,7 @@ void mesh_direct_kernel(const MeshDirect* __restrict__ table, int systems, long 
     __shared__ float4 src[4][128];
     __shared__ float jpart[4][3][BLOCK];
     for (int k = 0; k < systems; ++k) {
-        if (!mesh_skip(table[k].cost)) continue;
+        if (!mesh_skip(table[k].cost, table[k].cost_max)) continue;
         const MeshDirect d = table[k];
         SymPlace at{0, 0};
         SymItem it;
@@ -910,7 +958,7 @@ inline size_t mesh_own(const MeshArgs& m, char* base, MeshBufs& b)
     a.take(&b.count, (size_t)m.ncx * m.ncy * m.nzb * 4);
     a.take(&b.green, (size_t)m.M * m.ng * 8);
     a.take(&b.near0, 4);
-    a.take(&b.cost, 2 * sizeof(long long));
+    a.take(&b.cost, 3 * sizeof(long long));
     a.take(&b.direct, sizeof(MeshDirect));
     return a.at;
 }
@@ -949,7 +997,7 @@ inline hipError_t mesh_start(const MeshArgs& m, const MeshBufs& b, hipStream_t s
     if (e == hipSuccess)
         e = hipFuncSetAttribute((const void*)mesh_gather_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e == hipSuccess) e = hipMemsetAsync(b.count, 0, (size_t)m.ncx * m.ncy * m.nzb * 4, st);
-    if (e == hipSuccess) e = hipMemsetAsync(b.cost, 0, 2 * sizeof(long long), st);
+    if (e == hipSuccess) e = hipMemsetAsync(b.cost, 0, 3 * sizeof(long long), st);
     if (e != hipSuccess) return e;
     mesh_zero_kernel<<<1, 64, 0, st>>>(m, b.near0);
     mesh_green_kernel<<<dim3(m.M, (m.ng + 63) / 64), 256, 0, st>>>(m, mesh_i0(kMeshBeta), b.green);
@@ -965,7 +1013,7 @@ inline hipError_t mesh_launch(const MeshArgs& m, const MeshBufs& b, const float*
     const long long v = (long long)m.n[0] * m.n[1] * m.n[2];
     mesh_bin_kernel<<<gc, 256, 0, st>>>(x, plane, m, b);
     mesh_scan_kernel<<<ncol, 256, 0, st>>>(m, b);
-    mesh_cols_kernel<<<1, 1024, 0, st>>>(m, b);
+    mesh_cols_kernel<<<1 + std::min(1024, (ncol * ((m.nzb + kMeshSlab - 1) / kMeshSlab) + 63) / 64), 1024, 0, st>>>(m, b);
     mesh_place_kernel<<<gi, 256, 0, st>>>(m, b);
     mesh_order_kernel<<<gc, 256, 0, st>>>(x, plane, m, b);
     mesh_box_kernel<<<gc, 256, 0, st>>>(m, b);

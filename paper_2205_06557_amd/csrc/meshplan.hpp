@@ -39,6 +39,7 @@ constexpr int kMeshKx = 4;          // column width in cells
 constexpr int kMeshZsub = 2;        // sort bins per cell along z
 constexpr int kMeshG = 4;           // a brick is kMeshG x kMeshG columns ...
 constexpr int kMeshBz = 7;          // ... and kMeshBz cells along z
+constexpr int kMeshSlab = kMeshBz * kMeshZsub;  // a brick's sort bins along z, about r_c thick
 // nodes that the ions of a brick reach, per axis and in all
 constexpr int kMeshLx = kMeshG * kMeshKx + kMeshP - 1, kMeshLz = kMeshBz + kMeshP - 1;
 constexpr int kMeshNodes = kMeshLx * kMeshLx * kMeshLz;
@@ -51,6 +52,7 @@ struct MeshArgs {
     int nbx, nby, nbz;              // bricks per axis
     int parts, gparts;              // blocks per brick that spread its charges, that gather its forces
     int ng;                         // entries of one Green's table (zero padded)
+    long long cost_max;             // estimated cost (mesh_cost) above which a step is summed directly
     double R, Hh, h, inv_h;         // domain radius and half height; grid spacing
     float rc, rc2, irc2, cw;        // near radius, its square, -2 / rc^2; column width
     float near[kMeshNearDeg + 1];   // f_L(r) = -L'/r in powers of 1 - 2 r^2 / r_c^2
@@ -219,6 +221,20 @@ inline int mesh_parts(const MeshArgs& a, int most)
     return best;
 }
 
+// What a step may cost as a split, in near pairs of 1.1 ps: the direct sum's
+// N^2 / 4,200 ns less 2.4 ns per ion for the kernels that do not depend on where
+// the ions are (each has 0.1 ms besides).  Near pairs and the fullest column of a
+// brick (340 ns per ion: one wave spreads it) count against it.  Uniform ions
+// reach 0.38 of it at 40,960, 0.21 at 2^16 and 0.05 at 2^18; with 30 % of the ions in a
+// ball of 0.1 r_De a pair sum took 4.5 ms at 40,960 ions, 7.4 at 2^16 and 31 at
+// 2^18, with all of them 14, 24 and 101, against 0.53, 1.2 and 16 directly.
+constexpr double kMeshPairNs = 1.1e-3, kMeshColumnNs = 340.0;
+
+inline long long mesh_cost_max(long long N)
+{
+    return (long long)(((double)N * N / 4200.0 - 2.4 * N) / kMeshPairNs);
+}
+
 // r_c trades near pairs (r_c^3) against the grid (its nodes go as r_c^-3, the
 // convolutions as r_c^-4) and scales with the ion spacing: in units of
 // (27 / n)^(1/3), a step took 0.61 ms at 1.6, 0.65 at 1.68, 0.65 at 1.75 and
@@ -246,6 +262,7 @@ inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
     a.nbx = (a.ncx + kMeshG - 1) / kMeshG;
     a.nby = (a.ncy + kMeshG - 1) / kMeshG;
     a.nbz = (a.nc[2] + kMeshBz - 1) / kMeshBz;
+    a.cost_max = mesh_cost_max(N);
     a.parts = mesh_parts(a, 2);
     a.gparts = mesh_parts(a, 3);
     a.ng = std::max(a.n[0], a.n[2]) + 80;

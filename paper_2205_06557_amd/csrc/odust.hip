@@ -242,7 +242,7 @@ od_status setup_mesh(od_system* s, hipStream_t st)
     }
     odk::mesh_own(s->ma, (char*)s->mesh_mem, s->mb);
     odk::mesh_scratch(s->ma, (char*)s->mesh_mem + own, s->mb);
-    const odk::MeshDirect d{s->mb.cost, (const float*)s->x, s->acc_fix, sym_runs((int)(s->Npad / kPairBlock)),
+    const odk::MeshDirect d{s->mb.cost, s->ma.cost_max, (const float*)s->x, s->acc_fix, sym_runs((int)(s->Npad / kPairBlock)),
                             (int)s->N, s->pa.sym_scale, &s->ctl->status};
     hipError_t e = odk::mesh_start(s->ma, s->mb, st);
     if (e == hipSuccess) e = hipMemcpyAsync(s->mb.direct, &d, sizeof d, hipMemcpyHostToDevice, st);
