@@ -137,7 +137,10 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
 /* Advances n_steps >= 0 time steps (Section 2 and Appendix B): forces at the
  * current positions and charges, kick, charge exchange, drift, absorption,
  * exit, charge update, collection force (Eq. 3), reinjection, recording.
- * Asynchronous; returns after the launches are queued. */
+ * Asynchronous; returns after the launches are queued.  The exception is the
+ * first step that needs the memory of a large FP32 system's pair sum (see
+ * od_set_pair_kernel) without an allocator of the caller's: it allocates that
+ * memory, up to some hundred MB, and waits for its set-up (a few milliseconds). */
 od_status od_step(od_system* sys, int64_t n_steps);
 
 /* Waits for the system's stream and returns the device status. */
@@ -262,8 +265,10 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * OD_PAIR_SYMMETRIC always sums every pair directly.
  * The symmetric kernel needs 24 bytes per ion of accumulators.  FP64 systems
  * have a sum of their own, which neither choice changes (each pair once too,
- * in 64 bits with totals of two words, 48 bytes per ion; one-sided for a step
- * whose closest pair they cannot hold): OD_PAIR_SYMMETRIC is refused for them
+ * in 64 bits with totals of two words, 48 bytes per ion and a work list of at
+ * most 2 MB, taken at creation; one-sided for a step whose closest pair the
+ * words cannot hold, and throughout where that memory is refused):
+ * OD_PAIR_SYMMETRIC is refused for them
  * and OD_PAIR_ONE_SIDED reported.  A cutoff (od_set_cutoff) takes precedence
  * over either.  In test-particle mode (OD_FLAG_NO_ION_ION) the symmetric
  * setting runs no pair kernel at all: the step's tail adds the grain, drive
@@ -414,7 +419,9 @@ od_status od_batch_get_sym_config(od_batch* b, int32_t* persistent, int32_t* one
 od_status od_batch_autotune(od_batch* b, const char* cache_path, double* best_ms);
 
 /* Capture steps_per_graph (0..1000; 0: no graph) steps as one HIP graph that
- * od_step_batch replays; the remainder of a step count runs eagerly. */
+ * od_step_batch replays; the remainder of a step count runs eagerly.
+ * od_step_batch is asynchronous as od_step is, with the same exception for the
+ * first step of a batch that has large members. */
 od_status od_batch_set_graph(od_batch* b, int32_t steps_per_graph);
 od_status od_step_batch(od_batch* b, int64_t n_steps);
 od_status od_batch_sync(od_batch* b);

@@ -135,8 +135,7 @@ struct od_system {
     odk::MeshBufs mb{};
     void* mesh_mem = nullptr;
     bool fix_in_mem = false;            // acc_fix lies in mem
-    void* fix64 = nullptr;              // FP64: room for acc_fix in mem, or null
-    bool sym64_set = false;             // FP64: acc_fix and the items set up, or refused
+    bool items_in_mem = false;          // and sym_items
     // device memory: one allocation (mem), cut into the buffers below
     void* mem = nullptr;
     void* x = nullptr;
@@ -209,20 +208,21 @@ void free_mesh(od_system* s)
 void free_sym(od_system* s)
 {
     if (!s->fix_in_mem) dev_free(s, s->acc_fix);
-    dev_free(s, s->sym_items);
+    if (!s->items_in_mem) dev_free(s, s->sym_items);
     s->acc_fix = nullptr;
     s->sym_items = nullptr;
     s->n_sym_items = 0;
-    s->sym = s->fix_in_mem = false;
+    s->sym = s->fix_in_mem = s->items_in_mem = false;
 }
 
 // Work items of the direct symmetric sum.  In test-particle mode there are
-// none (no pair kernel runs).
-od_status setup_items(od_system* s, hipStream_t st)
+// none (no pair kernel runs).  room: memory set aside for them, or null.
+od_status setup_items(od_system* s, hipStream_t st, void* room = nullptr)
 {
     if (s->n_sym_items > 0 || !s->pa.ion_ion) return OD_OK;
     const std::vector<odk::SymItem> items = sym_items((int)(s->Npad / kPairBlock));
-    s->sym_items = (odk::SymItem*)dev_alloc(s, items.size() * sizeof(odk::SymItem));
+    s->items_in_mem = room != nullptr;
+    s->sym_items = (odk::SymItem*)(room ? room : dev_alloc(s, items.size() * sizeof(odk::SymItem)));
     if (!s->sym_items) return fail(OD_ENOMEM, "device allocation of the symmetric pair sum failed");
     HIPCHK(hipMemcpyAsync(s->sym_items, items.data(), items.size() * sizeof(odk::SymItem), hipMemcpyHostToDevice, st));
     HIPCHK(hipStreamSynchronize(st));
@@ -284,18 +284,24 @@ size_t fix_bytes(const od_system* s)
     return (s->prec == OD_PREC_FP32 ? 3 : 6) * (size_t)s->Npad * sizeof(unsigned long long);
 }
 
-// Totals and work items of an FP64 system's sum, set up by the first step (at
-// creation it would cost 0.1 ms, a third of it); where their memory is refused
-// the system is summed one-sided.
-od_status setup_sym64(od_system* s, hipStream_t st)
+// Bytes of an FP64 system's work items (none in test-particle mode).
+size_t items64_bytes(const od_system* s)
 {
-    s->sym64_set = true;
-    s->fix_in_mem = s->fix64 != nullptr;
-    s->acc_fix = (unsigned long long*)(s->fix64 ? s->fix64 : dev_alloc(s, fix_bytes(s)));
-    if (s->acc_fix && setup_items(s, st) != OD_OK) free_sym(s);
+    if (s->prec != OD_PREC_FP64 || !s->pa.ion_ion) return 0;
+    return (size_t)sym_items_count((int)(s->Npad / kPairBlock)) * sizeof(odk::SymItem);
+}
+
+// Totals and work items of an FP64 system's sum, at creation, while the device
+// draws the initial state.  room: memory set aside for both, or null; where
+// their memory is refused the system is summed one-sided.
+od_status setup_sym64(od_system* s, char* room)
+{
+    if (!s->pa.ion_ion) return OD_OK;
+    s->fix_in_mem = room != nullptr;
+    s->acc_fix = (unsigned long long*)(room ? room : dev_alloc(s, fix_bytes(s)));
+    if (s->acc_fix && setup_items(s, s->stream, room ? room + fix_bytes(s) : nullptr) != OD_OK) free_sym(s);
     (void)hipGetLastError();
-    if (s->acc_fix) HIPCHK(hipMemsetAsync(s->acc_fix, 0, fix_bytes(s), st));
-    HIPCHK(hipStreamSynchronize(st));
+    if (s->acc_fix) HIPCHK(hipMemsetAsync(s->acc_fix, 0, fix_bytes(s), s->stream));
     return OD_OK;
 }
 
@@ -306,8 +312,6 @@ od_status setup_sym64(od_system* s, hipStream_t st)
 // its caller's takes it at creation, where the allocator may be called.
 od_status first_step_setup(od_system* s)
 {
-    if (s->prec == OD_PREC_FP64 && s->pa.ion_ion && !s->sym64_set)
-        return outside_capture(s->stream, [s](hipStream_t st) { return setup_sym64(s, st); });
     if (s->cut || !use_mesh(s) || s->mesh) return OD_OK;
     return outside_capture(s->stream, [s](hipStream_t st) { return setup_mesh(s, st); });
 }
@@ -881,7 +885,7 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
     size_t at[7] = {0};
     for (int k = 0; k < 6; ++k) at[k + 1] = at[k] + (sizes[k] + 255) / 256 * 256;
     // with room for the default pair sum
-    const size_t fix = fix_bytes(s);
+    const size_t fix = fix_bytes(s) + items64_bytes(s);
     bool roomy = true;
     s->mem = dev_alloc(s, at[6] + fix);
     if (!s->mem) {
@@ -923,7 +927,8 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
     }
     // while the device draws the initial state
     s->mesh_planned = plan_mesh(s->prec, s->pa, s->pu, s->ma) ? 1 : -1;
-    st = read_status(s);
+    if (s->prec == OD_PREC_FP64) st = setup_sym64(s, roomy ? base + at[6] : nullptr);
+    if (st == OD_OK) st = read_status(s);
     if (st == OD_OK && (sim->flags & OD_FLAG_CONFINEMENT)) {
         // the grid's sums use the acceleration planes, which no step has
         // written yet: at most 8.5 bytes per ion and one slice
@@ -943,12 +948,7 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         s->pa = c.pa;
         s->fa = c.fa;
     }
-    if (st == OD_OK)
-        st = apply_pair_kind(s, roomy ? base + at[6] : nullptr);
-    if (st == OD_OK && s->prec == OD_PREC_FP64) {
-        s->fix64 = roomy ? base + at[6] : nullptr;
-        if (s->custom_alloc) st = first_step_setup(s);
-    }
+    if (st == OD_OK) st = apply_pair_kind(s, roomy ? base + at[6] : nullptr);
     if (st != OD_OK) {
         od_destroy(s);
         return st;

@@ -47,16 +47,29 @@ inline odk::SymRuns sym_runs(int T, bool one_row = false, double target = kSymIt
     return {T, 1, (int)std::max(1.0, std::ceil(pairs / target))};
 }
 
+// Whether the runs, one tile each, are cut into sub-tiles.
+inline bool sym_cut(const odk::SymRuns& s)
+{
+    return s.rows == 1 && s.C == 1 && 0.5 * (double)s.T * (s.T + 1) < kSymMinItems;
+}
+
 std::vector<odk::SymItem> sym_items_of(int T, bool one_row = false, double target = kSymItemsTarget)
 {
     const odk::SymRuns runs = sym_runs(T, one_row, target);
-    const bool sub = runs.rows == 1 && runs.C == 1 && 0.5 * (double)T * (T + 1) < kSymMinItems;
+    const bool sub = sym_cut(runs);
     std::vector<odk::SymItem> v;
     odk::SymPlace at{0, 0};
     odk::SymItem it{};
     for (int k = 0; odk::sym_item_at(runs, k, at, it); ++k)
         for (int st = 0; st < 4; st += sub ? 1 : 4) v.push_back({it.I, it.J0, it.J1, it.rows, st, sub ? st + 1 : 4});
     return v;
+}
+
+// Length of sym_items_of(T).
+inline int sym_items_count(int T)
+{
+    const odk::SymRuns runs = sym_runs(T);
+    return sym_count(runs) * (sym_cut(runs) ? 4 : 1);
 }
 
 // Work of an item: target rows times 64-ion source sub-tiles.
