@@ -413,8 +413,9 @@ od_status od_batch_get_sym_config(od_batch* b, int32_t* persistent, int32_t* one
  * persistent or not, jsplit 1, 2, 4, split_max_n 2^15, 2^16; symmetric:
  * persistent or not, one target row per item or the size rule), keeps the
  * fastest, and returns its time in *best_ms.  With cache_path (a text file of one JSON object per
- * line, keyed by GPU architecture, CU count and the histogram of log2 N of
- * the systems) a cached choice is reused and a new one appended.  The
+ * line, keyed by GPU architecture, CU count, the histogram of log2 N of the
+ * systems and, where members are split into near pairs and a far part, theirs)
+ * a cached choice is reused and a new one appended.  The
  * systems' state is unchanged. */
 od_status od_batch_autotune(od_batch* b, const char* cache_path, double* best_ms);
 
