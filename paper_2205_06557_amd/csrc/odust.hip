@@ -310,10 +310,12 @@ od_status setup_sym64(od_system* s, char* room)
 // 64 MB take 0.3 ms, and milliseconds in a row, which a program that only
 // draws initial states would pay for nothing.  A system with an allocator of
 // its caller's takes it at creation, where the allocator may be called.
+// Where neither its memory nor that of the direct sum's items is to be had, the
+// step fails, and the next one asks again.
 od_status first_step_setup(od_system* s)
 {
-    if (s->cut || !use_mesh(s) || s->mesh) return OD_OK;
-    return outside_capture(s->stream, [s](hipStream_t st) { return setup_mesh(s, st); });
+    if (s->cut || !s->sym || !s->pa.ion_ion || (use_mesh(s) ? s->mesh : s->n_sym_items > 0)) return OD_OK;
+    return outside_capture(s->stream, [s](hipStream_t st) { return use_mesh(s) ? setup_mesh(s, st) : setup_items(s, st); });
 }
 
 // Sets up the symmetric pair sum: its fixed-point totals, and the work items
