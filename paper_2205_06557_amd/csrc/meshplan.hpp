@@ -195,24 +195,21 @@ inline bool mesh_dims(double R, double H, double rc, MeshArgs& a)
     return true;
 }
 
-// The split of a system of N ions (dimensionless R, H).  False: use the direct
-// sum.
-//
-// Blocks per brick, at most `most`: a compute unit holds one block, a last
+// Blocks per brick, at most `most`, on `cus` compute units: each holds one block, a last
 // round that is nearly empty costs as much as a full one, a block has 0.08 of
 // a brick's work to do whatever its part (the brick's nodes in and out of
 // LDS), and a tenth of the bricks lie in the corners outside the cylinder.
 // More than one only where that should gain a tenth.  One against the blocks
-// chosen, us per pair sum: 336 / 281 at 40,960 ions (128 bricks), 405 / 382 at
+// chosen, us per pair sum on 256: 336 / 281 at 40,960 ions (128 bricks), 405 / 382 at
 // 2^16 (144), 638 / 597 at 2^17 (300; 612 with four to gather); 489 / 507 with four at
 // 98,304 (275).
-inline int mesh_parts(const MeshArgs& a, int most)
+inline int mesh_parts(const MeshArgs& a, int most, int cus)
 {
     const double bricks = 0.9 * a.nbx * a.nby * a.nbz;
     int best = 1;
-    double cost = 0.9 * std::ceil(bricks / 256.0) * 1.08;
+    double cost = 0.9 * std::ceil(bricks / cus) * 1.08;
     for (int p = 2; p <= most; ++p) {
-        const double c = std::ceil(bricks * p / 256.0) * (1.0 / p + 0.08);
+        const double c = std::ceil(bricks * p / cus) * (1.0 / p + 0.08);
         if (c < cost) {
             cost = c;
             best = p;
@@ -235,12 +232,15 @@ inline long long mesh_cost_max(long long N)
     return (long long)(((double)N * N / 4200.0 - 2.4 * N) / kMeshPairNs);
 }
 
+// The split of a system of N ions (dimensionless R, H) on a device of `cus`
+// compute units.  False: use the direct sum.
+//
 // r_c trades near pairs (r_c^3) against the grid (its nodes go as r_c^-3, the
 // convolutions as r_c^-4) and scales with the ion spacing: in units of
 // (27 / n)^(1/3), a step took 0.61 ms at 1.6, 0.65 at 1.68, 0.65 at 1.75 and
 // 0.66 at 1.82 for 2^17 ions; 1.11, 1.12, 1.14 and 1.10 for 2^18; 4.55, 4.44,
 // 4.28 and 4.39 for 2^20.
-inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
+inline bool mesh_plan(long long N, double R, double H, MeshArgs& a, int cus = 256)
 {
     const double diag = std::sqrt(4.0 * R * R + H * H);
     if (diag > 24.0 || N < 1024 || N > (1ll << 26)) return false;
@@ -263,8 +263,8 @@ inline bool mesh_plan(long long N, double R, double H, MeshArgs& a)
     a.nby = (a.ncy + kMeshG - 1) / kMeshG;
     a.nbz = (a.nc[2] + kMeshBz - 1) / kMeshBz;
     a.cost_max = mesh_cost_max(N);
-    a.parts = mesh_parts(a, 2);
-    a.gparts = mesh_parts(a, 3);
+    a.parts = mesh_parts(a, 2, cus);
+    a.gparts = mesh_parts(a, 3, cus);
     a.ng = std::max(a.n[0], a.n[2]) + 80;
 
     // As few Gaussians as fit to kMeshFit.  The fit's error of the acceleration,

@@ -193,9 +193,9 @@ constexpr int64_t kMeshMinN = 40960;
 
 // Whether a system's pair sum is split into near pairs and a far part on a
 // grid (mesh.hpp); plans it.
-bool plan_mesh(int prec, const odk::PairArgs& pa, const odk::PushArgs& pu, odk::MeshArgs& m)
+bool plan_mesh(int prec, const odk::PairArgs& pa, const odk::PushArgs& pu, int cus, odk::MeshArgs& m)
 {
-    return prec == OD_PREC_FP32 && pa.N >= kMeshMinN && pa.ion_ion && odk::mesh_plan(pa.N, pu.R, pu.H, m);
+    return prec == OD_PREC_FP32 && pa.N >= kMeshMinN && pa.ion_ion && odk::mesh_plan(pa.N, pu.R, pu.H, m, cus);
 }
 
 void free_mesh(od_system* s)
@@ -928,7 +928,7 @@ od_status od_init_system(const od_plasma* plasma, const od_sim* sim, const od_du
         return fail(OD_EDEVICE, "init kernel launch failed: %s", hipGetErrorString(e));
     }
     // while the device draws the initial state
-    s->mesh_planned = plan_mesh(s->prec, s->pa, s->pu, s->ma) ? 1 : -1;
+    s->mesh_planned = plan_mesh(s->prec, s->pa, s->pu, s->cus, s->ma) ? 1 : -1;
     if (s->prec == OD_PREC_FP64) st = setup_sym64(s, roomy ? base + at[6] : nullptr);
     if (st == OD_OK) st = read_status(s);
     if (st == OD_OK && (sim->flags & OD_FLAG_CONFINEMENT)) {

@@ -1,4 +1,5 @@
-"""The near / far split's error does not grow with the number of ions."""
+"""The plans of the near / far split: an error that does not grow with the number
+of ions, and blocks per brick within their range."""
 import os
 import subprocess
 
@@ -10,10 +11,11 @@ from tests.gpu_util import accel_errors, say
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_fit_of_every_plan(tmp_path):
-    exe = str(tmp_path / "mesh_fit_check")
+@pytest.mark.parametrize("check", ["mesh_fit_check", "mesh_parts_check"])
+def test_every_plan(tmp_path, check):
+    exe = str(tmp_path / check)
     subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-o", exe,
-                           os.path.join(ROOT, "tests", "mesh_fit_check.cpp")])
+                           os.path.join(ROOT, "tests", check + ".cpp")])
     out = subprocess.run([exe], capture_output=True, text=True, timeout=300)
     assert out.returncode == 0, out.stdout
 
