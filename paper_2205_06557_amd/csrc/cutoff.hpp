@@ -36,7 +36,7 @@ namespace odk {
 constexpr int kMaxSlabs = 1024;
 
 struct CutArgs {
-    int nslab;        // slabs that od_get_cutoff_info reports
+    int nslab;        // slabs that od_get_cutoff_info counts in
     int nblk;         // blocks of 256 ions
     int reach;        // slabs on either side that can hold a source within r_cut
     int nlay, lreach; // sort layers along z; layers above that can hold one
