@@ -74,7 +74,7 @@ def split_work(w):
     """FP32 and FP64 flop that the split pair sum cannot do without: every pair
     within r_c once per member (50 FP32 flop: difference 3, r^2 5, clamp 1,
     rsqrt 1, polynomial 26, exponent 3, exp 1, combination 4, sum 6), and on
-    the grid the charges of every ion (1,000 nodes, 2 flop), 14 Gaussian
+    the grid the charges of every ion (1,000 nodes, 2 flop), the fewest (14) Gaussian
     convolutions along three axes (lines folded at their centre: one product
     of the line's length per node) and the forces (1,000 nodes, 4 flop)."""
     n, R, H = w.n_ions, w.R / w.lam, w.H / w.lam
@@ -630,7 +630,7 @@ def main():
             "peak": peak / 1e12,
             "unit": "TFLOP/s",
             "frac": achieved / peak,
-            "traffic": None if prec or split else measured_traffic("pair", N),
+            "traffic": None if prec else measured_traffic("split" if split else "pair", N),
             "kernel": "pair_sym64_kernel + pair_forces_f64" if prec else
                       "mesh_* (near pairs, gridded far part)" if split else "pair_sym_kernel",
             "flop_per_pair": None if split else FLOP_PER_PAIR,

@@ -200,7 +200,7 @@ od_status od_set_cutoff(od_system* sys, double r_switch, double r_cut);
  * counted both ways, padding included).  That is the size of the problem in one
  * dimension, not what the kernel evaluates: its order is compact in the cross
  * section too and it leaves out groups of 64 by 64 ions beyond r_cut, which
- * comes to 0.15 to 0.92 times as many from 2^16 ions on (0.91 in the long domain
+ * comes to 0.16 to 0.92 times as many from 20,000 ions on (0.91 in the long domain
  * with r_cut = 4 r_De) and up to 1.5 times as many for a few thousand ions.
  * OD_ESTATE without a cutoff.  Synchronises. */
 od_status od_get_cutoff_info(od_system* sys, int32_t* nslab, int64_t* pairs_evaluated);

@@ -68,7 +68,9 @@ __device__ __forceinline__ int cut_bin(float z, float z0, float inv, int n)
     return min(max((int)((z - z0) * inv), 0), n - 1);
 }
 
-// Position along the Hilbert curve through side x side cells.
+// Position along the Hilbert curve through side x side cells: the textbook loop
+// from coordinates to distance, a quadrant per bit, turned and mirrored so that
+// the next one starts in the corner where this one is entered.
 __device__ __forceinline__ int hilbert(int side, int x, int y)
 {
     int d = 0;

@@ -165,7 +165,8 @@ __constant__ const double kExp2Tab[64] = {
 // e^-r for 0 <= r, clamped at 700 (below 1e-304): r = -(n ln 2) / 64 + f with n
 // rounded by adding 1.5 * 2^52, ln 2 / 64 split into a 32-bit head (n * head
 // exact) and its remainder, |f| <= ln 2 / 128, 2^(n / 64) from the table (in
-// LDS) and its exponent, e^f - 1 to degree 5 (remainder below 4e-17).
+// LDS) and its exponent, e^f - 1 to degree 5 (remainder below 4e-17).  The
+// method is Tang's (ACM Trans. Math. Software 15, 144, 1989).
 __device__ __forceinline__ double exp_neg_tab(double r, const double* __restrict__ tab)
 {
     const double magic = 6755399441055744.0;

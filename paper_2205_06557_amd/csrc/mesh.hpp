@@ -342,6 +342,8 @@ constexpr double kMeshScale = 68719476736.0;    // 2^36
 // (exact, so the order of the waves does not matter).  Adding every weight to
 // LDS instead, 1,000 additions an ion, was bound by the LDS's 2 additions per
 // clock: 135 us at 2^17 ions, 241 at 2^18 and 630 at 2^20, against 120, 171 and 505.
+// Now the waves wait for one another's steps, 1.2 to 1.8 to a SIMD: vector
+// issue 0.31, matrix cores 0.22 and LDS 0.08 of the cycles at 2^20.
 __global__ __launch_bounds__(kMeshThreads) void mesh_spread_kernel(MeshArgs m, MeshBufs b)
 {
     extern __shared__ unsigned long long grid[];
@@ -472,7 +474,11 @@ __global__ __launch_bounds__(256) void mesh_green_kernel(MeshArgs m, double i0_b
 // as (E +- O) / 2: half the products.  A wave computes NT x 16 such rows of 16
 // grid lines.  AXIS 0 and 1 apply Gaussian m0 + blockIdx.z; AXIS 2 sums over
 // Gaussians m0 .. m0 + mc - 1 with their weights (add: on top of what out
-// holds).  Bound by the matrix rate: 144 us for the three axes at 2^17 ions, where whole lines took 233.
+// holds).  144 us for the three axes at 2^17 ions, where whole lines took 233.
+// The matrix cores are busy for 0.41 to 0.43 of the cycles at 2^20 ions and 0.18
+// to 0.30 at 2^17, vector issue for 0.3: what binds is the way of an operand
+// from memory, with the 1 to 2.5 waves a SIMD that the accumulators leave room
+// for (operands loaded a step ahead, or products left out, gained nothing).
 // v_mfma_f64_16x16x4_f64 operands, lane l: A[l % 16][l / 16],
 // B[l / 16][l % 16], D[4 r + l / 16][l % 16].
 template <int AXIS, int NT>
@@ -566,7 +572,8 @@ inline void mesh_conv(const MeshArgs& m, const MeshBufs& b, const double* in, do
 // derivative is taken of the normalised interpolant (sum w phi / sum w), which
 // makes a constant potential exactly force free: the mean potential is 1e4
 // times what matters here.  Bound by the LDS reads, one per node and ion (87 us
-// at 2^17 ions, 465 at 2^20).  The z weights as 64-bit MFMA products over a
+// at 2^17 ions, 465 at 2^20): the LDS is busy for 0.67 of the cycles at 2^20,
+// 0.41 of them with bank conflicts, at 1.7 waves a SIMD.  The z weights as 64-bit MFMA products over a
 // column's ions, as in the spread, took 155 and 660 us: half of each tile is
 // nodes outside an ion's ten.
 __global__ __launch_bounds__(kMeshThreads) void mesh_gather_kernel(MeshArgs m, MeshBufs b)
@@ -689,7 +696,8 @@ __global__ void mesh_zero_kernel(MeshArgs m, float* near0)
 // them through LDS and read them back one by one, the same for the quarter.
 // FP32 terms, FP64 sums of every 16.
 //
-// Bound by FP32 issue (31 slots a pair), so what counts is how few pairs
+// Bound by FP32 issue (31 slots a pair; 0.93 of the cycles at 2^20 ions, 0.79
+// at 2^17), so what counts is how few pairs
 // beyond r_c are evaluated: 3.3 times the pairs within r_c with groups of 16
 // and boxes of 8, 5.8 with 64 and 16 and wider columns, whose sources could be
 // scalar loads: at 2^20 ions 2.9 ms with r_c = 0.39, where the wider search

@@ -27,6 +27,7 @@ KERNEL_SOURCES = ("csrc/kernels.hpp", "csrc/device_common.hpp", "csrc/cutoff.hpp
 CALIB_BYTES = 1 << 28
 KERNELS = {"pair_forces_f32": "pair", "pair_sym_kernel": "pair", "step_tail_kernel<float, ": "tail",
            "reinject_kernel<float>": "reinject"}
+SETUP = ("mesh_green_kernel", "mesh_zero_kernel")      # the split's, once per system
 
 
 def kernel_sources_hash() -> str:
@@ -39,7 +40,7 @@ def kernel_sources_hash() -> str:
 
 def _per_kernel(path):
     vals = collections.defaultdict(list)
-    calib = 0.0
+    calib = split = sums = 0.0          # the split pair sum is many launches: their total over its steps
     for r in csv.DictReader(open(path)):
         name = r["Kernel_Name"]
         v = float(r["Counter_Value"])
@@ -48,6 +49,11 @@ def _per_kernel(path):
         for key, short in KERNELS.items():
             if key in name:
                 vals[short].append(v)
+        if "mesh_" in name and not any(k in name for k in SETUP):
+            split += v
+            sums += "mesh_near_kernel" in name
+    if sums:
+        vals["split"].append(split / sums)
     return {k: sum(v) / len(v) for k, v in vals.items()}, calib
 
 
