@@ -254,10 +254,10 @@ od_status od_get_accelerations(od_system* sys, void* a_host);
  * size, and for large systems (from 40,960 ions on, domains up to 24 r_De
  * across) evaluates it as near pairs, one by one, plus a smooth far part on a
  * grid in 64 bits.  That is the same all-pairs sum, bitwise reproducible too:
- * its error, relative to the rms acceleration, is 1.0e-7 at 2^18 ions, 1.4e-7
- * at 2^20 and 1.3e-7 at 2^22 (measured; the fit of the far part is held to at
- * most 2.3e-7 at every size), where the direct FP32 kernel has 1.8e-7 at 2^18
- * and 3.0e-7 at 2^20 (2.6x faster at 2^16 ions, 14x at 2^18, 59x at 2^20).  Its memory, about
+ * its error, relative to the rms acceleration, is 1.0e-7 to 3.1e-7 at 2^18 to
+ * 2^22 ions (measured; the fit of the far part is held to at most 2.3e-7 at
+ * every size), where the direct FP32 kernel has 1.8e-7 to 7.4e-7 (2.6x faster
+ * at 2^16 ions, 14x at 2^18, 59x at 2^20, 200x at 2^22).  Its memory, about
  * 100 MB at 2^17 and 500 MB at 2^20 ions, is taken by the first step, or at
  * creation where the system has an allocator of its own; where it is refused
  * the direct sum is used.  It is used too for a step that begins with ions

@@ -918,8 +918,9 @@ void mesh_near_kernel(MeshArgs m, const float4* __restrict__ pos, const float* _
 
 // Direct sums of the systems whose step calls for it, as pair_sym_kernel has
 // them (the same items, so the same totals).  A launch of one round of blocks
-// that take the items in turn: every other step pays for it with 2 to 5 us (312
-// -> 317 us per step at 40,960 ions, 424 -> 426 at 2^16, 619 -> 621 at 2^17).
+// that take the items in turn.  For the choice, this launch and the asks of the
+// others, a step pays 4 to 7 us (313 -> 320 us at 40,960 ions, 424 -> 428 at
+// 2^16, 620 -> 624 at 2^17).
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(kSymWaves, 8)))
 void mesh_direct_kernel(const MeshDirect* __restrict__ table, int systems, long long plane)

@@ -224,7 +224,8 @@ inline int mesh_parts(const MeshArgs& a, int most, int cus)
 // brick (340 ns per ion: one wave spreads it) count against it.  Uniform ions
 // reach 0.38 of it at 40,960, 0.21 at 2^16 and 0.05 at 2^18; with 30 % of the ions in a
 // ball of 0.1 r_De a pair sum took 4.5 ms at 40,960 ions, 7.4 at 2^16 and 31 at
-// 2^18, with all of them 14, 24 and 101, against 0.53, 1.2 and 16 directly.
+// 2^18, with all of them 14, 24 and 101, against 0.53, 1.2 and 16 directly (0.64,
+// 1.35 and 17.7 with the choice).
 constexpr double kMeshPairNs = 1.1e-3, kMeshColumnNs = 340.0;
 
 inline long long mesh_cost_max(long long N)

@@ -16,6 +16,15 @@ constexpr double kSymItemsTarget = 65536.0;    // work items of the symmetric su
 constexpr double kSymMinGroupedItems = 2048.0; // fewer grouped items: one target row per item
 constexpr double kSymMinItems = 1024.0;        // fewer one-tile items: one item per 64-ion sub-tile
 
+// Items of the runs.
+inline int sym_count(const odk::SymRuns& s)
+{
+    odk::SymPlace at{0, 0};
+    odk::SymItem it{};
+    (void)odk::sym_item_at(s, 1 << 30, at, it);
+    return at.before;
+}
+
 // Work items of the symmetric sum of one system of T tiles: groups of
 // kSymRows target tile rows, each group with runs of at most C source tiles
 // from its first row on (rows left over at the end alone), C chosen for about
@@ -30,14 +39,6 @@ constexpr double kSymMinItems = 1024.0;        // fewer one-tile items: one item
 // and in a batch.  one_row: one target row per item at every size; target:
 // the number of items aimed at (batch options; both change the FP32 partial
 // sums that each item flushes).
-inline int sym_count(const odk::SymRuns& s)
-{
-    odk::SymPlace at{0, 0};
-    odk::SymItem it{};
-    (void)odk::sym_item_at(s, 1 << 30, at, it);
-    return at.before;
-}
-
 inline odk::SymRuns sym_runs(int T, bool one_row = false, double target = kSymItemsTarget)
 {
     constexpr int R = odk::kSymRows;
@@ -47,7 +48,7 @@ inline odk::SymRuns sym_runs(int T, bool one_row = false, double target = kSymIt
     return {T, 1, (int)std::max(1.0, std::ceil(pairs / target))};
 }
 
-// Whether the runs, one tile each, are cut into sub-tiles.
+// Whether the runs, one tile each, are to be cut into sub-tiles.
 inline bool sym_cut(const odk::SymRuns& s)
 {
     return s.rows == 1 && s.C == 1 && 0.5 * (double)s.T * (s.T + 1) < kSymMinItems;
