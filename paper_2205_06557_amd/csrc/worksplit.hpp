@@ -59,6 +59,7 @@ std::vector<odk::SymItem> sym_items_of(int T, bool one_row = false, double targe
     const odk::SymRuns runs = sym_runs(T, one_row, target);
     const bool sub = sym_cut(runs);
     std::vector<odk::SymItem> v;
+    v.reserve((size_t)sym_count(runs) * (sub ? 4 : 1));
     odk::SymPlace at{0, 0};
     odk::SymItem it{};
     for (int k = 0; odk::sym_item_at(runs, k, at, it); ++k)
@@ -80,14 +81,20 @@ inline long long sym_item_cost(int rows, int J0, int J1, int st0, int st1)
 }
 inline long long sym_item_cost(const odk::SymItem& a) { return sym_item_cost(a.rows, a.J0, a.J1, a.st0, a.st1); }
 
-// Longest items first, so that the short ones fill the tail.
+// Longest items first, so that the short ones fill the tail; items of one
+// length in their order.  By counting, since creating a system waits for it
+// (28,000 ions: 0.3 ms with a comparison sort).
 std::vector<odk::SymItem> sym_items(int T)
 {
-    std::vector<odk::SymItem> v = sym_items_of(T);
-    std::stable_sort(v.begin(), v.end(), [](const odk::SymItem& a, const odk::SymItem& b) {
-        return sym_item_cost(a) > sym_item_cost(b);
-    });
-    return v;
+    const std::vector<odk::SymItem> v = sym_items_of(T);
+    long long most = 0;
+    for (const odk::SymItem& q : v) most = std::max(most, sym_item_cost(q));
+    std::vector<size_t> at((size_t)most + 2, 0);        // at[k]: items longer than most - k
+    for (const odk::SymItem& q : v) ++at[(size_t)(most - sym_item_cost(q)) + 1];
+    for (size_t k = 1; k < at.size(); ++k) at[k] += at[k - 1];
+    std::vector<odk::SymItem> o(v.size());
+    for (const odk::SymItem& q : v) o[at[(size_t)(most - sym_item_cost(q))]++] = q;
+    return o;
 }
 
 }  // namespace
